@@ -72,41 +72,6 @@ __device__ __forceinline__ float act_fn(float z) {
   }
 }
 
-struct Tile {
-  int e, r0, rows, n0;
-};
-
-// Logical tile L -> (group, first row, row count, first column); e = -1 if
-// this block has no tile.  Tiles per group: ceil(cnt_e / TM) * NT.
-template <int TM>
-__device__ Tile decode_tile(const int32_t* __restrict__ off, int G, int NT) {
-  int total = 0;
-  for (int e = 0; e < G; ++e) total += ((off[e + 1] - off[e] + TM - 1) / TM) * NT;
-  const int per = (total + kXcds - 1) / kXcds;
-  const int xcd = blockIdx.x % kXcds;
-  const int slot = blockIdx.x / kXcds;
-  const int L = xcd * per + slot;
-  Tile t{-1, 0, 0, 0};
-  if (slot >= per || L >= total) return t;
-  int acc = 0;
-  for (int e = 0; e < G; ++e) {
-    const int cnt = off[e + 1] - off[e];
-    const int mt = (cnt + TM - 1) / TM;
-    const int tiles = mt * NT;
-    if (L < acc + tiles) {
-      const int local = L - acc;
-      const int m = local % mt;
-      t.e = e;
-      t.r0 = off[e] + m * TM;
-      t.rows = min(TM, cnt - m * TM);
-      t.n0 = (local / mt);
-      return t;
-    }
-    acc += tiles;
-  }
-  return t;
-}
-
 // Group of logical tile L: the number of group tile prefixes <= L, minus
 // one, from two ballots (groups 0-63 in toff0, 64-127 in toff1: lane l holds
 // the prefixes of groups l and 64 + l, INT_MAX past the last group); also
@@ -1173,95 +1138,259 @@ __global__ __launch_bounds__(256) void reduce_partials_kernel(
 }
 
 // ---------------------------------------------------------------------------
-// fp32 grouped GEMM (fp32 layers): 64 x 64 block tile (token rows by output
-// columns), 16-wide k-steps through LDS, four waves of 32 x 32 on the fp32
-// matrix cores (v_mfma_f32_32x32x2_f32, fp32 products accumulated in fp32).
+// fp32 grouped GEMM (fp32 layers) on the fp32 matrix cores
+// (v_mfma_f32_16x16x4_f32, fp32 products accumulated in fp32).
+//
+// At the sizes fp32 layers run (tens to a few hundred rows per expert) the
+// weights are the stream: every weight byte feeds one tile, and below about
+// 60 rows per expert the launch is bound by how fast the CUs pull them in,
+// above that by the fp32 MFMA rate.  A tile is therefore up to 128 rows of an
+// expert (more are split into equal parts) by 64 output columns: four waves,
+// each 16 columns (weights, the A operand) by all of the tile's 16-row tiles
+// (token rows, the B operand), so that every wave has the same work whatever
+// the row count and rows cost MFMAs in steps of 16.  A lane holds four
+// consecutive output columns of one row.  The operands sit in LDS as 128-byte
+// rows of 32 floats with the large kernel's XOR-swizzled 16-byte chunks,
+// filled by direct global -> LDS loads into a ring of 48 KB: two stages of
+// up to 128 rows, three of up to 64 or four of up to 32, so that short tiles
+// keep more k-tiles in flight.  Three blocks share a CU: with few stages it
+// is the other blocks that cover a block's wait (two blocks with 72 KB were
+// 6 % slower on the weight stream).  One ds_read_b128 serves four MFMAs: MFMA
+// j of a step takes element j of every lane's 16 bytes, the same k in both
+// operands.  Loads of row groups past the tile's rows are skipped.  Units
+// are dealt to the XCDs in runs of eight (one expert's columns): experts
+// differ by tens of percent in rows, and contiguous ranges left the XCD of
+// the two fullest experts behind (204 against 191 us on a full step).  The
+// down projection may split K into `split` pieces (units), whose
+// partial sums go to part[piece][row][column] and are added in piece order
+// by reduce_partials_f32_kernel, so that layers with few output columns
+// still give every CU work.
+//
+// Measured at 2 x 333 tokens, 16 experts of 1152 x 4608, top-2 (340 MB of
+// weights per launch; the earlier kernel: 64 x 64 tiles, 16-wide k steps,
+// one LDS buffer, no loads in flight during the MFMAs): up 125 -> 74 us on
+// cache steps (25 rows per expert: 4.6 TB/s) and 217 -> 191 us on full ones
+// (83 rows: 74 TFLOP/s), down 246 -> 74 + 5 us and 325 -> 193 + 7 us; at 256
+// tokens, 8 experts of 384 x 1536: up 22 -> 18 us, down 55 -> 16 + 4 us.
 // ---------------------------------------------------------------------------
-constexpr int kF32T = 64;
-constexpr int kF32K = 16;
+constexpr int kF32TM = 128;
+constexpr int kF32TN = 64;
+constexpr int kF32K = 32;  // floats: 128-byte rows
+constexpr int kF32Waves = 4;
+constexpr int kF32Threads = kF32Waves * kWave;
+constexpr int kF32LdsBytes = 2 * (kF32TM + kF32TN) * kF32K * 4;  // 48 KB
+constexpr int kF32Blocks = 3;  // per CU
+constexpr int kF32Run = 8;     // consecutive units dealt to one XCD
+constexpr int kF32LoadsA = kF32TM / 8 / kF32Waves;               // 4 per wave, fewer with few rows
+constexpr int kF32LoadsB = kF32TN / 8 / kF32Waves;               // 2
+static_assert(kF32TN == 16 * kF32Waves, "a wave takes 16 columns");
 
 template <int KIND, int ACT>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(
+__global__ __launch_bounds__(kF32Threads, kF32Blocks) void gemm_f32_kernel(
     const float* __restrict__ A, const float* __restrict__ W, const float* __restrict__ Wsh,
-    const int32_t* __restrict__ off, const int32_t* __restrict__ list,
-    const int32_t* __restrict__ row_dst, int E, int G, int k, int K, int Nout,
-    float* __restrict__ dst, float* __restrict__ dst_sh) {
+    const int32_t* __restrict__ off, const int32_t* __restrict__ tile_off,
+    const int32_t* __restrict__ list, const int32_t* __restrict__ row_dst, int E, int G, int k,
+    int K, int Nout, int split, int64_t part_rows, float* __restrict__ dst,
+    float* __restrict__ dst_sh, float* __restrict__ part) {
   constexpr bool kGated = ACT == kActSwiglu;
-  __shared__ float As[kF32K][kF32T + 4];  // token rows, k-major
-  __shared__ float Bs[kF32K][kF32T + 4];  // weight rows, k-major
-  __shared__ int s_src[kF32T];
-  __shared__ int s_dst[kF32T];
-  __shared__ int s_tile[4];
+  __shared__ __attribute__((aligned(16))) float lds[kF32LdsBytes / 4];
   const int tid = threadIdx.x;
-  if (tid == 0) {
-    const Tile t = decode_tile<kF32T>(off, G, Nout / kF32T);
-    s_tile[0] = t.e;
-    s_tile[1] = t.r0;
-    s_tile[2] = t.rows;
-    s_tile[3] = t.n0 * kF32T;
-  }
-  __syncthreads();
-  const int e = s_tile[0];
-  if (e < 0) return;
-  const int r0 = s_tile[1], rows = s_tile[2], n0 = s_tile[3];
-  if (tid < kF32T) group_row<KIND>(e, E, r0, rows, tid, k, off, list, row_dst, s_src[tid], s_dst[tid]);
-  __syncthreads();
-  // tile loads: thread -> row lr, k columns lk .. lk + 3 of the 16-wide k-step
-  const int lr = tid >> 2, lk = (tid & 3) * 4;
-  const float* Wg = e < E ? W + int64_t(e) * Nout * K : Wsh + int64_t(e - E) * Nout * K;
-  float* const og = e < E ? dst : dst_sh;
-  const float* ap = A + int64_t(s_src[lr]) * K + lk;
-  const float* bp = Wg + int64_t(n0 + lr) * K + lk;
-  // MFMA: wave w computes outputs 32 (w & 1) .. + 31 (weights, the A operand)
-  // by tokens 32 (w >> 1) .. + 31 (the B operand) with v_mfma_f32_32x32x2_f32;
-  // lane l supplies output / token (l & 31) at k-row l >> 5 of each 2-wide
-  // k-step and holds D[8 (v / 4) + 4 (l >> 5) + v % 4][l & 31] in acc[v]:
-  // four consecutive outputs of one token per group v / 4
-  const int lane = tid & 63, wv = tid >> 6;
-  const int wo = (wv & 1) * 32, wt = (wv >> 1) * 32;
-  const int lc = lane & 31, lh = lane >> 5;
-  typedef __attribute__((ext_vector_type(16))) float f32x16_v;
-  f32x16_v acc;
+  const int lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int total = tile_off[G];
+  const int xcd = blockIdx.x % kXcds;
+  constexpr int kDeal = kXcds * kF32Run;
+  const int nidx = (total + kDeal - 1) / kDeal * kF32Run;  // units dealt to an XCD, at most
+  const int stride = gridDim.x / kXcds;
+  const int toff0 = lane < G ? tile_off[lane] : 0x7fffffff;
+  const int toff1 = lane + 64 < G ? tile_off[lane + 64] : 0x7fffffff;
+  const int KT = K / kF32K;
+  const int NT = Nout / kF32TN;
+  // stored chunk position: chunk ^ ((row >> 1) & 7) with row = 8 i + lane / 8
+  // and i = wv + 4 u (the parity of wv), as in the large kernel
+  const int chunk = (lane & 7) ^ (4 * (wv & 1) + (lane >> 4));
+  const uint32_t lds0 = __builtin_amdgcn_readfirstlane(lds_addr(lds) + wv * 1024);
+
+  for (int idx = static_cast<int>(blockIdx.x) / kXcds; idx < nidx; idx += stride) {
+    const int L = (idx / kF32Run * kXcds + xcd) * kF32Run + idx % kF32Run;
+    if (L >= total) continue;
+    int e_base;
+    const int e = __builtin_amdgcn_readfirstlane(tile_group(L, toff0, toff1, e_base));
+    const int o0 = off[e];
+    const int cnt = off[e + 1] - o0;
+    const int mt = (cnt + kF32TM - 1) / kF32TM;
+    const int local = __builtin_amdgcn_readfirstlane(L - e_base);
+    const int m = local % mt;
+    const int rest = local / mt;
+    // part m of mt equal parts of the expert's rows (at most kF32TM each)
+    const int r0 = __builtin_amdgcn_readfirstlane(o0 + static_cast<int>(int64_t(m) * cnt / mt));
+    const int rows =
+        __builtin_amdgcn_readfirstlane(o0 + static_cast<int>(int64_t(m + 1) * cnt / mt) - r0);
+    const int ks = __builtin_amdgcn_readfirstlane(rest / NT);
+    const int n0 = __builtin_amdgcn_readfirstlane((rest % NT) * kF32TN);
+    const int kt0 = ks * KT / split, kt1 = (ks + 1) * KT / split;
+    const float* Wg = e < E ? W + int64_t(e) * Nout * K : Wsh + int64_t(e - E) * Nout * K;
+    float* const og = e < E ? dst : dst_sh;
+
+    // this lane's loads; instructions whose eight rows all lie past the
+    // tile are skipped, single rows past it re-read its first row
+    const float* ga[kF32LoadsA];
+    const float* gb[kF32LoadsB];
+    int na = 0;  // token-row instructions of this wave (wave-uniform)
 #pragma unroll
-  for (int v = 0; v < 16; ++v) acc[v] = 0.0f;
-  for (int k0 = 0; k0 < K; k0 += kF32K) {
-    const float4 va = *reinterpret_cast<const float4*>(ap + k0);
-    const float4 vb = *reinterpret_cast<const float4*>(bp + k0);
-    As[lk + 0][lr] = va.x;
-    As[lk + 1][lr] = va.y;
-    As[lk + 2][lr] = va.z;
-    As[lk + 3][lr] = va.w;
-    Bs[lk + 0][lr] = vb.x;
-    Bs[lk + 1][lr] = vb.y;
-    Bs[lk + 2][lr] = vb.z;
-    Bs[lk + 3][lr] = vb.w;
-    __syncthreads();
+    for (int u = 0; u < kF32LoadsA; ++u) {
+      const int i = wv + kF32Waves * u;
+      int src = 0, dr = -1;
+      if (8 * i < rows) {
+        group_row<KIND>(e, E, r0, rows, 8 * i + (lane >> 3), k, off, list, row_dst, src, dr);
+        na = u + 1;
+      }
+      ga[u] = A + int64_t(src) * K + chunk * 4;
+    }
 #pragma unroll
-    for (int kk = 0; kk < kF32K; kk += 2)
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(Bs[kk + lh][wo + lc], As[kk + lh][wt + lc], acc,
-                                                 0, 0, 0);
-    __syncthreads();
-  }
-  const int drow = s_dst[wt + lc];
-  if (drow < 0) return;
+    for (int u = 0; u < kF32LoadsB; ++u)
+      gb[u] = Wg + int64_t(n0 + 8 * (wv + kF32Waves * u) + (lane >> 3)) * K + chunk * 4;
+    const bool once = mt == 1;  // no other tile reads these weights
+    // the p-th of this wave's loads of k-tile kt (weight rows, then token
+    // rows) into the stage at `base` (bytes; weight rows at tile_a)
+    auto issue_one = [&](int kt, uint32_t base, uint32_t tile_a, int p)
+        __attribute__((always_inline)) {
+      if (p < kF32LoadsB) {
+        const auto* g = reinterpret_cast<const uint16_t*>(gb[p] + kt * kF32K);
+        const uint32_t at = base + tile_a + p * kF32Waves * 1024;
+        if (once) dma16_nt(g, at);
+        else dma16(g, at);
+      } else if (p - kF32LoadsB < na) {
+        dma16(reinterpret_cast<const uint16_t*>(ga[p - kF32LoadsB] + kt * kF32K),
+              base + (p - kF32LoadsB) * kF32Waves * 1024);
+      }
+    };
+
+    // The tile for NR 16-row tiles: k-loop and epilogue, one instantiation
+    // per NR so that the accumulators stay in fixed registers.
+    auto run = [&](auto nr_c) __attribute__((always_inline)) {
+      constexpr int NR = decltype(nr_c)::value;
+      f32x4_t acc[NR];
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int c = n0 + wo + 8 * q + 4 * lh;  // outputs c .. c + 3
-    if constexpr (kGated) {  // columns (gate, up, gate, up) -> two outputs
-      *reinterpret_cast<float2*>(og + int64_t(drow) * (Nout / 2) + c / 2) =
-          make_float2(silu_f(acc[4 * q]) * acc[4 * q + 1], silu_f(acc[4 * q + 2]) * acc[4 * q + 3]);
-    } else {
-      *reinterpret_cast<float4*>(og + int64_t(drow) * Nout + c) =
-          make_float4(act_fn<ACT>(acc[4 * q]), act_fn<ACT>(acc[4 * q + 1]),
-                      act_fn<ACT>(acc[4 * q + 2]), act_fn<ACT>(acc[4 * q + 3]));
+      for (int r = 0; r < NR; ++r) acc[r] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+      // ring of kStg stages of this many rows: kStg - 1 k-tiles in flight
+      constexpr int kRows = NR <= 2 ? 32 : NR <= 4 ? 64 : kF32TM;
+      constexpr int kStageB = (kRows + kF32TN) * kF32K * 4;  // bytes
+      constexpr int kStg = kF32LdsBytes / kStageB;           // 4, 3 or 2
+      constexpr int kMaxNa = (kRows / 8 + kF32Waves - 1) / kF32Waves;
+      // this wave's loads of the oldest stage in flight have landed once at
+      // most kStg - 2 later stages' (na + kF32LoadsB each) are outstanding
+      auto wait_stage = [&](bool tail) __attribute__((always_inline)) {
+        if (tail) {
+          wait_vmcnt<0>();
+          return;
+        }
+        constexpr int P = kStg - 2;
+        if (na == 0) wait_vmcnt<P * kF32LoadsB>();
+        else if (na == 1) wait_vmcnt<P * (kF32LoadsB + 1)>();
+        else if (kMaxNa >= 2 && na == 2) wait_vmcnt<P * (kF32LoadsB + (kMaxNa >= 2 ? 2 : 0))>();
+        else if (kMaxNa >= 3 && na == 3) wait_vmcnt<P * (kF32LoadsB + (kMaxNa >= 3 ? 3 : 0))>();
+        else wait_vmcnt<P * (kF32LoadsB + (kMaxNa >= 4 ? 4 : 0))>();
+      };
+      constexpr uint32_t kTileAB = kRows * kF32K * 4;
+#pragma unroll
+      for (int p = 0; p < kStg - 1; ++p)
+        if (kt0 + p < kt1)
+#pragma unroll
+          for (int u = 0; u < kF32LoadsB + kMaxNa; ++u)
+            issue_one(kt0 + p, lds0 + p * kStageB, kTileAB, u);
+      int st = 0;
+      for (int kt = kt0; kt < kt1; ++kt) {
+        // every wave's loads of this stage have landed after the barrier,
+        // and every wave is done with the stage refilled next
+        wait_stage(kt + kStg - 1 > kt1);
+        __builtin_amdgcn_s_barrier();
+        const bool more = kt + kStg - 1 < kt1;
+        const uint32_t nbase = lds0 + (st == 0 ? kStg - 1 : st - 1) * kStageB;
+        const float* xs = lds + st * (kStageB / 4);
+        const float* ws = xs + kRows * kF32K;
+        f32x4_t wb[2], xa[2][NR];
+#pragma unroll
+        for (int s2 = 0; s2 < 2; ++s2) {
+          const int c = 4 * s2 + (lane >> 4);  // logical 16-byte chunk of this lane
+          const int wrow = wv * 16 + (lane & 15);
+          wb[s2] = *reinterpret_cast<const f32x4_t*>(ws + (wrow * 8 + (c ^ ((wrow >> 1) & 7))) * 4);
+#pragma unroll
+          for (int r = 0; r < NR; ++r) {
+            const int row = 16 * r + (lane & 15);
+            xa[s2][r] =
+                *reinterpret_cast<const f32x4_t*>(xs + (row * 8 + (c ^ ((row >> 1) & 7))) * 4);
+          }
+        }
+        // the next loads go out one after each group of MFMAs: in one burst
+        // they hold the wave at the load queue, away from its MFMAs
+#pragma unroll
+        for (int s2 = 0; s2 < 2; ++s2)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+#pragma unroll
+            for (int r = 0; r < NR; ++r)
+              acc[r] = __builtin_amdgcn_mfma_f32_16x16x4f32(wb[s2][j], xa[s2][r][j], acc[r], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            const int q = 4 * s2 + j;
+            if (more && q < kF32LoadsB + kMaxNa) issue_one(kt + kStg - 1, nbase, kTileAB, q);
+          }
+        st = st == kStg - 1 ? 0 : st + 1;
+      }
+      __syncthreads();  // every wave done with the LDS before a next tile's loads
+
+      // lane: columns c .. c + 3 of row 16 r + (lane & 15)
+      const int c = n0 + 16 * wv + 4 * (lane >> 4);
+#pragma unroll
+      for (int r = 0; r < NR; ++r) {
+        const int row = 16 * r + (lane & 15);
+        if (row >= rows) continue;
+        const f32x4_t& a = acc[r];
+        if (KIND == kDown && split > 1) {
+          *reinterpret_cast<f32x4_t*>(part + (int64_t(ks) * part_rows + r0 + row) * Nout + c) = a;
+          continue;
+        }
+        int src, drow;
+        group_row<KIND>(e, E, r0, rows, row, k, off, list, row_dst, src, drow);
+        if constexpr (kGated) {  // columns (gate, up, gate, up) -> two outputs
+          *reinterpret_cast<float2*>(og + int64_t(drow) * (Nout / 2) + c / 2) =
+              make_float2(silu_f(a[0]) * a[1], silu_f(a[2]) * a[3]);
+        } else {
+          *reinterpret_cast<f32x4_t*>(og + int64_t(drow) * Nout + c) =
+              f32x4_t{act_fn<ACT>(a[0]), act_fn<ACT>(a[1]), act_fn<ACT>(a[2]), act_fn<ACT>(a[3])};
+        }
+      }
+    };
+    switch ((rows + 15) / 16) {
+      case 8: run(std::integral_constant<int, 8>{}); break;
+      case 7: run(std::integral_constant<int, 7>{}); break;
+      case 6: run(std::integral_constant<int, 6>{}); break;
+      case 5: run(std::integral_constant<int, 5>{}); break;
+      case 4: run(std::integral_constant<int, 4>{}); break;
+      case 3: run(std::integral_constant<int, 3>{}); break;
+      case 2: run(std::integral_constant<int, 2>{}); break;
+      default: run(std::integral_constant<int, 1>{}); break;
     }
   }
 }
 
-int max_tiles(const Shape& s, int TM, int NT) {
-  const int64_t mt = (s.mid_rows() + TM - 1) / TM + s.groups();
-  const int64_t g = mt * NT;
-  return static_cast<int>((g + kXcds - 1) / kXcds * kXcds);
+// h_c[row_dst[r]] = ((part[0][r] + part[1][r]) + ...) + part[split-1][r] for
+// the listed rows r < off[E], one thread per four columns.
+__global__ __launch_bounds__(256) void reduce_partials_f32_kernel(
+    const float* __restrict__ part, int64_t part_rows, const int32_t* __restrict__ off,
+    const int32_t* __restrict__ row_dst, int E, int d, int split, float* __restrict__ h_c) {
+  const int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x;
+  const int r = static_cast<int>(i / (d / 4)), g = static_cast<int>(i % (d / 4));
+  if (r >= off[E]) return;
+  const float* p = part + int64_t(r) * d + g * 4;
+  f32x4_t s = *reinterpret_cast<const f32x4_t*>(p);
+#pragma unroll 4
+  for (int q = 1; q < split; ++q) {
+    const f32x4_t v = *reinterpret_cast<const f32x4_t*>(p + int64_t(q) * part_rows * d);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) s[u] = __fadd_rn(s[u], v[u]);
+  }
+  *reinterpret_cast<f32x4_t*>(h_c + int64_t(row_dst[r]) * d + g * 4) = s;
 }
 
 constexpr int kBlocksPerCu = 2;
@@ -1342,10 +1471,27 @@ hipError_t launch_gemm(const Shape& s, const FfnPlan& plan, const void* A, const
           a, w, wsh, b.off, toff, b.list, b.row_dst, s.E, G, s.k, K, Nout, o, osh);
     }
   } else {
-    launch_kernel(&gemm_f32_kernel<KIND, ACT>, dim3(max_tiles(s, kF32T, Nout / kF32T)), dim3(256),
-        0, st, static_cast<const float*>(A), static_cast<const float*>(W),
-        static_cast<const float*>(Wsh), b.off, b.list, b.row_dst, s.E, G, s.k, K, Nout,
-        static_cast<float*>(dst), static_cast<float*>(dst_sh));
+    const int32_t* toff = b.tiles + (KIND == kUp ? 0 : G + 1);
+    const int split = KIND == kDown && b.part != nullptr ? plan.split_down : 1;
+    const int64_t rows = s.mid_rows();
+    // the stage's start event goes with the GEMM, its stop event with the
+    // addition of the partial sums
+    LaunchEvents ev = launch_events();
+    launch_events() = LaunchEvents{};
+    launch_kernel_ev(&gemm_f32_kernel<KIND, ACT>, dim3(device_cus() * kF32Blocks),
+                     dim3(kF32Threads), 0, st, ev.start, split > 1 ? nullptr : ev.stop,
+                     static_cast<const float*>(A), static_cast<const float*>(W),
+                     static_cast<const float*>(Wsh), b.off, toff, b.list, b.row_dst, s.E, G, s.k,
+                     K, Nout, split, rows, static_cast<float*>(dst), static_cast<float*>(dst_sh),
+                     b.part);
+    if (split > 1) {
+      const hipError_t e = hipGetLastError();
+      if (e != hipSuccess) return e;
+      launch_kernel_ev(&reduce_partials_f32_kernel,
+                       dim3(static_cast<unsigned>((s.branches() * (s.d / 4) + 255) / 256)),
+                       dim3(256), 0, st, nullptr, ev.stop, static_cast<const float*>(b.part), rows,
+                       b.off, b.row_dst, s.E, s.d, split, static_cast<float*>(b.h_c));
+    }
   }
   return hipGetLastError();
 }
@@ -1360,6 +1506,12 @@ FfnPlan ffn_plan(const Shape& s, bool thin, bool wide) {
   auto tn = [](int n) { return n >= 512 ? kBigTN : (n % 128 == 0 ? 128 : 64); };
   FfnPlan p;
   p.tm = p.tm_up = 128;
+  if (!s.bf16) {
+    static_assert(kF32TM == 128, "tm above");
+    p.tn_up = p.tn_down = kF32TN;
+    p.split_down = f32_split(s);
+    return p;
+  }
   if (thin && thin_capable(s)) {
     p.thin = true;
     p.tn_up = p.tn_down = kThinTN;
@@ -1374,6 +1526,21 @@ FfnPlan ffn_plan(const Shape& s, bool thin, bool wide) {
     p.tn_up = kWideTN;
   }
   return p;
+}
+
+// K pieces of an fp32 layer's down projection: as many (1, 2, 4 or 8) as it
+// takes to give every block slot a unit at the mean row count per expert,
+// each of at least 192 inputs, while the partial sums stay below 32 MB.
+int f32_split(const Shape& s) {
+  if (s.bf16 || s.S != 0) return 1;
+  const int64_t mt = std::max<int64_t>(1, (s.branches() / s.E + kF32TM - 1) / kF32TM);
+  const int64_t tiles = s.E * mt * (s.d / kF32TN);
+  int split = 1;
+  while (split < 8 && tiles * split < int64_t(device_cus()) * 4 &&
+         s.d_ff / (2 * split) >= 192 &&
+         2 * split * s.branches() * s.d * 4 <= (int64_t(32) << 20))
+    split *= 2;
+  return split;
 }
 
 bool wide_capable(const Shape& s) {

@@ -98,8 +98,9 @@ struct Buffers {
   int32_t* wide;    // [B][kWideWords] per-sample scratch of the multi-block decision path
   void* mid;        // [B*N*k + S*T][d_ff] FFN activation of listed and shared rows
   void* h_sh;       // [S][T][d] shared experts' outputs
-  float* part;      // [kThinSplit][B*N*k][d] fp32 partial sums of the down projection's
-                    // K pieces (layers that may take the weight-streaming plan)
+  float* part;      // [pieces][B*N*k][d] fp32 partial sums of the down projection's K
+                    // pieces: kThinSplit (layers that may take the weight-streaming
+                    // plan) or f32_split (fp32 layers); null: K is not split
 };
 
 // Tiling of the grouped expert FFN: M tile (rows of one expert), N tile of
@@ -127,6 +128,9 @@ constexpr int kThinRows = 112;
 // most this many branches per expert on average.
 constexpr int kWideRows = 320;
 FfnPlan ffn_plan(const Shape& s, bool thin = false, bool wide = false);
+// K pieces of an fp32 layer's down projection (1: not split).  Above 1 the
+// workspace holds `part`.
+int f32_split(const Shape& s);
 // Layers that may take the wide up projection: bf16, no shared experts,
 // ungated, d_ff a multiple of 144.
 bool wide_capable(const Shape& s);

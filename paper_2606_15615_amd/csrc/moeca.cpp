@@ -59,9 +59,7 @@ struct Layout {
 
 // external_mid: the FFN intermediate lives outside this workspace (the
 // blocks of a stack run one after another and share one).  partials: room
-// for the down projection's partial sums of the weight-streaming plan
-// (layers that can take it; not for the uncached forward of
-// moeca_forward_noalloc, which never does).
+// for the down projection's partial sums (layers that may split its K).
 Layout make_layout(const Shape& s, bool external_mid = false, bool partials = true) {
   const size_t nbr = static_cast<size_t>(s.branches());
   const size_t ntok = static_cast<size_t>(s.tokens());
@@ -95,9 +93,10 @@ Layout make_layout(const Shape& s, bool external_mid = false, bool partials = tr
   b[R_WIDE] = size_t(s.B) * moeca::kWideWords * 4;
   b[R_MID] = external_mid ? 0 : size_t(s.mid_rows()) * s.d_ff * act;
   b[R_H_SH] = size_t(s.S) * ntok * s.d * act;
-  b[R_PART] = partials && moeca::thin_capable(s)
-                  ? size_t(moeca::kThinSplit) * size_t(s.mid_rows()) * s.d * 4
-                  : 0;
+  const int pieces = !partials                   ? 1
+                     : moeca::thin_capable(s) ? moeca::kThinSplit
+                                              : moeca::f32_split(s);
+  b[R_PART] = pieces > 1 ? size_t(pieces) * size_t(s.mid_rows()) * s.d * 4 : 0;
   Layout L;
   size_t cur = 0;
   for (int i = 0; i < R_COUNT; ++i) {
@@ -317,7 +316,10 @@ int moeca_forward_noalloc(const moeca_layer* L, const void* x, int samples, void
     return fail(MOECA_E_INVAL, "samples must be in [1, " + std::to_string(L->shape.B) + "]");
   Shape s = L->shape;
   s.B = samples;
-  const Layout lay = make_layout(s, false, false);
+  // with the down projection's K pieces if they fit (fp32 layers; a bf16
+  // call never splits)
+  Layout lay = make_layout(s, false, !s.bf16);
+  if (lay.total > moeca::kNoallocScratchBytes) lay = make_layout(s, false, false);
   if (lay.total > moeca::kNoallocScratchBytes)
     return fail(MOECA_E_INVAL, "this call needs " + std::to_string(lay.total) +
                                    " bytes of scratch; the library's array holds " +
@@ -333,16 +335,18 @@ int moeca_forward_noalloc(const moeca_layer* L, const void* x, int samples, void
   const Buffers b = map_buffers(static_cast<char*>(base), lay, nullptr);
   const moeca_policy& p = L->pol;
   const auto st = static_cast<hipStream_t>(stream);
+  moeca::FfnPlan plan = moeca::ffn_plan(s);
+  if (b.part == nullptr) plan.split_down = 1;
   // the uncached layer: every branch recomputed, no statistic, no cache
   // metadata and no attention path (the MOECA_MODE_FULL step)
   if ((e = moeca::launch_router(s, x, L->W_r, L->b_r, p.norm_topk, p.beta, false, b, st)) ==
           hipSuccess &&
       (e = moeca::launch_decide(s, moeca::kSelFull, 0, p.lambda0, p.lambda1, p.lambda2, false,
                                 p.tau0, p.alpha, b, st)) == hipSuccess &&
-      (e = moeca::launch_lists(s, moeca::ffn_plan(s), b, st)) == hipSuccess &&
-      (e = moeca::launch_ffn_up(s, x, L->W_up, L->W_up_sh, p.act, moeca::ffn_plan(s), b, st)) ==
+      (e = moeca::launch_lists(s, plan, b, st)) == hipSuccess &&
+      (e = moeca::launch_ffn_up(s, x, L->W_up, L->W_up_sh, p.act, plan, b, st)) ==
           hipSuccess &&
-      (e = moeca::launch_ffn_down(s, L->W_down, L->W_down_sh, moeca::ffn_plan(s), b, st)) ==
+      (e = moeca::launch_ffn_down(s, L->W_down, L->W_down_sh, plan, b, st)) ==
           hipSuccess)
     e = moeca::launch_combine(s, 0, out, nullptr, nullptr, b, st);
   if (e != hipSuccess) return fail(MOECA_E_HIP, std::string("launch: ") + hipGetErrorString(e));

@@ -69,6 +69,21 @@ def test_unnormalised_gate_erf_gelu_and_bias():
     run_forced(S, 4, label="variants")
 
 
+@pytest.mark.parametrize("N,d_ff,ffn,n_shared", [
+    (1, 64, "gelu", 0), (16, 768, "gelu", 0), (17, 1536, "gelu", 0), (33, 832, "gelu", 0),
+    (64, 192, "swiglu", 0), (65, 768, "swiglu", 2), (128, 1600, "gelu", 0), (129, 384, "gelu", 1),
+    (257, 3072, "gelu", 0), (300, 128, "gelu", 0)])
+def test_fp32_tile_edges(N, d_ff, ffn, n_shared):
+    """One expert takes every token, so a full step's row count is N: the
+    edges of the fp32 GEMM's 16-row steps, its ring depths (32, 64, 128
+    rows), equal parts past 128 rows, and K pieces of the down projection
+    (d_ff from 384, uneven ones included; none with shared experts)."""
+    shape = LayerShape(d=192, E=1, k=1, d_ff=d_ff, B=1, N=N, dtype="fp32", ffn=ffn,
+                       n_shared=n_shared)
+    S = Setup(shape, mode="ratio", seed=21, T=3, ratio=0.4)
+    run_forced(S, 3, label=f"fp32 {N} {d_ff} {ffn} {n_shared}")
+
+
 WIDE = LayerShape(d=128, E=16, k=8, d_ff=128, B=2, N=1100, dtype="bf16")
 
 
