@@ -84,6 +84,21 @@ def test_fp32_tile_edges(N, d_ff, ffn, n_shared):
     run_forced(S, 3, label=f"fp32 {N} {d_ff} {ffn} {n_shared}")
 
 
+def test_erf_gelu_over_its_range():
+    """fp32 layer whose pre-activations cover [-9, 9]: one expert, W_up rows
+    scaled so that every range of the erf GELU polynomial is met, the clamp
+    past 6 included (tolerance 1e-4 of the largest output; the polynomial's
+    own error is 2.5e-7)."""
+    shape = LayerShape(d=64, E=1, k=1, d_ff=128, B=1, N=200, dtype="fp32")
+    S = Setup(shape, mode="full", seed=23, T=1, act="gelu_erf")
+    S.W.W_up *= np.float32(3.0)
+    S.dW[2].mul_(3.0)
+    S._bind()
+    z = O.to_f64(S.xs[0], "fp32").reshape(-1, 64) @ S.W.W_up[0].astype(np.float64).T
+    assert z.min() < -6.5 and z.max() > 6.5
+    run_forced(S, 1, label="erf range")
+
+
 WIDE = LayerShape(d=128, E=16, k=8, d_ff=128, B=2, N=1100, dtype="bf16")
 
 
