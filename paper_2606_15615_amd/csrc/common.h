@@ -88,6 +88,17 @@ __device__ __forceinline__ void dma16_s_nt(const void* base, uint32_t voff, uint
       : "memory", "m0");
 }
 
+// 4 bytes per lane: lane l lands at lds + 4 l.
+__device__ __forceinline__ void dma4(const void* g, uint32_t lds) {
+  asm volatile(
+      "s_mov_b32 m0, %0\n\t"
+      "s_nop 0\n\t"
+      "global_load_lds_dword %1, off"
+      :
+      : "s"(lds), "v"(g)
+      : "memory", "m0");
+}
+
 __device__ __forceinline__ uint32_t lds_addr(const void* p) {
   return static_cast<uint32_t>(
       reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) const void*)p));

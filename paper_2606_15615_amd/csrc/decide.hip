@@ -578,6 +578,34 @@ __device__ __forceinline__ void write_shared_groups(int32_t* __restrict__ off,
   }
 }
 
+// Rows of a tile (128, 192 or 256) for a launch of the 256-column GEMM with
+// nt column tiles: the count that makes rounds x cost of a tile least, a round
+// being one tile per CU.  t: this lane's expert's rows (lane < E, else 0); S
+// shared experts have T rows each.  Lane l looks at choice l % 4 for the
+// experts l / 4 + 16 i.  Wave-wide; every lane gets the result.
+__device__ __forceinline__ int tall_rows(int t, int E, int S, int T, int nt, int cus) {
+  const int lane = threadIdx.x & (kWave - 1);
+  const int c = min(lane & 3, 2);
+  auto parts = [&](int n) {
+    return c == 0 ? (n + 127) / 128 : c == 1 ? (n + 191) / 192 : (n + 255) / 256;
+  };
+  int mt = 0;
+  for (int i = 0; i < E; i += 16) {
+    const int n = __shfl(t, (lane >> 2) + i, kWave);  // 0 past the experts
+    mt += parts(n);
+  }
+#pragma unroll
+  for (int m = 4; m < kWave; m *= 2) mt += __shfl_xor(mt, m, kWave);
+  mt += S * parts(T);
+  const int rounds = (mt * nt + cus - 1) / cus;
+  // a tile's time per k-tile is about 160 + its rows (it loads 256 weight
+  // rows whatever its height)
+  const int cost = rounds * (160 + 128 + 64 * c);
+  const int c0 = __builtin_amdgcn_readlane(cost, 0), c1 = __builtin_amdgcn_readlane(cost, 1),
+            c2 = __builtin_amdgcn_readlane(cost, 2);
+  return c2 <= c1 && c2 <= c0 ? 256 : c1 <= c0 ? 192 : 128;
+}
+
 // ---------------------------------------------------------------------------
 // Per-expert lists of recomputed branches, ascending flat id within each
 // expert; one 1024-thread block per chunk of 1024 consecutive branches of a
@@ -592,7 +620,7 @@ __device__ __forceinline__ void write_shared_groups(int32_t* __restrict__ off,
 __global__ __launch_bounds__(kSelThreads) void lists_kernel(
     const uint8_t* __restrict__ mask, const int32_t* __restrict__ e_t,
     const int32_t* __restrict__ cnt_ch, int B, int N, int E, int S, int k, int tm_up, int tm,
-    int nt_up, int nt_down, const int32_t* __restrict__ sigma, int32_t* __restrict__ off,
+    int nt_up, int nt_down, int tall_up, int tall_down, int cus, const int32_t* __restrict__ sigma, int32_t* __restrict__ off,
     int32_t* __restrict__ tiles, int32_t* __restrict__ list, int32_t* __restrict__ pos,
     int32_t* __restrict__ row_dst) {
   __shared__ int s_part_tot[kSelThreads];
@@ -641,6 +669,8 @@ __global__ __launch_bounds__(kSelThreads) void lists_kernel(
         bf += s_part_bef[pp * E + lane];
       }
     }
+    if (tall_up) tm_up = tall_rows(lane < E ? t : 0, E, S, B * N, nt_up, cus);
+    if (tall_down) tm = tall_rows(lane < E ? t : 0, E, S, B * N, nt_down, cus);
     const int mt_up = (t + tm_up - 1) / tm_up;
     const int mt = (t + tm - 1) / tm;
     // inclusive scans over experts
@@ -654,8 +684,11 @@ __global__ __launch_bounds__(kSelThreads) void lists_kernel(
       off[lane] = o - t;
       tiles[lane] = tu - mt_up * nt_up;
       tiles[E + S + 1 + lane] = td - mt * nt_down;
-      if (lane == E - 1)
+      if (lane == E - 1) {
         write_shared_groups(off, tiles, E, S, B * N, tm_up, tm, nt_up, nt_down, o, tu, td);
+        tiles[2 * (E + S + 1)] = tm_up;
+        tiles[2 * (E + S + 1) + 1] = tm;
+      }
     }
   }
   int rk = 0;
@@ -1147,7 +1180,8 @@ hipError_t launch_lists(const Shape& s, const FfnPlan& plan, const Buffers& b, h
   const int rc_n = (nb + kSelThreads - 1) / kSelThreads;
   if (s.E > 64) return hipErrorInvalidValue;
   launch_kernel(&lists_kernel, dim3(s.B * rc_n), dim3(kSelThreads), 0, st, b.mask, b.e_t,
-                b.cnt_ch, s.B, s.N, s.E, s.S, s.k, plan.tm_up, plan.tm, nt_up, nt_down, b.sigma, b.off,
+                b.cnt_ch, s.B, s.N, s.E, s.S, s.k, plan.tm_up, plan.tm, nt_up, nt_down,
+                plan.tall_up ? 1 : 0, plan.tall_down ? 1 : 0, device_cus(), b.sigma, b.off,
                 b.tiles, b.list, b.pos, b.row_dst);
   return hipGetLastError();
 }

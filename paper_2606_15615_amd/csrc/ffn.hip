@@ -40,6 +40,7 @@ namespace {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
 typedef __attribute__((ext_vector_type(16))) float f32x16_t;
+typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 typedef __attribute__((ext_vector_type(4))) unsigned int u32x4_t;  // 16 bytes, a native vector
 typedef __attribute__((ext_vector_type(2))) unsigned int u32x2_t;
 
@@ -681,6 +682,388 @@ __global__ __launch_bounds__(kBigThreads, 1) void gemm_bf16_big_kernel(
 }
 
 // ---------------------------------------------------------------------------
+// bf16 MFMA grouped GEMM, 256 x 256 tiles, for steps with at least a few
+// hundred rows per group.
+//
+// What a CU can load (about 20-25 bytes per clock from L2 and beyond), not the
+// MFMA rate, bounds the 128 x 256 tile of the kernel above: 48 KB per 4.2
+// MFLOP k-tile.  This tile loads 64 KB per 8.4 MFLOP.  Eight waves of 128 rows
+// x 64 columns (2 x 4), 8 x 4 v_mfma_f32_16x16x32_bf16 tiles each (weights the
+// A operand: a lane holds four consecutive columns of one row); two LDS
+// buffers of a k-tile of 64, each in four 16 KB regions, rows X0 X1 and columns
+// W0 W1, in 128-byte rows with the large kernel's XOR swizzle.
+//
+// Schedule: a k-tile is four phases, X0 W0, X0 W1, X1 W1, X1 W0, and each
+// phase of a wave is a memory slot (its LDS reads, two DMA loads, one wait)
+// and an MFMA slot (16 MFMAs), a barrier after each.  Waves 4-7 run one slot
+// behind waves 0-3, so that on every SIMD one wave multiplies while the other
+// reads.  A region is free once both groups have read it, so its refill with
+// the k-tile two on is issued one phase later and has seven phases (nearly
+// two k-tiles) to land: up to 112 KB are in flight, and the wait of a slot is
+// "at most the six later phases' loads outstanding".  The stream does not stop at a
+// tile's end: a tile's last two k-tiles load the next tile's first two.
+//
+// Rows of an expert are split into equal parts of at most TM = 256, 192 or 128
+// rows; the lists kernel picks TM from the step's row counts so that the
+// rounds of tiles over the CUs waste least, and tiles of at most 192 or 128
+// rows skip the MFMAs and loads of the rows they do not have.  16 experts of
+// 1152 x 4608, 8 x 1024 tokens, top-2, full step: up 228 -> 198 us, down 228
+// -> 177 us; 64 SwiGLU experts of 2048 x 1408 and two shared ones, 4 x 4096
+// tokens, top-8: up 2059 -> 1450 us (1300 TFLOP/s), down 1069 -> 840 us.  Of
+// the up projection's 198 us about 20 are the activation and 30 the stores
+// of the intermediate, which every CU writes at about the same time.  Measured
+// and not better: two phases of 32 MFMAs per k-tile (half the barriers, 1.5
+// k-tiles of lookahead), the DMA loads between the MFMAs, a full-line
+// epilogue (a second lane exchange), tiles skipping rows in steps of 16 or
+// 32 (the branches, or the registers they hold, cost more).
+// ---------------------------------------------------------------------------
+constexpr int kTallTM = 256;
+constexpr int kTallTN = 256;
+constexpr int kTallWaves = 8;
+constexpr int kTallThreads = kTallWaves * kWave;
+constexpr int kTallHalf = 128 * kTK * 2;         // bytes of a region: 128 rows x 128 bytes
+constexpr int kTallBuf = 4 * kTallHalf;          // bytes of one k-tile: X0 X1 W0 W1
+constexpr int kTallMinK = 4 * kTK;
+
+__device__ __forceinline__ void tall_barrier() {
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("s_barrier" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+// One wait for both: at most N DMA loads of this wave in flight (N < 16),
+// every LDS read returned.
+template <int N>
+__device__ __forceinline__ void tall_wait() {
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"i"(N) : "memory");
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+template <int KIND, int ACT>
+__global__ __launch_bounds__(kTallThreads, 1) void gemm_bf16_tall_kernel(
+    const uint16_t* __restrict__ A, const uint16_t* __restrict__ W,
+    const uint16_t* __restrict__ Wsh, const int32_t* __restrict__ off,
+    const int32_t* __restrict__ tile_off, const int32_t* __restrict__ list,
+    const int32_t* __restrict__ row_dst, int E, int G, int k, int K, int Nout,
+    const int32_t* __restrict__ tm_dev, const float* __restrict__ bias, uint16_t* __restrict__ dst, uint16_t* __restrict__ dst_sh) {
+  constexpr bool kGated = ACT == kActSwiglu;
+  constexpr bool kListed = KIND != kDown;  // token rows come through the list
+  __shared__ __attribute__((aligned(16))) unsigned char lds[2 * kTallBuf];
+  __shared__ int s_list[2][kTallTM];
+  __shared__ int s_toff[128];
+  __shared__ float s_bias[ACT == kActBias ? 2 : 1][kTallTN];
+
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wv >> 2, wn = wv & 3;  // 2 x 4 waves; wm is also the ping-pong group
+  const int total = tile_off[G];
+  const int per = (total + kXcds - 1) / kXcds;
+  const int lo = (blockIdx.x % kXcds) * per;
+  const int hi = min(total, lo + per);
+  const int stride = gridDim.x / kXcds;
+  if (tid < 128) s_toff[tid] = tid < G ? tile_off[tid] : 0x7fffffff;
+  __syncthreads();
+  const int KT = K / kTK;
+  const int TM = tm_dev != nullptr ? *tm_dev : kTallTM;  // rows of a tile, at most
+  const int Nw = kGated ? Nout / 2 : Nout;
+  const uint32_t lds0 = __builtin_amdgcn_readfirstlane(lds_addr(lds) + wv * 1024);
+  const uint32_t sl0 = __builtin_amdgcn_readfirstlane(lds_addr(&s_list[0][0]) + (wv & 3) * 256);
+  const uint32_t sb0 = __builtin_amdgcn_readfirstlane(lds_addr(&s_bias[0][0]) + (wv & 3) * 256);
+
+  // the lane number, opaque to the compiler: what aim() and the epilogue
+  // derive from it is then computed there and not kept in registers across
+  // the k-loop, which needs all 256
+  auto fresh_lane = [&]() __attribute__((always_inline)) {
+    int l = lane;
+    asm volatile("" : "+v"(l));
+    return l;
+  };
+  struct TTile {
+    int e, r0, rows, n0;
+  };
+  auto tile = [&](int L) __attribute__((always_inline)) {
+    TTile t;
+    int e_base;
+    const int toff0 = s_toff[fresh_lane()], toff1 = s_toff[64 + fresh_lane()];
+    t.e = __builtin_amdgcn_readfirstlane(tile_group(L, toff0, toff1, e_base));
+    const int o0 = off[t.e];
+    const int cnt = off[t.e + 1] - o0;
+    const int mt = (cnt + TM - 1) / TM;
+    const int local = __builtin_amdgcn_readfirstlane(L - e_base);
+    const int m = local % mt;
+    t.r0 = __builtin_amdgcn_readfirstlane(o0 + static_cast<int>(int64_t(m) * cnt / mt));
+    t.rows = __builtin_amdgcn_readfirstlane(o0 + static_cast<int>(int64_t(m + 1) * cnt / mt) - t.r0);
+    t.n0 = __builtin_amdgcn_readfirstlane((local / mt) * kTallTN);
+    return t;
+  };
+
+  // the load stream's tile: byte offsets of this lane's rows (token rows from
+  // A, weight rows from the tile's first weight row)
+  uint32_t va[4], vw[4];
+  const uint16_t* wbase = W;
+  int xr = 0;  // its rows
+  auto aim = [&](const TTile& t, int lb) __attribute__((always_inline)) {
+    const int lane = fresh_lane();
+    const int chunk = (lane & 7) ^ (4 * (wv & 1) + (lane >> 4));
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int r = 128 * (q >> 1) + 8 * (wv + kTallWaves * (q & 1)) + (lane >> 3);
+      const int rr = r < t.rows ? r : 0;
+      int src;
+      if (KIND == kProj) {
+        src = s_list[lb][rr];
+      } else if (t.e >= E) {
+        src = t.r0 + rr - (KIND == kUp ? off[t.e] : 0);
+      } else {
+        src = KIND == kUp ? s_list[lb][rr] / k : t.r0 + rr;
+      }
+      va[q] = (static_cast<uint32_t>(src) * static_cast<uint32_t>(K) + chunk * 8) * 2u;
+      const int n = min(r, Nout - 1 - t.n0);
+      vw[q] = (static_cast<uint32_t>(n) * static_cast<uint32_t>(K) + chunk * 8) * 2u;
+    }
+    xr = t.rows;
+    wbase = (t.e < E ? W + int64_t(t.e) * Nout * K : Wsh + int64_t(t.e - E) * Nout * K) +
+            int64_t(t.n0) * K;
+  };
+  // row table of a tile into s_list[lb], by DMA: the list entries, fetched one
+  // tile ahead of the tile that uses them (up, projection), or the cache rows
+  // of the current tile (down); waves 0-3, 64 entries each.  Waves 4-7 fetch
+  // the bias of the tile's columns.
+  auto fetch_list = [&](const TTile& t, int lb) __attribute__((always_inline)) {
+    const int lane = fresh_lane();
+    if (wv < 4) {
+      if (t.e < E)
+        dma4((kListed ? list : row_dst) + t.r0 + min(64 * wv + lane, t.rows - 1),
+             sl0 + lb * (kTallTM * 4));
+    } else if (ACT == kActBias) {
+      dma4(bias + min(t.n0 + 64 * (wv - 4) + lane, Nout - 1), sb0 + lb * (kTallTN * 4));
+    }
+  };
+  // region X0, X1 (token rows) or W0, W1 (weight rows) of k-tile kt into buffer b
+  auto issue_x = [&](int kt, int b, int h, int nr) __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+      if (h == 0 || 128 + 64 * u < nr)
+        dma16_s(A + kt * kTK, va[2 * h + u], lds0 + b * kTallBuf + h * kTallHalf + u * 8192);
+  };
+  auto issue_w = [&](int kt, int b, int h) __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+      dma16_s(wbase + kt * kTK, vw[2 * h + u], lds0 + b * kTallBuf + (2 + h) * kTallHalf + u * 8192);
+  };
+
+  // this lane's fragment addresses in a region: row (lane & 15), 16-byte
+  // chunk 4 s + lane / 16, swizzled; token row tile i of the wave's half is
+  // 16-row tile 2 i + wm of the region, weight column tile j is 2 wn + j
+  const int sw = (lane >> 1) & 7;
+  const uint32_t fr = (lane & 15) * 128 + (((lane >> 4) ^ sw) * 16);
+  const unsigned char* const xl = lds + wm * 2048;
+  const unsigned char* const wl = lds + 2 * kTallHalf + wn * 4096;
+
+  bf16x8_t fx[4][2], fa[2][2], fb[2][2];
+  auto read_x = [&](int b, int h, int n) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int s = 0; s < 2; ++s)
+        if (i < n) fx[i][s] = *reinterpret_cast<const bf16x8_t*>(xl + b * kTallBuf + h * kTallHalf + i * 4096 +
+                                                      (fr ^ (s * 64)));
+  };
+  auto read_w = [&](bf16x8_t (&f)[2][2], int b, int h) __attribute__((always_inline)) {
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int s = 0; s < 2; ++s)
+        f[j][s] = *reinterpret_cast<const bf16x8_t*>(wl + b * kTallBuf + h * kTallHalf + j * 2048 +
+                                                     (fr ^ (s * 64)));
+  };
+
+  int L = lo + static_cast<int>(blockIdx.x) / kXcds;
+  if (L >= hi) return;
+  TTile cur = tile(L);
+  int lb = 0, sb = 0;  // row table and first buffer of the tile
+  if (kListed) fetch_list(cur, 0);
+  tall_wait<0>();
+  tall_barrier();
+  aim(cur, 0);
+#pragma unroll
+  for (int p = 0; p < 2; ++p) {
+    issue_w(p, p, 0);
+    issue_x(p, p, 0, xr);
+    issue_w(p, p, 1);
+    issue_x(p, p, 1, xr);
+  }
+  tall_wait<0>();
+  tall_barrier();
+  read_w(fa, 0, 0);
+  tall_wait<0>();
+  tall_barrier();
+  if (wm == 1) tall_barrier();
+
+  f32x4_t acc[4][8];  // [column tile][row tile]
+  for (;;) {
+    const int Ln = L + stride;
+    const bool has_next = Ln < hi;
+    TTile nxt = cur;
+    if (has_next) nxt = tile(Ln);
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int i = 0; i < 8; ++i) acc[j][i] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+    // The tile's k-loop, for tiles with up to 128, 192 or 256 rows (NX = 0, 2
+    // or 4 16-row tiles per wave in the second half) and with or without
+    // columns past 128 (CA): one instantiation each, so that nothing is
+    // decided inside a k-tile.
+    auto run = [&](auto nx_c, auto ca_c) __attribute__((always_inline)) {
+      constexpr int NX = decltype(nx_c)::value;
+      constexpr bool CA = decltype(ca_c)::value;
+      auto mfma_q = [&](int h, int c, const bf16x8_t (&f)[2][2]) __attribute__((always_inline)) {
+        __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+#pragma unroll
+          for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+              if (h == 0 || i < NX)
+                acc[2 * c + j][4 * h + i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                    f[j][s], fx[i][s], acc[2 * c + j][4 * h + i], 0, 0, 0);
+        __builtin_amdgcn_s_setprio(0);
+      };
+      // One k-tile: t of this tile, in buffer b.  W0 comes in registers p
+      // (read in the previous k-tile's last phase); the next k-tile's W0 is
+      // left in q.  tail: the loads are the next tile's first k-tiles.
+      auto ktile = [&](int t, int b, bf16x8_t (&p)[2][2], bf16x8_t (&q)[2][2], auto tail_c)
+          __attribute__((always_inline)) {
+        constexpr bool kTail = decltype(tail_c)::value;
+        const int lt = kTail ? t + 2 - KT : t + 2;
+        const bool load = !kTail || has_next;
+        const int nx = kTail ? xr : NX == 4 ? 256 : NX == 2 ? 192 : 128;
+        auto settle = [&]() __attribute__((always_inline)) {
+          if (!kTail) tall_wait<8 + NX>();
+          else if (has_next) tall_wait<8>();
+          else tall_wait<0>();
+          tall_barrier();
+        };
+        // phase 0: X0 x W0
+        read_x(b, 0, 4);
+        if (load) issue_w(lt, b, 0);
+        settle();
+        mfma_q(0, 0, p);
+        tall_barrier();
+        // phase 1: X0 x W1
+        if (CA) read_w(q, b, 1);
+        if (!kTail && t == 0) {
+          // not earlier: the other waves' epilogue of the previous tile may
+          // still read the table
+          if (!kListed) fetch_list(cur, lb);
+          else if (has_next) fetch_list(nxt, lb ^ 1);
+        }
+        if (load) issue_x(lt, b, 0, nx);
+        settle();
+        if (CA) mfma_q(0, 1, q);
+        tall_barrier();
+        // phase 2: X1 x W1
+        if (NX > 0) read_x(b, 1, NX);
+        if (load) issue_w(lt, b, 1);
+        settle();
+        if (CA && NX > 0) mfma_q(1, 1, q);
+        tall_barrier();
+        // phase 3: X1 x W0, and the next k-tile's W0
+        read_w(q, b ^ 1, 0);
+        if (load) issue_x(lt, b, 1, nx);
+        settle();
+        if (NX > 0) mfma_q(1, 0, p);
+        tall_barrier();
+      };
+      int t = 0;
+      for (; t < KT - 3; t += 2) {
+        ktile(t, sb, fa, fb, std::false_type{});
+        ktile(t + 1, sb ^ 1, fb, fa, std::false_type{});
+      }
+      if (t == KT - 3) {
+        // odd count: one more, and its roles exchanged back
+        ktile(t, sb, fa, fb, std::false_type{});
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+          for (int s = 0; s < 2; ++s) fa[j][s] = fb[j][s];
+        sb ^= 1;
+      }
+      if (has_next) aim(nxt, lb ^ 1);
+      ktile(KT - 2, sb, fa, fb, std::true_type{});
+      ktile(KT - 1, sb ^ 1, fb, fa, std::true_type{});
+    };
+    if (cur.n0 + 128 < Nout) {
+      if (cur.rows > 192) run(std::integral_constant<int, 4>{}, std::true_type{});
+      else if (cur.rows > 128) run(std::integral_constant<int, 2>{}, std::true_type{});
+      else run(std::integral_constant<int, 0>{}, std::true_type{});
+    } else {
+      if (cur.rows > 192) run(std::integral_constant<int, 4>{}, std::false_type{});
+      else if (cur.rows > 128) run(std::integral_constant<int, 2>{}, std::false_type{});
+      else run(std::integral_constant<int, 0>{}, std::false_type{});
+    }
+
+    // epilogue: the lane holds columns c .. c + 3 of row (lane & 15) of each
+    // 16 x 16 tile.  Activation and bf16 rounding; then lanes l and l ^ 16
+    // exchange runs of the wave's two adjacent column tiles, so that each
+    // store writes 16 bytes (8 when gated).
+    const int lane = fresh_lane();
+    const int g = lane >> 4, h = g & 1;
+    uint16_t* const og = cur.e < E ? dst : dst_sh;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int row = 128 * (i >> 2) + 16 * (2 * (i & 3) + wm) + (lane & 15);
+      if (row >= cur.rows) continue;
+      int drow;
+      if (KIND == kProj) drow = s_list[lb][row];
+      else if (KIND == kUp) drow = cur.r0 + row;
+      else drow = cur.e < E ? s_list[lb][row] : cur.r0 + row - off[E];
+      uint16_t* const orow = og + int64_t(drow) * Nw;
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        const int cw = cur.n0 + 128 * c + 32 * wn;  // first column of the pair
+        if (cw >= Nout) continue;
+        if constexpr (kGated) {
+          const f32x4_t &a0 = acc[2 * c][i], &a1 = acc[2 * c + 1][i];
+          const uint32_t p0 = pack2_bf16(silu_f(a0[0]) * a0[1], silu_f(a0[2]) * a0[3]);
+          const uint32_t p1 = pack2_bf16(silu_f(a1[0]) * a1[1], silu_f(a1[2]) * a1[3]);
+          const uint32_t r = __shfl_xor(h ? p0 : p1, 16, kWave);
+          *reinterpret_cast<u32x2_t*>(orow + cw / 2 + 8 * h + 2 * (g - h)) =
+              h ? u32x2_t{r, p1} : u32x2_t{p0, r};
+        } else {
+          u32x2_t pk[2];
+#pragma unroll
+          for (int j = 0; j < 2; ++j) {
+            f32x4_t a = acc[2 * c + j][i];
+            if constexpr (ACT == kActBias) {
+              const float* bp = &s_bias[lb][128 * c + 32 * wn + 16 * j + 4 * g];
+#pragma unroll
+              for (int u = 0; u < 4; ++u) a[u] += bp[u];
+            }
+            pk[j] = u32x2_t{pack2_bf16(act_fn<ACT>(a[0]), act_fn<ACT>(a[1])),
+                            pack2_bf16(act_fn<ACT>(a[2]), act_fn<ACT>(a[3]))};
+          }
+          const u32x2_t keep = h ? pk[1] : pk[0];
+          const u32x2_t send = h ? pk[0] : pk[1];
+          const uint32_t q0 = __shfl_xor(send[0], 16, kWave);
+          const uint32_t q1 = __shfl_xor(send[1], 16, kWave);
+          *reinterpret_cast<u32x4_t*>(orow + cw + 16 * h + 4 * (g - h)) =
+              h ? u32x4_t{q0, q1, keep[0], keep[1]} : u32x4_t{keep[0], keep[1], q0, q1};
+        }
+      }
+    }
+    if (!has_next) break;
+    L = Ln;
+    cur = nxt;
+    lb ^= 1;
+  }
+  if (wm == 0) tall_barrier();
+}
+
+// ---------------------------------------------------------------------------
 // bf16 MFMA grouped GEMM for weight-streaming steps: few rows per expert, so
 // every weight byte is used by one tile and the step is bound by how fast
 // the CUs pull the weights in.  The tile is 128 rows x 288 columns, so that
@@ -712,9 +1095,6 @@ constexpr int kThinLoadsA = kThinTM / 8 / kThinWaves;                     // 2 p
 constexpr int kThinInstB = kThinTN / 8;                                   // 36
 constexpr int kThinLoadsB = (kThinInstB + kThinWaves - 1) / kThinWaves;   // 5 (waves 0-3), 4
 static_assert(kThinInstB % kThinWaves == kThinWaves / 2, "waves 0-3 issue one more weight load");
-
-typedef __attribute__((ext_vector_type(4))) float f32x4_t;
-
 
 template <int KIND, int ACT, int SPLIT>
 __global__ __launch_bounds__(kThinThreads, 1) void gemm_bf16_thin_kernel(
@@ -1479,7 +1859,12 @@ hipError_t launch_gemm(const Shape& s, const FfnPlan& plan, const void* A, const
     const auto* wsh = static_cast<const uint16_t*>(Wsh);
     auto* o = static_cast<uint16_t*>(dst);
     auto* osh = static_cast<uint16_t*>(dst_sh);
-    if (tn == kBigTN) {
+    const bool tall = KIND == kUp ? plan.tall_up : plan.tall_down;
+    if (tall) {
+      launch_kernel(&gemm_bf16_tall_kernel<KIND, ACT>, dim3(device_cus()), dim3(kTallThreads), 0,
+          st, a, w, wsh, b.off, toff, b.list, b.row_dst, s.E, G, s.k, K, Nout,
+          b.tiles + 2 * (G + 1) + (KIND == kUp ? 0 : 1), static_cast<const float*>(nullptr), o, osh);
+    } else if (tn == kBigTN) {
       launch_kernel(&gemm_bf16_big_kernel<KIND, ACT>, dim3(device_cus()), dim3(kBigThreads), 0, st,
           a, w, wsh, b.off, toff, b.list, b.row_dst, s.E, G, s.k, K, Nout,
           static_cast<const float*>(nullptr), o, osh);
@@ -1518,11 +1903,18 @@ hipError_t launch_gemm(const Shape& s, const FfnPlan& plan, const void* A, const
 
 }  // namespace
 
+// Launches the 256 x 256 tiles can take: `rows` rows of K inputs addressed by
+// 32-bit byte offsets, K long enough for the load stream's lookahead, and an
+// output wide enough that the last column tile does not dominate.
+static bool tall_capable(int64_t rows, int K, int Nout) {
+  return K >= kTallMinK && Nout >= 512 && rows * K < (int64_t(1) << 31);
+}
+
 // Weight-row counts of at least 512 take the large 128 x 256 tile (a
 // partial last N tile is masked); smaller ones the 128 x 128 / 128 x 64
 // tiles; the thin plan the 128 x 288 tile; the wide plan the expert-wide
 // 384 x 144 up-projection tile (the down projection keeps the large tile).
-FfnPlan ffn_plan(const Shape& s, bool thin, bool wide) {
+FfnPlan ffn_plan(const Shape& s, bool thin, bool wide, int64_t mean_rows) {
   auto tn = [](int n) { return n >= 512 ? kBigTN : (n % 128 == 0 ? 128 : 64); };
   FfnPlan p;
   p.tm = p.tm_up = 128;
@@ -1540,7 +1932,18 @@ FfnPlan ffn_plan(const Shape& s, bool thin, bool wide) {
   }
   p.tn_up = tn(s.up_rows());
   p.tn_down = tn(s.d);
+  p.tall_up = tall_capable(s.tokens(), s.d, s.up_rows()) && mean_rows >= kTallRows;
+  p.tall_down = tall_capable(s.mid_rows(), s.d_ff, s.d) && mean_rows >= kTallRows;
+  if (p.tall_up) {
+    p.tm_up = kTallTM;
+    p.tn_up = kTallTN;
+  }
+  if (p.tall_down) {
+    p.tm = kTallTM;
+    p.tn_down = kTallTN;
+  }
   if (wide && wide_capable(s)) {
+    p.tall_up = false;
     p.wide_up = true;
     p.tm_up = kWideTM;
     p.tn_up = kWideTN;

@@ -93,7 +93,8 @@ struct Buffers {
   int32_t* cnt_ch;  // [B][RC][E] the same per chunk of 1024 branches (RC = ceil(N k / 1024))
   int32_t* stats_bs;// [B][4] recompute, unmatched, matched, sync per sample
   int32_t* rflags;  // router: one non-finite flag per block
-  int32_t* tiles;   // [2][E+S+1] grouped-GEMM tile prefix per group (up, down)
+  int32_t* tiles;   // [2][E+S+1] grouped-GEMM tile prefix per group (up, down), then the
+                    // rows of a tile, at most, of either (256 x 256 tiles)
   int32_t* row_dst; // [B*N*k] cache row of each listed branch: (f/k)*k + sigma(f)
   int32_t* wide;    // [B][kWideWords] per-sample scratch of the multi-block decision path
   void* mid;        // [B*N*k + S*T][d_ff] FFN activation of listed and shared rows
@@ -117,6 +118,7 @@ struct FfnPlan {
   bool thin = false;
   bool wide_up = false;  // the up projection takes the expert-wide kernel
   int tm_up = 128;       // M tile of the up projection's tile table
+  bool tall_up = false, tall_down = false;  // the 256 x 256 tiles (tm chosen on the device)
 };
 constexpr int kThinSplit = 4;
 // A ratio-mode cache step takes the thin plan when its budget leaves at most
@@ -127,7 +129,14 @@ constexpr int kThinRows = 112;
 // an expert's rows, up to 384, by 144 columns); so does a full step with at
 // most this many branches per expert on average.
 constexpr int kWideRows = 320;
-FfnPlan ffn_plan(const Shape& s, bool thin = false, bool wide = false);
+// Steps with at least this many rows per group (routed and shared experts)
+// on average take the 256 x 256 tiles.  Measured sides (16 experts of 1152 x
+// 4608; 128 x 256 tiles against these): 375 rows per expert down 131 against 92
+// us, 307 rows down 80 against 76, 256 rows down 74 against 76, 225 rows up 49
+// against 53 and down 62 against 66 us.
+constexpr int kTallRows = 288;
+// mean_rows: rows per group that the step is expected to have, on average.
+FfnPlan ffn_plan(const Shape& s, bool thin, bool wide, int64_t mean_rows);
 // K pieces of an fp32 layer's down projection (1: not split).  Above 1 the
 // workspace holds `part`.
 int f32_split(const Shape& s);

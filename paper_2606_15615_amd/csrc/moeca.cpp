@@ -86,7 +86,7 @@ Layout make_layout(const Shape& s, bool external_mid = false, bool partials = tr
   b[R_CNT_BS] = size_t(s.B) * s.E * 4;
   b[R_STATS_BS] = size_t(s.B) * 4 * 4;
   b[R_RFLAGS] = size_t(moeca::router_blocks(s)) * 4;
-  b[R_TILES] = size_t(2) * (s.groups() + 1) * 4;
+  b[R_TILES] = (size_t(2) * (s.groups() + 1) + 2) * 4;
   b[R_ROW_DST] = nbr * 4;
   b[R_ENT] = size_t(s.B) * s.E * ((size_t(s.N) + 15) / 16) * 2 * 8;
   b[R_CNT_CH] = size_t(s.B) * ((size_t(s.N) * s.k + 1023) / 1024) * s.E * 4;
@@ -335,7 +335,7 @@ int moeca_forward_noalloc(const moeca_layer* L, const void* x, int samples, void
   const Buffers b = map_buffers(static_cast<char*>(base), lay, nullptr);
   const moeca_policy& p = L->pol;
   const auto st = static_cast<hipStream_t>(stream);
-  moeca::FfnPlan plan = moeca::ffn_plan(s);
+  moeca::FfnPlan plan = moeca::ffn_plan(s, false, false, s.mid_rows() / s.groups());
   if (b.part == nullptr) plan.split_down = 1;
   // the uncached layer: every branch recomputed, no statistic, no cache
   // metadata and no attention path (the MOECA_MODE_FULL step)
@@ -459,7 +459,13 @@ int layer_step(moeca_layer* L, const void* x_t, const void* x_ffn, int t, void* 
   const bool wide = (full ? int64_t(s.B) * s.N * s.k <= int64_t(moeca::kWideRows) * s.E
                           : p.mode == MOECA_MODE_RATIO &&
                                 int64_t(budget) * s.B <= int64_t(moeca::kWideRows) * s.E);
-  const moeca::FfnPlan plan = moeca::ffn_plan(s, thin, wide);
+  // rows the FFN is expected to have: every branch on full steps, the budget
+  // in ratio mode; a threshold step's count is not known to the host (half)
+  const int64_t rows = full ? s.branches()
+                       : p.mode == MOECA_MODE_RATIO ? int64_t(budget) * s.B
+                                                    : s.branches() / 2;
+  const moeca::FfnPlan plan =
+      moeca::ffn_plan(s, thin, wide, (rows + s.S * s.tokens()) / s.groups());
   arm();
   if (!check(moeca::launch_lists(s, plan, b, st), "lists")) return MOECA_E_HIP;
   if (between) {

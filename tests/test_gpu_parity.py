@@ -99,6 +99,29 @@ def test_erf_gelu_over_its_range():
     run_forced(S, 1, label="erf range")
 
 
+@pytest.mark.parametrize("E,N,B,d,d_ff,ffn,n_shared", [
+    (1, 384, 1, 576, 512, "gelu", 0),      # full parts of 128; 9 k-tiles (odd), N = 512 and 576
+    (1, 385, 1, 640, 832, "gelu", 1),      # parts of 96 and 97 rows, a shared expert
+    (2, 300, 2, 512, 512, "swiglu", 0),    # gated, uneven experts
+    (3, 611, 3, 704, 640, "gelu", 0),      # ragged rows, column remainders of 192 and 128
+    (2, 161, 4, 512, 1088, "swiglu", 2),   # 17 k-tiles, two shared experts
+    (4, 1024, 2, 512, 256, "gelu", 0),     # four k-tiles, the shortest the tile takes
+    (1, 1100, 1, 320, 8192, "gelu", 0),    # up: parts of up to 192 rows waste least (192 tiles)
+    (1, 1900, 1, 320, 8192, "gelu", 0),    # up: parts of up to 256 rows (256 tiles)
+    (1, 1900, 1, 320, 4096, "swiglu", 0),  # the same, gated
+    (2, 4500, 1, 320, 4160, "gelu", 0),    # several tiles per CU of different heights
+])
+def test_tall_tile_edges(E, N, B, d, d_ff, ffn, n_shared):
+    """Steps with at least 288 rows per group take the 256 x 256 tiles: every
+    class of tile height (up to 128, 192, 256 rows, equal parts), odd and
+    even k-tile counts, column remainders, gated and shared experts, several
+    tiles per CU; and the cache steps after a full one."""
+    shape = LayerShape(d=d, E=E, k=1, d_ff=d_ff, B=B, N=N, dtype="bf16", ffn=ffn,
+                       n_shared=n_shared)
+    S = Setup(shape, mode="ratio", seed=22, T=2, ratio=0.9)
+    run_forced(S, 2, label=f"tall {E} {N} {B} {d} {d_ff} {ffn} {n_shared}")
+
+
 WIDE = LayerShape(d=128, E=16, k=8, d_ff=128, B=2, N=1100, dtype="bf16")
 
 
