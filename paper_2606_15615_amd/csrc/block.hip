@@ -401,13 +401,16 @@ __global__ __launch_bounds__(kLnWaves * kWave) void ln_kernel(LnArgs p) {
 // sync[t] != 0.  Block b counts the flags of samples 0 .. b-1 (its base in
 // the list), then lists its own tokens in ascending order.  Writes slist
 // (flat token ids, by sample), soff[B + 1] and, from the last block,
-// tab[0..3] = {0, nS, 0, tiles of nS rows x ntn_q} for the projections
-// (128-row tiles); the full-list call also writes ident[t] = t and
-// tab[4..7] = {0, T, 0, tiles of T rows x ntn_kv}.
+// tab[0..3] = {0, nS, 0, tiles of nS rows x ntn_q} and tab[8] = the rows of a
+// tile, at most, for the projections of the listed tokens; the full-list call
+// also writes ident[t] = t and the same for the k/v projection, tab[4..7] and
+// tab[9].  cus_q, cus_kv > 0: 256-column tiles, their height chosen for that
+// many CUs; 0: 64-row tiles.
 constexpr int kListThreads = 1024;
 
 __global__ __launch_bounds__(kListThreads) void slist_kernel(
-    const uint8_t* __restrict__ sync, int all, int B, int N, int ntn_q, int ntn_kv,
+    const uint8_t* __restrict__ sync, int all, int B, int N, int ntn_q, int ntn_kv, int cus_q,
+    int cus_kv,
     int32_t* __restrict__ slist, int32_t* __restrict__ soff, int32_t* __restrict__ ident,
     int32_t* __restrict__ tab) {
   __shared__ int s_wave[kListThreads / kWave];
@@ -449,20 +452,25 @@ __global__ __launch_bounds__(kListThreads) void slist_kernel(
     if (f) slist[before + __popcll(bal & ((1ull << lane) - 1ull))] = b * N + i;
     run += tot;
   }
-  if (tid == 0) {
-    soff[b] = base;
-    if (b == B - 1) {
-      const int ns = run;
+  if (wv != 0) return;
+  if (lane == 0) soff[b] = base;
+  if (b == B - 1) {
+    const int ns = run;
+    const int tm_q = cus_q > 0 ? tall_rows(lane == 0 ? ns : 0, 1, 0, 0, ntn_q, cus_q) : kSlimRows;
+    const int tm_kv = cus_kv > 0 ? tall_rows(lane == 0 ? T : 0, 1, 0, 0, ntn_kv, cus_kv) : kSlimRows;
+    if (lane == 0) {
       soff[B] = ns;
       tab[0] = 0;
       tab[1] = ns;
       tab[2] = 0;
-      tab[3] = (ns + kProjTM - 1) / kProjTM * ntn_q;
+      tab[3] = (ns + tm_q - 1) / tm_q * ntn_q;
+      tab[8] = tm_q;
       if (all) {
         tab[4] = 0;
         tab[5] = T;
         tab[6] = 0;
-        tab[7] = (T + kProjTM - 1) / kProjTM * ntn_kv;
+        tab[7] = (T + tm_kv - 1) / tm_kv * ntn_kv;
+        tab[9] = tm_kv;
       }
     }
   }
@@ -822,10 +830,12 @@ hipError_t launch_ln_final(const BlockBufs& k, int T, int N, int d, const float*
 }
 
 hipError_t launch_slist(const BlockBufs& k, const uint8_t* sync, int N, int d, hipStream_t st) {
-  const int ntn_q = (d + kProjTN - 1) / kProjTN;
-  const int ntn_kv = (2 * d + kProjTN - 1) / kProjTN;
+  const int64_t T = int64_t(k.B) * N;
+  const bool tq = proj_tall(T, d, d), tkv = proj_tall(T, d, 2 * d);
+  const int cq = proj_tile_cols(tq), ckv = proj_tile_cols(tkv);
   launch_kernel(&slist_kernel, dim3(k.B), dim3(kListThreads), 0, st, sync, sync == nullptr ? 1 : 0,
-                k.B, N, ntn_q, ntn_kv, k.slist, k.soff, k.ident, k.tab);
+                k.B, N, (d + cq - 1) / cq, (2 * d + ckv - 1) / ckv, tq ? device_cus() : 0,
+                tkv ? device_cus() : 0, k.slist, k.soff, k.ident, k.tab);
   return hipGetLastError();
 }
 

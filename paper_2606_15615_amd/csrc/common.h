@@ -212,4 +212,48 @@ __device__ __forceinline__ uint32_t f32_order_key(float f) {
   return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
+// A tile's time per k-tile, in units of a row: it loads 256 weight rows
+// whatever its height.
+__host__ __device__ constexpr int tall_cost(int tm) { return 160 + tm; }
+
+// Rows of a tile for `rows` rows of one group (host): tall_rows below.
+inline int tall_rows_one(int64_t rows, int nt, int cus) {
+  int best = 256;
+  int64_t cost = -1;
+  for (int tm = 256; tm >= 128; tm -= 64) {
+    const int64_t c = ((rows + tm - 1) / tm * nt + cus - 1) / cus * tall_cost(tm);
+    if (cost < 0 || c < cost) {
+      cost = c;
+      best = tm;
+    }
+  }
+  return best;
+}
+
+// Rows of a tile (128, 192 or 256) for a launch of the 256-column GEMM with
+// nt column tiles: the count that makes rounds x cost of a tile least, a round
+// being one tile per CU.  t: this lane's expert's rows (lane < E, else 0); S
+// shared experts have T rows each.  Lane l looks at choice l % 4 for the
+// experts l / 4 + 16 i.  Wave-wide; every lane gets the result.
+__device__ __forceinline__ int tall_rows(int t, int E, int S, int T, int nt, int cus) {
+  const int lane = threadIdx.x & (kWave - 1);
+  const int c = min(lane & 3, 2);
+  auto parts = [&](int n) {
+    return c == 0 ? (n + 127) / 128 : c == 1 ? (n + 191) / 192 : (n + 255) / 256;
+  };
+  int mt = 0;
+  for (int i = 0; i < E; i += 16) {
+    const int n = __shfl(t, (lane >> 2) + i, kWave);  // 0 past the experts
+    mt += parts(n);
+  }
+#pragma unroll
+  for (int m = 4; m < kWave; m *= 2) mt += __shfl_xor(mt, m, kWave);
+  mt += S * parts(T);
+  const int rounds = (mt * nt + cus - 1) / cus;
+  const int cost = rounds * tall_cost(128 + 64 * c);
+  const int c0 = __builtin_amdgcn_readlane(cost, 0), c1 = __builtin_amdgcn_readlane(cost, 1),
+            c2 = __builtin_amdgcn_readlane(cost, 2);
+  return c2 <= c1 && c2 <= c0 ? 256 : c1 <= c0 ? 192 : 128;
+}
+
 }  // namespace moeca

@@ -578,34 +578,6 @@ __device__ __forceinline__ void write_shared_groups(int32_t* __restrict__ off,
   }
 }
 
-// Rows of a tile (128, 192 or 256) for a launch of the 256-column GEMM with
-// nt column tiles: the count that makes rounds x cost of a tile least, a round
-// being one tile per CU.  t: this lane's expert's rows (lane < E, else 0); S
-// shared experts have T rows each.  Lane l looks at choice l % 4 for the
-// experts l / 4 + 16 i.  Wave-wide; every lane gets the result.
-__device__ __forceinline__ int tall_rows(int t, int E, int S, int T, int nt, int cus) {
-  const int lane = threadIdx.x & (kWave - 1);
-  const int c = min(lane & 3, 2);
-  auto parts = [&](int n) {
-    return c == 0 ? (n + 127) / 128 : c == 1 ? (n + 191) / 192 : (n + 255) / 256;
-  };
-  int mt = 0;
-  for (int i = 0; i < E; i += 16) {
-    const int n = __shfl(t, (lane >> 2) + i, kWave);  // 0 past the experts
-    mt += parts(n);
-  }
-#pragma unroll
-  for (int m = 4; m < kWave; m *= 2) mt += __shfl_xor(mt, m, kWave);
-  mt += S * parts(T);
-  const int rounds = (mt * nt + cus - 1) / cus;
-  // a tile's time per k-tile is about 160 + its rows (it loads 256 weight
-  // rows whatever its height)
-  const int cost = rounds * (160 + 128 + 64 * c);
-  const int c0 = __builtin_amdgcn_readlane(cost, 0), c1 = __builtin_amdgcn_readlane(cost, 1),
-            c2 = __builtin_amdgcn_readlane(cost, 2);
-  return c2 <= c1 && c2 <= c0 ? 256 : c1 <= c0 ? 192 : 128;
-}
-
 // ---------------------------------------------------------------------------
 // Per-expert lists of recomputed branches, ascending flat id within each
 // expert; one 1024-thread block per chunk of 1024 consecutive branches of a

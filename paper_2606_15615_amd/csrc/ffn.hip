@@ -119,10 +119,8 @@ __device__ __forceinline__ void group_row(int e, int E, int r0, int rows, int r,
                                           const int32_t* __restrict__ row_dst, int& src,
                                           int& dst) {
   const int rr = r < rows ? r : 0;
-  if (KIND == kProj) {
-    src = list[r0 + rr];
-    dst = r < rows ? list[r0 + r] : -1;
-  } else if (e < E) {
+  static_assert(KIND != kProj, "projections read the list directly");
+  if (e < E) {
     if (KIND == kUp) {
       src = list[r0 + rr] / k;
       dst = r < rows ? r0 + r : -1;
@@ -367,7 +365,6 @@ constexpr int kStageElems = kTileA + kTileB;  // 48 KB
 constexpr int kLoadsA = kBigTM / 8 / kBigWaves;  // DMA instructions per wave per stage (A)
 constexpr int kLoadsB = kBigTN / 8 / kBigWaves;  // (B)
 constexpr int kLoadsPerStage = kLoadsA + kLoadsB;
-static_assert(kProjTM == kBigTM && kProjTN == kBigTN, "projection tables use the big tile");
 
 __device__ __forceinline__ void s_waitcnt_vm(int n) {
   // gfx9 encoding: vmcnt[3:0] | expcnt[6:4] | lgkmcnt[11:8] | vmcnt[5:4] << 14
@@ -484,7 +481,7 @@ __global__ __launch_bounds__(kBigThreads, 1) void gemm_bf16_big_kernel(
     const uint16_t* __restrict__ Wsh, const int32_t* __restrict__ off,
     const int32_t* __restrict__ tile_off, const int32_t* __restrict__ list,
     const int32_t* __restrict__ row_dst, int E, int G, int k, int K, int Nout,
-    const float* __restrict__ bias, uint16_t* __restrict__ dst, uint16_t* __restrict__ dst_sh) {
+    uint16_t* __restrict__ dst, uint16_t* __restrict__ dst_sh) {
   constexpr int TM = kBigTM, TN = kBigTN;
   constexpr bool kGated = ACT == kActSwiglu;
   constexpr int FM = 2, FN = 2;  // wave tile: 64 rows x 64 columns
@@ -647,18 +644,8 @@ __global__ __launch_bounds__(kBigThreads, 1) void gemm_bf16_big_kernel(
           uint32_t pk[4][2];
 #pragma unroll
           for (int q = 0; q < 4; ++q) {
-            if constexpr (ACT == kActBias) {
-              // columns c .. c + 3 of the bias (clamped: masked columns are not stored)
-              const int c = c0 + i * 32 + 8 * q + 4 * h;
-              float bv[4];
-#pragma unroll
-              for (int s2 = 0; s2 < 4; ++s2) bv[s2] = bias[min(c + s2, Nout - 1)];
-              pk[q][0] = pack2_bf16(a[4 * q] + bv[0], a[4 * q + 1] + bv[1]);
-              pk[q][1] = pack2_bf16(a[4 * q + 2] + bv[2], a[4 * q + 3] + bv[3]);
-            } else {
-              pk[q][0] = pack2_bf16(act_fn<ACT>(a[4 * q]), act_fn<ACT>(a[4 * q + 1]));
-              pk[q][1] = pack2_bf16(act_fn<ACT>(a[4 * q + 2]), act_fn<ACT>(a[4 * q + 3]));
-            }
+            pk[q][0] = pack2_bf16(act_fn<ACT>(a[4 * q]), act_fn<ACT>(a[4 * q + 1]));
+            pk[q][1] = pack2_bf16(act_fn<ACT>(a[4 * q + 2]), act_fn<ACT>(a[4 * q + 3]));
           }
 #pragma unroll
           for (int p = 0; p < 2; ++p) {
@@ -1538,6 +1525,122 @@ __global__ __launch_bounds__(256) void reduce_partials_kernel(
 }
 
 // ---------------------------------------------------------------------------
+// bf16 projection of few listed rows: dst[list[r]] = A[list[r]] . W^T + bias.
+//
+// With a few hundred rows the 256 x 256 tiles leave most CUs idle (250 rows by
+// 1152 columns: 5 tiles) and a launch lasts as long as one tile's chain of
+// k-tiles, whose loads wait on memory.  Here a tile is up to 64 rows (equal
+// parts) by 64 columns: four waves, each 16 columns by the tile's 16-row tiles
+// (as in the fp32 kernel below), and a ring of eight 16 KB stages, seven
+// k-tiles in flight, so that at K = 1152 most of the operands are requested
+// before the first MFMA.
+// ---------------------------------------------------------------------------
+constexpr int kSlimTM = kSlimRows;
+constexpr int kSlimTN = 64;
+constexpr int kSlimWaves = 4;
+constexpr int kSlimThreads = kSlimWaves * kWave;
+constexpr int kSlimStages = 8;
+constexpr int kSlimStage = (kSlimTM + kSlimTN) * kTK;  // bf16 elements (16 KB)
+
+__global__ __launch_bounds__(kSlimThreads, 1) void gemm_bf16_slim_kernel(
+    const uint16_t* __restrict__ A, const uint16_t* __restrict__ W,
+    const int32_t* __restrict__ off, const int32_t* __restrict__ tiles,
+    const int32_t* __restrict__ list, int K, int Nout, const float* __restrict__ bias,
+    uint16_t* __restrict__ dst) {
+  __shared__ __attribute__((aligned(16))) uint16_t lds[kSlimStages * kSlimStage];
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int cnt = off[1];
+  const int total = tiles[1];
+  const int per = (total + kXcds - 1) / kXcds;
+  const int lo = (blockIdx.x % kXcds) * per;
+  const int hi = min(total, lo + per);
+  const int stride = gridDim.x / kXcds;
+  const int mt = (cnt + kSlimTM - 1) / kSlimTM;
+  const int KT = K / kTK;
+  // stored chunk position: chunk ^ ((row >> 1) & 7), as in the large kernel
+  const int chunk = (lane & 7) ^ (4 * (wv & 1) + (lane >> 4));
+  const uint32_t lds0 = __builtin_amdgcn_readfirstlane(lds_addr(lds) + wv * 1024);
+
+  for (int L = lo + static_cast<int>(blockIdx.x) / kXcds; L < hi; L += stride) {
+    const int m = L % mt;
+    const int r0 = static_cast<int>(int64_t(m) * cnt / mt);
+    const int rows = static_cast<int>(int64_t(m + 1) * cnt / mt) - r0;
+    const int n0 = L / mt * kSlimTN;
+    const uint16_t* ga[2];
+    const uint16_t* gb[2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int r = 8 * (wv + kSlimWaves * u) + (lane >> 3);
+      ga[u] = A + int64_t(list[r0 + (r < rows ? r : 0)]) * K + chunk * 8;
+      gb[u] = W + int64_t(min(n0 + r, Nout - 1)) * K + chunk * 8;
+    }
+    // the output rows and the bias of this lane, requested with the rows
+    const int c = n0 + 16 * wv + 4 * (lane >> 4);  // columns c .. c + 3
+    int drow[kSlimTM / 16];
+#pragma unroll
+    for (int r = 0; r < kSlimTM / 16; ++r) {
+      const int row = 16 * r + (lane & 15);
+      drow[r] = row < rows ? list[r0 + row] : -1;
+    }
+    float bv[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) bv[u] = bias[min(c + u, Nout - 1)];
+    auto issue = [&](int kt, int st) __attribute__((always_inline)) {
+      const uint32_t base = lds0 + st * (kSlimStage * 2);
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        dma16(gb[u] + kt * kTK, base + kSlimTM * kTK * 2 + u * kSlimWaves * 1024);
+        dma16(ga[u] + kt * kTK, base + u * kSlimWaves * 1024);
+      }
+    };
+    f32x4_t acc[kSlimTM / 16];
+#pragma unroll
+    for (int r = 0; r < kSlimTM / 16; ++r) acc[r] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int p = 0; p < kSlimStages - 1; ++p)
+      if (p < KT) issue(p, p);
+    for (int kt = 0; kt < KT; ++kt) {
+      // four loads a stage: the stage's own have landed once at most the six
+      // later stages' are outstanding (near the end, once none is)
+      if (kt + kSlimStages - 1 <= KT)
+        asm volatile("s_waitcnt vmcnt(%0)" ::"i"(4 * (kSlimStages - 2)) : "memory");
+      else
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      tall_barrier();
+      if (kt + kSlimStages - 1 < KT) issue(kt + kSlimStages - 1, (kt + kSlimStages - 1) % kSlimStages);
+      const uint16_t* xs = lds + (kt % kSlimStages) * kSlimStage;
+      const uint16_t* ws = xs + kSlimTM * kTK;
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        const int ch = 4 * s + (lane >> 4);
+        const int wrow = 16 * wv + (lane & 15);
+        const bf16x8_t wb =
+            *reinterpret_cast<const bf16x8_t*>(ws + (wrow * 8 + (ch ^ ((wrow >> 1) & 7))) * 8);
+#pragma unroll
+        for (int r = 0; r < kSlimTM / 16; ++r) {
+          const int row = 16 * r + (lane & 15);
+          const bf16x8_t xa =
+              *reinterpret_cast<const bf16x8_t*>(xs + (row * 8 + (ch ^ ((row >> 1) & 7))) * 8);
+          acc[r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wb, xa, acc[r], 0, 0, 0);
+        }
+      }
+    }
+    __syncthreads();  // every wave done with the LDS before a next tile's loads
+    if (c < Nout) {
+#pragma unroll
+      for (int r = 0; r < kSlimTM / 16; ++r) {
+        if (drow[r] < 0) continue;
+        const f32x4_t& a = acc[r];
+        *reinterpret_cast<u32x2_t*>(dst + int64_t(drow[r]) * Nout + c) =
+            u32x2_t{pack2_bf16(a[0] + bv[0], a[1] + bv[1]), pack2_bf16(a[2] + bv[2], a[3] + bv[3])};
+      }
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
 // fp32 grouped GEMM (fp32 layers) on the fp32 matrix cores
 // (v_mfma_f32_16x16x4_f32, fp32 products accumulated in fp32).
 //
@@ -1866,8 +1969,7 @@ hipError_t launch_gemm(const Shape& s, const FfnPlan& plan, const void* A, const
           b.tiles + 2 * (G + 1) + (KIND == kUp ? 0 : 1), static_cast<const float*>(nullptr), o, osh);
     } else if (tn == kBigTN) {
       launch_kernel(&gemm_bf16_big_kernel<KIND, ACT>, dim3(device_cus()), dim3(kBigThreads), 0, st,
-          a, w, wsh, b.off, toff, b.list, b.row_dst, s.E, G, s.k, K, Nout,
-          static_cast<const float*>(nullptr), o, osh);
+          a, w, wsh, b.off, toff, b.list, b.row_dst, s.E, G, s.k, K, Nout, o, osh);
     } else if (tn == 128) {
       launch_kernel(&gemm_bf16_kernel<128, 128, KIND, ACT>, dim3(grid), dim3(kGemmThreads), 0, st,
           a, w, wsh, b.off, toff, b.list, b.row_dst, s.E, G, s.k, K, Nout, o, osh);
@@ -2009,18 +2111,33 @@ hipError_t launch_ffn_down(const Shape& s, const void* W_down, const void* W_dow
                                       b.h_sh, st);
 }
 
+// 256-column tiles when the 64 x 64 ones would take more than about three
+// rounds over the CUs (at K = 1152 a round of them is 6 us, a 256-column tile
+// of 128 rows 18) and the tile can be taken.
+bool proj_tall(int64_t T, int K, int Nout) {
+  const int64_t slim = (T + kSlimTM - 1) / kSlimTM * ((Nout + kSlimTN - 1) / kSlimTN);
+  return slim > 3 * device_cus() && tall_capable(T, K, Nout);
+}
+
+int proj_tile_cols(bool tall) { return tall ? kTallTN : kSlimTN; }
+
 hipError_t launch_proj(const void* A, const void* W, const float* bias, const int32_t* off,
-                       const int32_t* tiles, const int32_t* list, int K, int Nout, void* dst,
-                       hipStream_t st, int blocks_per_xcd) {
-  if (K % kTK != 0 || Nout < 1 || blocks_per_xcd < 0) return hipErrorInvalidValue;
+                       const int32_t* tiles, const int32_t* list, const int32_t* tm, int64_t T,
+                       int K, int Nout, void* dst, hipStream_t st, int blocks_per_xcd) {
+  if (K % kTK != 0 || Nout % 4 != 0 || Nout < 1 || blocks_per_xcd < 0) return hipErrorInvalidValue;
   // the grid stays a multiple of the XCD count (block b runs on XCD b % 8)
   const int grid = blocks_per_xcd > 0 ? kXcds * std::min(blocks_per_xcd, cus_per_xcd())
                                       : device_cus();
   const auto* w = static_cast<const uint16_t*>(W);
-  launch_kernel(&gemm_bf16_big_kernel<kProj, kActBias>, dim3(grid), dim3(kBigThreads), 0,
-                st, static_cast<const uint16_t*>(A), w, w, off, tiles, list,
-                static_cast<const int32_t*>(nullptr), 1, 1, 1, K, Nout, bias,
-                static_cast<uint16_t*>(dst), static_cast<uint16_t*>(dst));
+  if (proj_tall(T, K, Nout))
+    launch_kernel(&gemm_bf16_tall_kernel<kProj, kActBias>, dim3(grid), dim3(kTallThreads), 0, st,
+                  static_cast<const uint16_t*>(A), w, w, off, tiles, list,
+                  static_cast<const int32_t*>(nullptr), 1, 1, 1, K, Nout, tm, bias,
+                  static_cast<uint16_t*>(dst), static_cast<uint16_t*>(dst));
+  else
+    launch_kernel(&gemm_bf16_slim_kernel, dim3(grid), dim3(kSlimThreads), 0, st,
+                  static_cast<const uint16_t*>(A), w, off, tiles, list, K, Nout, bias,
+                  static_cast<uint16_t*>(dst));
   return hipGetLastError();
 }
 

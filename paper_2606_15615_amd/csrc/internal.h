@@ -204,8 +204,7 @@ const Buffers& layer_buffers(const moeca_layer* L);
 // ---- DiT block kernels (block.hip, ffn.hip) -----------------------------
 constexpr int kFreqDim = 256;    // timestep embedding width
 constexpr int kMaxWidth = 2048;  // largest block width d
-constexpr int kProjTM = 128;     // projection GEMM tile: rows
-constexpr int kProjTN = 256;     // and output columns
+constexpr int kSlimRows = 64;    // rows of a 64-column projection tile, at most
 
 // Shared per-step activations of a block stack (device).
 struct BlockBufs {
@@ -224,17 +223,22 @@ struct BlockBufs {
   int32_t* slist;  // [T] synchronised tokens by sample
   int32_t* soff;   // [B+1]
   int32_t* ident;  // [T] identity row list
-  int32_t* tab;    // [8] projection row offsets and tile counts (see launch_slist)
+  int32_t* tab;    // [10] projection row offsets, tile counts and heights (see launch_slist)
 };
 
 // dst[list[r]] = bf16(A[list[r]] . W^T + bias) for r < off[1]: one group of
-// listed rows (tables off[2], tiles[2] on the device), K inputs, Nout outputs.
+// listed rows out of T (tables off[2], tiles[2] and, for the 256-column tiles,
+// the tile height tm on the device), K inputs, Nout outputs (a multiple of 4).
 // blocks_per_xcd > 0 gives the persistent grid that many blocks per XCD
 // instead of one per CU (the rest of the CUs stay free for kernels on another
 // stream that run beside it).
 hipError_t launch_proj(const void* A, const void* W, const float* bias, const int32_t* off,
-                       const int32_t* tiles, const int32_t* list, int K, int Nout, void* dst,
-                       hipStream_t st, int blocks_per_xcd = 0);
+                       const int32_t* tiles, const int32_t* list, const int32_t* tm, int64_t T,
+                       int K, int Nout, void* dst, hipStream_t st, int blocks_per_xcd = 0);
+// Whether a projection of up to T rows takes the 256-column tiles (of 256, 192
+// or 128 rows) or the 64 x 64 ones, and the columns of a tile of either kind.
+bool proj_tall(int64_t T, int K, int Nout);
+int proj_tile_cols(bool tall);
 // CUs per XCD (the device's CU count over 8).
 int cus_per_xcd();
 hipError_t launch_sinusoid(const float* t_values, int B, double* e, hipStream_t st);

@@ -23,6 +23,7 @@
 #include <string>
 #include <vector>
 
+#include "common.h"
 #include "internal.h"
 #include "moeca.h"
 
@@ -154,7 +155,7 @@ moeca_stack* moeca_stack_create(int n_blocks, int d, int heads, int E, int k, in
   b[S_SLIST] = T * 4;
   b[S_SOFF] = size_t(S->B + 1) * 4;
   b[S_IDENT] = T * 4;
-  b[S_TAB] = 8 * 4;
+  b[S_TAB] = 10 * 4;
   b[S_SC] = size_t(S->B) * d * 8;
   b[S_EMB] = size_t(S->B) * moeca::kFreqDim * 8;
   b[S_H1] = size_t(S->B) * d * 8;
@@ -318,20 +319,23 @@ int moeca_stack_step_blocks(moeca_stack* S, float* x, const float* c, int t, int
     }
     // On a cache step its persistent grid takes only as many blocks per XCD
     // as it needs to finish in the rounds of tiles it takes on every CU
-    // (1024 x 8 tokens: 576 tiles, 72 per XCD, three rounds: 24 of an
-    // XCD's 32 CUs), so that the decision kernels beside it find free CUs
-    // (the one-block-per-sample decide kernel, 1024 threads, cannot share a
-    // CU with a GEMM block) and the q projection starts on them.
+    // (1024 x 8 tokens of width 1152: 387 tiles of 192 rows, 49 per XCD, two
+    // rounds: 25 of an XCD's 32 CUs), so that the decision kernels beside it
+    // find free CUs (the one-block-per-sample decide kernel, 1024 threads,
+    // cannot share a CU with a GEMM block) and the q projection starts on them.
     int kv_share = 0;
     if (fork && !full) {
-      const int per_xcd =
-          ((T + moeca::kProjTM - 1) / moeca::kProjTM * ((2 * d + moeca::kProjTN - 1) / moeca::kProjTN) +
-           7) / 8;
+      const bool tall = moeca::proj_tall(T, d, 2 * d);
+      const int cols = moeca::proj_tile_cols(tall);
+      const int nt = (2 * d + cols - 1) / cols;
+      const int cus = moeca::cus_per_xcd() * 8;
+      const int tm = tall ? moeca::tall_rows_one(T, nt, cus) : moeca::kSlimRows;
+      const int per_xcd = ((T + tm - 1) / tm * nt + 7) / 8;
       const int rounds = (per_xcd + moeca::cus_per_xcd() - 1) / moeca::cus_per_xcd();
       kv_share = std::max(1, (per_xcd + rounds - 1) / std::max(1, rounds));
     }
-    rc = hip(moeca::launch_proj(k.h, Wkv, W.b_qkv + d, k.tab + 4, k.tab + 6, k.ident, d, 2 * d,
-                                k.kv, fork ? S->side : st, kv_share),
+    rc = hip(moeca::launch_proj(k.h, Wkv, W.b_qkv + d, k.tab + 4, k.tab + 6, k.ident, k.tab + 9,
+                                T, d, 2 * d, k.kv, fork ? S->side : st, kv_share),
              "kv projection");
     if (fork) {
       // the side stream's end is recorded even after a failed launch, so
@@ -354,12 +358,14 @@ int moeca_stack_step_blocks(moeca_stack* S, float* x, const float* c, int t, int
     // queries, attention, output projection and LN2 of the listed tokens
     auto refresh = [&](uint16_t* u_out) -> int {
       int r;
-      if ((r = hip(moeca::launch_proj(k.h, Wq, W.b_qkv, k.tab, k.tab + 2, k.slist, d, d, k.q, st),
+      if ((r = hip(moeca::launch_proj(k.h, Wq, W.b_qkv, k.tab, k.tab + 2, k.slist, k.tab + 8, T,
+                                  d, d, k.q, st),
                    "q projection")) != MOECA_OK)
         return r;
       if ((r = join()) != MOECA_OK) return r;
       if ((r = hip(moeca::launch_attention(k, N, H, dh, st), "attention")) != MOECA_OK) return r;
-      if ((r = hip(moeca::launch_proj(k.o, W.W_o, W.b_o, k.tab, k.tab + 2, k.slist, d, d, a, st),
+      if ((r = hip(moeca::launch_proj(k.o, W.W_o, W.b_o, k.tab, k.tab + 2, k.slist, k.tab + 8, T,
+                                  d, d, a, st),
                    "output projection")) != MOECA_OK)
         return r;
       return hip(moeca::launch_ln_mlp(k, T, N, d, mod, full ? nullptr : mod_prev, a, u_out, full,

@@ -254,6 +254,17 @@ def test_stack_head_widths_ragged_forced(d, heads):
     run_forced(SS, 3)
 
 
+@pytest.mark.parametrize("B,N", [(16, 345), (3, 257), (2, 32)])
+def test_stack_projection_tiles_forced(B, N):
+    """Projection tilings at d = 576 (nine k-tiles, 64-column remainders): 5520
+    tokens take the 256-column tiles for q, k/v and the output, 771 and 64 the
+    64 x 64 ones (parts of 60 rows, and one exactly full)."""
+    sh = StackShape(L=1, d=576, heads=8, E=4, k=2, d_ff=128, B=B, N=N)
+    say(f"projection tiles {B} x {N}")
+    SS = StackSetup(sh, mode="ratio", seed=4, T=2, ratio=0.5)
+    run_forced(SS, 2)
+
+
 def test_stack_full_mode_forced():
     """The uncached comparator: every step is a full step."""
     say("stack_tiny full mode")
