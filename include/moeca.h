@@ -206,10 +206,13 @@ typedef struct moeca_stats {
   double reuse_over_match; /* n_reused / n_matched (Sec. 5.4, Fig. 8); 0 if none */
   int32_t expert_count[64];/* recomputed branches per expert                  */
   int32_t ffn_plan;        /* tiling of the last step's expert FFN: 0 the
-                              128 x 256 or 256 x 256 tiles, 1 the weight-streaming tiles
-                              (few rows per expert), 2 the expert-wide
-                              up-projection tiles (a few hundred rows per
-                              expert) with a down projection as in 0         */
+                              128 x 256 or 256 x 256 tiles, 1 a cache step in
+                              the weight-streaming tiles (few rows per
+                              expert), 2 the expert-wide up-projection tiles
+                              (a few hundred rows per expert) with a down
+                              projection as in 0; a full step with few rows
+                              per expert also streams its weights and reports
+                              2 or, where the layer cannot take those, 0    */
 } moeca_stats;
 
 /* Copy the last step's statistics to *out.  Synchronises the stream. */

@@ -1917,7 +1917,7 @@ hipError_t launch_gemm(const Shape& s, const FfnPlan& plan, const void* A, const
       return hipGetLastError();
     }
   }
-  if (plan.thin) {
+  if (KIND == kUp ? plan.thin_up : plan.thin_down) {
     // bf16, ungated, no shared experts (thin_capable)
     if constexpr (ACT == kActSwiglu || ACT == kActBias) {
       return hipErrorInvalidValue;
@@ -2016,7 +2016,7 @@ static bool tall_capable(int64_t rows, int K, int Nout) {
 // partial last N tile is masked); smaller ones the 128 x 128 / 128 x 64
 // tiles; the thin plan the 128 x 288 tile; the wide plan the expert-wide
 // 384 x 144 up-projection tile (the down projection keeps the large tile).
-FfnPlan ffn_plan(const Shape& s, bool thin, bool wide, int64_t mean_rows) {
+FfnPlan ffn_plan(const Shape& s, int64_t rows, bool partials) {
   auto tn = [](int n) { return n >= 512 ? kBigTN : (n % 128 == 0 ? 128 : 64); };
   FfnPlan p;
   p.tm = p.tm_up = 128;
@@ -2026,29 +2026,33 @@ FfnPlan ffn_plan(const Shape& s, bool thin, bool wide, int64_t mean_rows) {
     p.split_down = f32_split(s);
     return p;
   }
-  if (thin && thin_capable(s)) {
-    p.thin = true;
-    p.tn_up = p.tn_down = kThinTN;
-    p.split_down = kThinSplit;
-    return p;
-  }
+  const int64_t mean_rows = (rows + s.S * s.tokens()) / s.groups();
+  const bool few = rows <= int64_t(kThinRows) * s.E && thin_capable(s);
+  p.thin_up = few;
+  p.thin_down = few && partials;
   p.tn_up = tn(s.up_rows());
   p.tn_down = tn(s.d);
   p.tall_up = tall_capable(s.tokens(), s.d, s.up_rows()) && mean_rows >= kTallRows;
   p.tall_down = tall_capable(s.mid_rows(), s.d_ff, s.d) && mean_rows >= kTallRows;
-  if (p.tall_up) {
-    p.tm_up = kTallTM;
-    p.tn_up = kTallTN;
-  }
-  if (p.tall_down) {
-    p.tm = kTallTM;
-    p.tn_down = kTallTN;
-  }
-  if (wide && wide_capable(s)) {
+  if (p.thin_up) {
+    p.tall_up = false;
+    p.tn_up = kThinTN;
+  } else if (rows <= int64_t(kWideRows) * s.E && wide_capable(s)) {
     p.tall_up = false;
     p.wide_up = true;
     p.tm_up = kWideTM;
     p.tn_up = kWideTN;
+  } else if (p.tall_up) {
+    p.tm_up = kTallTM;
+    p.tn_up = kTallTN;
+  }
+  if (p.thin_down) {
+    p.tall_down = false;
+    p.tn_down = kThinTN;
+    p.split_down = kThinSplit;
+  } else if (p.tall_down) {
+    p.tm = kTallTM;
+    p.tn_down = kTallTN;
   }
   return p;
 }

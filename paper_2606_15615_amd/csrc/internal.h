@@ -115,19 +115,24 @@ struct FfnPlan {
   int tn_up;
   int tn_down;
   int split_down = 1;
-  bool thin = false;
+  bool thin_up = false, thin_down = false;  // the weight-streaming kernel
   bool wide_up = false;  // the up projection takes the expert-wide kernel
   int tm_up = 128;       // M tile of the up projection's tile table
   bool tall_up = false, tall_down = false;  // the 256 x 256 tiles (tm chosen on the device)
 };
 constexpr int kThinSplit = 4;
-// A ratio-mode cache step takes the thin plan when its budget leaves at most
-// this many rows per expert on average (unmatched branches come on top).
+// A step takes the weight-streaming tiles for both projections when it is
+// expected to leave at most this many rows per expert on average (the
+// unmatched branches of a cache step come on top).  Measured (16 experts of
+// 1152 x 4608): a full step with 32 rows per expert, up and down, 108 us with
+// the expert-wide and the 128 x 256 tiles, 63 us with these; with 256 rows 144
+// against 205 us (two 128-row tiles read each weight slice twice).
 constexpr int kThinRows = 112;
-// A ratio-mode cache step with more rows per expert than that, and at most
-// this many on average, takes the expert-wide up-projection tiles (all of
-// an expert's rows, up to 384, by 144 columns); so does a full step with at
-// most this many branches per expert on average.
+// A step with more rows per expert than that, and at most this many on
+// average, takes the expert-wide up-projection tiles (all of an expert's
+// rows, up to 384, by 144 columns).  Measured (same experts): 307 rows 75
+// against 92 us; a threshold-mode step with about 232, in the 128 x 256 tiles
+// before, the cycle of three 655 -> 591 us.
 constexpr int kWideRows = 320;
 // Steps with at least this many rows per group (routed and shared experts)
 // on average take the 256 x 256 tiles.  Measured sides (16 experts of 1152 x
@@ -135,8 +140,9 @@ constexpr int kWideRows = 320;
 // us, 307 rows down 80 against 76, 256 rows down 74 against 76, 225 rows up 49
 // against 53 and down 62 against 66 us.
 constexpr int kTallRows = 288;
-// mean_rows: rows per group that the step is expected to have, on average.
-FfnPlan ffn_plan(const Shape& s, bool thin, bool wide, int64_t mean_rows);
+// rows: branches the routed experts are expected to have in this step;
+// partials: the down projection may split K (its partial sums have a place).
+FfnPlan ffn_plan(const Shape& s, int64_t rows, bool partials);
 // K pieces of an fp32 layer's down projection (1: not split).  Above 1 the
 // workspace holds `part`.
 int f32_split(const Shape& s);

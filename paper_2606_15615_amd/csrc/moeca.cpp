@@ -316,9 +316,10 @@ int moeca_forward_noalloc(const moeca_layer* L, const void* x, int samples, void
     return fail(MOECA_E_INVAL, "samples must be in [1, " + std::to_string(L->shape.B) + "]");
   Shape s = L->shape;
   s.B = samples;
-  // with the down projection's K pieces if they fit (fp32 layers; a bf16
-  // call never splits)
-  Layout lay = make_layout(s, false, !s.bf16);
+  // with the down projection's K pieces if they fit (fp32 layers, and bf16
+  // calls of few enough rows for the weight-streaming tiles)
+  const bool split = !s.bf16 || s.branches() <= int64_t(moeca::kThinRows) * s.E;
+  Layout lay = make_layout(s, false, split);
   if (lay.total > moeca::kNoallocScratchBytes) lay = make_layout(s, false, false);
   if (lay.total > moeca::kNoallocScratchBytes)
     return fail(MOECA_E_INVAL, "this call needs " + std::to_string(lay.total) +
@@ -335,7 +336,7 @@ int moeca_forward_noalloc(const moeca_layer* L, const void* x, int samples, void
   const Buffers b = map_buffers(static_cast<char*>(base), lay, nullptr);
   const moeca_policy& p = L->pol;
   const auto st = static_cast<hipStream_t>(stream);
-  moeca::FfnPlan plan = moeca::ffn_plan(s, false, false, s.mid_rows() / s.groups());
+  moeca::FfnPlan plan = moeca::ffn_plan(s, s.branches(), b.part != nullptr);
   if (b.part == nullptr) plan.split_down = 1;
   // the uncached layer: every branch recomputed, no statistic, no cache
   // metadata and no attention path (the MOECA_MODE_FULL step)
@@ -449,23 +450,17 @@ int layer_step(moeca_layer* L, const void* x_t, const void* x_ffn, int t, void* 
                                   p.alpha, b, st),
              "decide"))
     return MOECA_E_HIP;
-  // ratio-mode cache steps whose budget leaves few rows per expert stream
-  // the weights with the thin plan
-  const bool thin = !full && p.mode == MOECA_MODE_RATIO &&
-                    int64_t(budget) * s.B <= int64_t(moeca::kThinRows) * s.E &&
-                    L->buf.part != nullptr;
-  // and those that leave a few hundred take the expert-wide up projection,
-  // as do full steps of that many rows per expert (every branch)
-  const bool wide = (full ? int64_t(s.B) * s.N * s.k <= int64_t(moeca::kWideRows) * s.E
-                          : p.mode == MOECA_MODE_RATIO &&
-                                int64_t(budget) * s.B <= int64_t(moeca::kWideRows) * s.E);
-  // rows the FFN is expected to have: every branch on full steps, the budget
-  // in ratio mode; a threshold step's count is not known to the host (half)
+  // rows the routed experts are expected to have: every branch on full
+  // steps, the budget in ratio mode; a threshold step's count is not known to
+  // the host (the default settings recompute five eighths of the branches)
   const int64_t rows = full ? s.branches()
                        : p.mode == MOECA_MODE_RATIO ? int64_t(budget) * s.B
-                                                    : s.branches() / 2;
-  const moeca::FfnPlan plan =
-      moeca::ffn_plan(s, thin, wide, (rows + s.S * s.tokens()) / s.groups());
+                                                    : s.branches() * 5 / 8;
+  // A full step of a stack's block adds K in one piece: its output goes on
+  // into every later block's router, where another order of the sums moves
+  // tied branches.  (The up projection's sums are the same in any tiling.)
+  const bool pieces = b.part != nullptr && !(full && s.bf16 && L->mid_outside);
+  const moeca::FfnPlan plan = moeca::ffn_plan(s, rows, pieces);
   arm();
   if (!check(moeca::launch_lists(s, plan, b, st), "lists")) return MOECA_E_HIP;
   if (between) {
@@ -485,7 +480,9 @@ int layer_step(moeca_layer* L, const void* x_t, const void* x_ffn, int t, void* 
   if (timed) ++L->timed_steps;
   if (!uncached) L->valid = true;
   L->last_full = full;
-  L->last_plan = plan.thin ? 1 : plan.wide_up ? 2 : 0;
+  // a full step reports its size class whichever tiles stream its weights
+  L->last_plan = plan.thin_up && !full ? 1
+                 : plan.wide_up || (plan.thin_up && moeca::wide_capable(s)) ? 2 : 0;
   return MOECA_OK;
 }
 

@@ -366,6 +366,19 @@ def test_thin_plan_trajectory(shape, ratio):
     assert [i["ffn_plan"] for i in infos] == [full_step_plan(S.shape), 1, 1, 1]
 
 
+@pytest.mark.parametrize("shape,plan", [
+    (THIN_SHAPES[0][0], 1),
+    (LayerShape(d=576, E=8, k=2, d_ff=1152, B=4, N=512, dtype="bf16"), 2),
+])
+def test_threshold_mode_plans(shape, plan):
+    """Threshold-mode cache steps choose their tiles by an expected row count:
+    20 rows per expert (weight-streaming tiles) and 320, the most that take
+    the expert-wide up projection."""
+    S = Setup(shape, mode="threshold", seed=32, T=3, refresh_cycle=0)
+    infos = run_forced(S, 3, label=f"threshold {shape}")
+    assert [i["ffn_plan"] for i in infos] == [full_step_plan(S.shape), plan, plan]
+
+
 # ---------------------------------------------------------------------------
 # The expert-wide up projection at sizes the oracle evaluates whole: up to
 # 384 rows of an expert in one tile by 144 columns; experts past 384 rows

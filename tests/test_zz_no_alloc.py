@@ -53,6 +53,8 @@ CASES = [
     # gated experts with a shared expert, ragged token count
     (LayerShape(d=256, E=8, k=2, d_ff=128, B=3, N=77, dtype="bf16", ffn="swiglu", n_shared=1),
      "swiglu", 3, 1),
+    # 32 rows per expert, then 16: the weight-streaming tiles, K in four pieces
+    (LayerShape(d=576, E=16, k=2, d_ff=2304, B=2, N=128, dtype="bf16"), "gelu_erf", 2, 1),
     # fp32 layer with erf GELU
     (LayerShape(d=384, E=8, k=2, d_ff=1536, B=2, N=256, dtype="fp32"), "gelu_erf", 2, 1),
 ]
