@@ -64,7 +64,10 @@ constexpr int kXcds = 8;
 // against 4.5e-7 and 1.1e-5 of 0.5 z (1 + erff(z / sqrt 2)); it has no
 // branch, where erff's two ranges both ran in every wave.  With erff the
 // epilogue took a fifth of the up projection (3 x 1000 tokens, 16 experts).
-enum { kActGeluTanh = 0, kActGeluErf = 1, kActNone = 2, kActSwiglu = 3, kActBias = 4 };
+// kActGeluErff keeps erff: a block of a stack hands its output on to the later
+// blocks' routers, where other last bits move tied branches.
+enum { kActGeluTanh = 0, kActGeluErf = 1, kActNone = 2, kActSwiglu = 3, kActBias = 4,
+       kActGeluErff = 5 };
 
 // silu(z) = z / (1 + exp(-z)), exp(-z) = 2^(-z log2 e) by the hardware exp2.
 __device__ __forceinline__ float silu_f(float z) {
@@ -88,6 +91,8 @@ __device__ __forceinline__ float act_fn(float z) {
     q = fmaf(q, a, -1.1511110067f);
     const float h = __builtin_amdgcn_exp2f(fmaf(a, q, -1.0f));
     return fmaf(-a, h, z < 0.0f ? z * 0.0f : z);  // (z 0: -inf and NaN stay NaN)
+  } else if constexpr (ACT == kActGeluErff) {
+    return 0.5f * z * (1.0f + erff(z * 0.7071067811865476f));
   } else {
     return z;
   }
@@ -2100,12 +2105,15 @@ int device_cus() {
 }
 
 hipError_t launch_ffn_up(const Shape& s, const void* x, const void* W_up, const void* W_up_sh,
-                         int act, const FfnPlan& plan, const Buffers& b, hipStream_t st) {
+                         int act, bool chained, const FfnPlan& plan, const Buffers& b,
+                         hipStream_t st) {
   const int n = s.up_rows();
   if (act == MOECA_ACT_SWIGLU)
     return launch_gemm<kUp, kActSwiglu>(s, plan, x, W_up, W_up_sh, s.d, n, b, b.mid, b.mid, st);
   if (act == MOECA_ACT_GELU_ERF)
     return launch_gemm<kUp, kActGeluErf>(s, plan, x, W_up, W_up_sh, s.d, n, b, b.mid, b.mid, st);
+  if (act == MOECA_ACT_GELU_ERF && chained)
+    return launch_gemm<kUp, kActGeluErff>(s, plan, x, W_up, W_up_sh, s.d, n, b, b.mid, b.mid, st);
   return launch_gemm<kUp, kActGeluTanh>(s, plan, x, W_up, W_up_sh, s.d, n, b, b.mid, b.mid, st);
 }
 
