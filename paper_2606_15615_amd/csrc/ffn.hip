@@ -1936,12 +1936,13 @@ hipError_t launch_gemm(const Shape& s, const FfnPlan& plan, const void* A, const
         // the addition of the partial sums
         const LaunchEvents ev = launch_events();
         launch_events() = LaunchEvents{};
+        const bool reduce = !combine_sums(s);
         launch_kernel_ev(&gemm_bf16_thin_kernel<kDown, kActNone, kThinSplit>, dim3(device_cus()),
-                         dim3(kThinThreads), 0, st, ev.start, nullptr, a, w, b.off, toff, b.list,
+                         dim3(kThinThreads), 0, st, ev.start, reduce ? nullptr : ev.stop, a, w, b.off, toff, b.list,
                          b.row_dst, s.E, s.k, K, Nout, rows, static_cast<uint16_t*>(nullptr),
                          b.part);
         const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
+        if (e != hipSuccess || !reduce) return e;
         launch_kernel_ev(&reduce_partials_kernel<kThinSplit>,
                          dim3(static_cast<unsigned>((rows + 3) / 4)), dim3(256), 0, st, nullptr,
                          ev.stop, static_cast<const float*>(b.part), rows, b.off, b.row_dst, s.E,
@@ -1985,18 +1986,19 @@ hipError_t launch_gemm(const Shape& s, const FfnPlan& plan, const void* A, const
   } else {
     const int32_t* toff = b.tiles + (KIND == kUp ? 0 : G + 1);
     const int split = KIND == kDown && b.part != nullptr ? plan.split_down : 1;
+    const bool reduce = split > 1 && !combine_sums(s);
     const int64_t rows = s.mid_rows();
     // the stage's start event goes with the GEMM, its stop event with the
     // addition of the partial sums
     LaunchEvents ev = launch_events();
     launch_events() = LaunchEvents{};
     launch_kernel_ev(&gemm_f32_kernel<KIND, ACT>, dim3(device_cus() * kF32Blocks),
-                     dim3(kF32Threads), 0, st, ev.start, split > 1 ? nullptr : ev.stop,
+                     dim3(kF32Threads), 0, st, ev.start, reduce ? nullptr : ev.stop,
                      static_cast<const float*>(A), static_cast<const float*>(W),
                      static_cast<const float*>(Wsh), b.off, toff, b.list, b.row_dst, s.E, G, s.k,
                      K, Nout, split, rows, static_cast<float*>(dst), static_cast<float*>(dst_sh),
                      b.part);
-    if (split > 1) {
+    if (reduce) {
       const hipError_t e = hipGetLastError();
       if (e != hipSuccess) return e;
       launch_kernel_ev(&reduce_partials_f32_kernel,
@@ -2110,10 +2112,10 @@ hipError_t launch_ffn_up(const Shape& s, const void* x, const void* W_up, const 
   const int n = s.up_rows();
   if (act == MOECA_ACT_SWIGLU)
     return launch_gemm<kUp, kActSwiglu>(s, plan, x, W_up, W_up_sh, s.d, n, b, b.mid, b.mid, st);
-  if (act == MOECA_ACT_GELU_ERF)
-    return launch_gemm<kUp, kActGeluErf>(s, plan, x, W_up, W_up_sh, s.d, n, b, b.mid, b.mid, st);
   if (act == MOECA_ACT_GELU_ERF && chained)
     return launch_gemm<kUp, kActGeluErff>(s, plan, x, W_up, W_up_sh, s.d, n, b, b.mid, b.mid, st);
+  if (act == MOECA_ACT_GELU_ERF)
+    return launch_gemm<kUp, kActGeluErf>(s, plan, x, W_up, W_up_sh, s.d, n, b, b.mid, b.mid, st);
   return launch_gemm<kUp, kActGeluTanh>(s, plan, x, W_up, W_up_sh, s.d, n, b, b.mid, b.mid, st);
 }
 

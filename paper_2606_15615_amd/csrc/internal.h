@@ -176,8 +176,12 @@ hipError_t launch_ffn_up(const Shape& s, const void* x, const void* W_up, const 
 // rows, except where the combine does (combine_sums).
 hipError_t launch_ffn_down(const Shape& s, const void* W_down, const void* W_down_sh,
                            const FfnPlan& plan, const Buffers& b, hipStream_t st);
-hipError_t launch_combine(const Shape& s, int write_cache, void* out, const void* attn_in,
-                          void* attn_cache, const Buffers& b, hipStream_t st);
+// pieces: 1, or the K pieces whose partial sums the combine adds into the
+// cache rows itself (layers of combine_sums)
+hipError_t launch_combine(const Shape& s, int write_cache, int pieces, void* out,
+                          const void* attn_in, void* attn_cache, const Buffers& b,
+                          hipStream_t st);
+bool combine_sums(const Shape& s);
 hipError_t launch_reset(const Shape& s, const Buffers& b, hipStream_t st);
 
 // ---- the entry point that allocates nothing (noalloc.hip) --------------

@@ -349,7 +349,8 @@ int moeca_forward_noalloc(const moeca_layer* L, const void* x, int samples, void
           hipSuccess &&
       (e = moeca::launch_ffn_down(s, L->W_down, L->W_down_sh, plan, b, st)) ==
           hipSuccess)
-    e = moeca::launch_combine(s, 0, out, nullptr, nullptr, b, st);
+    e = moeca::launch_combine(s, 0, moeca::combine_sums(s) ? plan.split_down : 1, out, nullptr,
+                              nullptr, b, st);
   if (e != hipSuccess) return fail(MOECA_E_HIP, std::string("launch: ") + hipGetErrorString(e));
   return MOECA_OK;
 }
@@ -476,7 +477,9 @@ int layer_step(moeca_layer* L, const void* x_t, const void* x_ffn, int t, void* 
   if (!check(moeca::launch_ffn_down(s, L->W_down, L->W_down_sh, plan, b, st), "ffn down"))
     return MOECA_E_HIP;
   arm();
-  if (!check(moeca::launch_combine(s, uncached ? 0 : 1, out, L->attn_in, L->attn_cache, b, st),
+  if (!check(moeca::launch_combine(s, uncached ? 0 : 1,
+                                   moeca::combine_sums(s) ? plan.split_down : 1, out, L->attn_in,
+                                   L->attn_cache, b, st),
              "combine"))
     return MOECA_E_HIP;
   if (timed) ++L->timed_steps;
