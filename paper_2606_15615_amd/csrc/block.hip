@@ -84,99 +84,115 @@ __global__ void silu_kernel(const float* __restrict__ in, int n, double* __restr
 // (every block's AdaLN map at once).
 //
 // The products run on the fp64 matrix cores (v_mfma_f64_16x16x4f64), which
-// here deliver several times the fp64 rate of the vector units: a wave
-// takes 16 weight rows (the A operand) against up to kGemvSamples samples
-// (the B operand; the other columns of the 16 are zero and discarded).
-// Lane l loads 8 consecutive bf16 of weight row l % 16 at columns
-// c + 8 (l / 16) of each 32-column block c and feeds them to 8 MFMAs in turn,
-// MFMA u taking column c + 8 (l / 16) + u for k-row l / 16 in both operands,
-// so that one 16-byte load serves 8 MFMAs, and kGemvDepth such loads are in
-// flight per lane.  The samples' inputs are staged in LDS once per block
-// (persistent blocks walk the 16-row tiles of all the matrices).  Four
-// accumulator chains rotate over the MFMAs and are added in a fixed order
-// (eight were slower).  The AdaLN vectors feed the routing input, so they
+// here deliver several times the fp64 rate of the vector units: a tile is 16
+// weight rows (the A operand) against up to kGemvSamples samples (the B
+// operand; the other columns of the 16 are zero and discarded).  Lane l loads
+// 8 consecutive bf16 of weight row l % 16 at columns c + 8 (l / 16) of each
+// 32-column block c and feeds them to 8 MFMAs in turn, MFMA u taking column
+// c + 8 (l / 16) + u for k-row l / 16 in both operands, so that one 16-byte
+// load serves 8 MFMAs.
+//
+// The eight waves of a block split a tile's K: wave w takes the 32-column
+// blocks w, w + 8, ... (at most kGemvDepth), whose sample values it keeps in
+// registers for every tile the block walks; a block's weights are requested
+// again, for the next tile, as soon as they are converted.  Four accumulator
+// chains rotate over the MFMAs; the chains, then the waves' sums (through LDS,
+// one barrier per tile), are added in a fixed order.  One wave per tile left a
+// chain of K / 4 MFMAs and of K / 256 waits on memory, with 72 waves on 256 CUs
+// for a 1152 x 1152 map: 18 against 8.8 us.  The twelve launches of a four-step
+// cycle (256 -> 1152, 1152 -> 1152, the AdaLN maps of all blocks) took 233 and
+// now take 174 us with one sample and four blocks, 250 and 160 us with eight
+// samples and two blocks.  The AdaLN vectors feed the routing input, so they
 // take the decision path's arithmetic: an fp64 evaluation with one rounding.
 constexpr int kGemvWaves = 8;
 constexpr int kGemvSamples = 8;
-constexpr int kGemvDepth = 8;  // 32-column blocks of weights in flight per wave
+constexpr int kGemvDepth = kMaxWidth / 32 / kGemvWaves;  // 32-column blocks of a wave, at most
 
 typedef __attribute__((ext_vector_type(4))) double f64x4_g;
 
+// DEPTH = ceil(K / 256): 32-column blocks of a wave, at most.
+template <int DEPTH>
 __global__ __launch_bounds__(kGemvWaves * kWave) void gemv_kernel(
     const double* __restrict__ in, int B, int K, GemvBatch mats, int n_mats, int Nout,
     const uint16_t* __restrict__ table, const int32_t* __restrict__ labels, int n_classes,
     double* __restrict__ out64) {
-  __shared__ __attribute__((aligned(16))) double s_in[kGemvSamples * kMaxWidth];  // 128 KB
+  __shared__ __attribute__((aligned(16))) f64x4_g s_sum[2][kGemvWaves][kWave];  // 32 KB
   const int lane = threadIdx.x & 63;
-  const int wv = threadIdx.x >> 6;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int n = lane & 15, g = lane >> 4;
   const int per_mat = (Nout + 15) / 16;
   const int tiles = per_mat * n_mats;
   const int nblk = K / 32;
+  int buf = 0;
   for (int b0 = 0; b0 < B; b0 += kGemvSamples) {
     const int nb = min(kGemvSamples, B - b0);
-    __syncthreads();  // every wave is done with the previous samples' inputs
-    for (int i = threadIdx.x; i < nb * K; i += kGemvWaves * kWave)
-      s_in[i] = in[int64_t(b0) * K + i];
-    __syncthreads();
-    const bool has_col = n < nb;  // B column n is a staged sample
-    const double* __restrict__ xin = s_in + (has_col ? n : 0) * K + 8 * g;
-    for (int tt = blockIdx.x + gridDim.x * wv; tt < tiles; tt += gridDim.x * kGemvWaves) {
-      const int m = tt / per_mat;
-      const int r0 = (tt % per_mat) * 16;
-      const uint16_t* __restrict__ wrow =
-          mats.W[m] + int64_t(min(r0 + n, Nout - 1)) * K + 8 * g;
+    auto wrow = [&](int tt) {
+      return mats.W[tt / per_mat] + int64_t(min((tt % per_mat) * 16 + n, Nout - 1)) * K + 8 * g;
+    };
+    u32x4_t raw[DEPTH];
+    if (static_cast<int>(blockIdx.x) < tiles) {
+      const uint16_t* w = wrow(blockIdx.x);
+#pragma unroll
+      for (int i = 0; i < DEPTH; ++i)
+        if (wv + kGemvWaves * i < nblk)
+          raw[i] = *reinterpret_cast<const u32x4_t*>(w + 32 * (wv + kGemvWaves * i));
+    }
+    // this lane's sample values: column n of the B operand
+    double xv[DEPTH][8];
+    const double* __restrict__ xin = in + int64_t(b0 + (n < nb ? n : 0)) * K + 8 * g;
+#pragma unroll
+    for (int i = 0; i < DEPTH; ++i)
+      if (wv + kGemvWaves * i < nblk)
+#pragma unroll
+        for (int e = 0; e < 8; e += 2) {
+          const double2 t2 =
+              *reinterpret_cast<const double2*>(xin + 32 * (wv + kGemvWaves * i) + e);
+          xv[i][e] = n < nb ? t2.x : 0.0;
+          xv[i][e + 1] = n < nb ? t2.y : 0.0;
+        }
+    for (int tt = blockIdx.x; tt < tiles; tt += gridDim.x) {
+      const int tn = tt + static_cast<int>(gridDim.x);
+      const uint16_t* const wn = wrow(min(tn, tiles - 1));
       f64x4_g acc[4];
 #pragma unroll
       for (int c = 0; c < 4; ++c) acc[c] = f64x4_g{0.0, 0.0, 0.0, 0.0};
-      u32x4_t raw[kGemvDepth];
 #pragma unroll
-      for (int d0 = 0; d0 < kGemvDepth; ++d0)
-        if (d0 < nblk) raw[d0] = *reinterpret_cast<const u32x4_t*>(wrow + 32 * d0);
-      for (int c0 = 0; c0 < nblk; c0 += kGemvDepth) {
+      for (int i = 0; i < DEPTH; ++i) {
+        const int c = wv + kGemvWaves * i;
+        if (c < nblk) {
+          double wv8[8];
 #pragma unroll
-        for (int d0 = 0; d0 < kGemvDepth; ++d0) {
-          const int c = c0 + d0;
-          if (c < nblk) {
-            double wv8[8], xv[8];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              wv8[2 * e] = __uint_as_float(raw[d0][e] << 16);
-              wv8[2 * e + 1] = __uint_as_float(raw[d0][e] & 0xffff0000u);
-            }
-            // the block kGemvDepth ahead reuses this register set
-            if (c + kGemvDepth < nblk)
-              raw[d0] = *reinterpret_cast<const u32x4_t*>(wrow + 32 * (c + kGemvDepth));
-#pragma unroll
-            for (int e = 0; e < 8; e += 2) {
-              const double2 t2 = *reinterpret_cast<const double2*>(xin + 32 * c + e);
-              xv[e] = has_col ? t2.x : 0.0;
-              xv[e + 1] = has_col ? t2.y : 0.0;
-            }
-#pragma unroll
-            for (int u = 0; u < 8; ++u)
-              acc[u & 3] = __builtin_amdgcn_mfma_f64_16x16x4f64(wv8[u], xv[u], acc[u & 3], 0, 0, 0);
+          for (int e = 0; e < 4; ++e) {
+            wv8[2 * e] = __uint_as_float(raw[i][e] << 16);
+            wv8[2 * e + 1] = __uint_as_float(raw[i][e] & 0xffff0000u);
           }
+          if (tn < tiles) raw[i] = *reinterpret_cast<const u32x4_t*>(wn + 32 * c);
+#pragma unroll
+          for (int u = 0; u < 8; ++u)
+            acc[u & 3] =
+                __builtin_amdgcn_mfma_f64_16x16x4f64(wv8[u], xv[i][u], acc[u & 3], 0, 0, 0);
         }
       }
-      // lane l, register r: weight row r0 + 4 r + l / 16, sample l % 16
-      const float* __restrict__ bias = mats.bias[m];
-      float* __restrict__ out = mats.out[m];
+      s_sum[buf][wv][lane] = (acc[0] + acc[1]) + (acc[2] + acc[3]);
+      __syncthreads();  // (the other buffer's readers are past their sums)
+      // wave w < 4 finishes register w of the sums: lane l has weight row
+      // 4 w + l / 16 of the tile, sample l % 16
+      const int m = tt / per_mat;
+      const int row = (tt % per_mat) * 16 + 4 * wv + g;
+      if (wv < 4 && n < nb && row < Nout) {
+        double v = 0.0;
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int row = r0 + 4 * r + g;
-        if (has_col && row < Nout) {
-          const int b = b0 + n;
-          double v = ((acc[0][r] + acc[1][r]) + (acc[2][r] + acc[3][r])) +
-                     static_cast<double>(bias[row]);
-          if (table != nullptr) {
-            const int lab = labels[b];
-            if (lab >= 0 && lab < n_classes) v += bf16_to_f32(table[int64_t(lab) * Nout + row]);
-          }
-          if (out64 != nullptr) out64[int64_t(b) * Nout + row] = silu64(v);
-          else out[int64_t(b) * Nout + row] = static_cast<float>(v);
+        for (int w = 0; w < kGemvWaves; ++w) v += s_sum[buf][w][lane][wv];
+        v += static_cast<double>(mats.bias[m][row]);
+        const int b = b0 + n;
+        if (table != nullptr) {
+          const int lab = labels[b];
+          if (lab >= 0 && lab < n_classes) v += bf16_to_f32(table[int64_t(lab) * Nout + row]);
         }
+        if (out64 != nullptr) out64[int64_t(b) * Nout + row] = silu64(v);
+        else mats.out[m][int64_t(b) * Nout + row] = static_cast<float>(v);
       }
+      buf ^= 1;
     }
   }
 }
@@ -777,13 +793,24 @@ hipError_t launch_gemv(const double* in, int B, int K, const GemvBatch& mats, in
                        double* out64, hipStream_t st) {
   if (K % 32 != 0 || K > kMaxWidth || n_mats < 1 || n_mats > kGemvBatch)
     return hipErrorInvalidValue;
-  // a small launch spreads its tiles over up to one block per CU (tile t
-  // goes to block t mod blocks, wave t / blocks mod kGemvWaves)
   const int tiles = (Nout + 15) / 16 * n_mats;
-  const int blocks = std::min(tiles, device_cus());
-  launch_kernel(&gemv_kernel, dim3(blocks), dim3(kGemvWaves * kWave), 0,
-                st, in, B, K, mats, n_mats, Nout, static_cast<const uint16_t*>(table), labels,
-                n_classes, out64);
+  const dim3 grid(std::min(tiles, device_cus())), block(kGemvWaves * kWave);
+  const auto* tab = static_cast<const uint16_t*>(table);
+#define MOECA_GEMV(D)                                                                     \
+  launch_kernel(&gemv_kernel<D>, grid, block, 0, st, in, B, K, mats, n_mats, Nout, tab,   \
+                labels, n_classes, out64)
+  static_assert(kGemvDepth == 8, "one instantiation per depth");
+  switch ((K / 32 + kGemvWaves - 1) / kGemvWaves) {
+    case 1: MOECA_GEMV(1); break;
+    case 2: MOECA_GEMV(2); break;
+    case 3: MOECA_GEMV(3); break;
+    case 4: MOECA_GEMV(4); break;
+    case 5: MOECA_GEMV(5); break;
+    case 6: MOECA_GEMV(6); break;
+    case 7: MOECA_GEMV(7); break;
+    default: MOECA_GEMV(8); break;
+  }
+#undef MOECA_GEMV
   return hipGetLastError();
 }
 
