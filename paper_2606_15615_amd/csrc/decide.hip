@@ -86,9 +86,11 @@ __device__ __forceinline__ int match_score(int e, float w, const int* ej, const 
 // order; on full steps branch p takes slot p.  sq / sm: the token's matched
 // slots and recompute flags; writes the k slots to sg and returns whether
 // any branch of the token is recomputed (its sync flag), adding the
-// recomputed count to rec.
+// recomputed count to rec.  sl, when set, also gets the slots (it may be sq:
+// entry p is read before it is written).
 __device__ __forceinline__ bool token_slots(const int8_t* sq, const uint8_t* sm, int k, bool full,
-                                            int32_t* __restrict__ sg, int& rec) {
+                                            int32_t* __restrict__ sg, int& rec,
+                                            int8_t* sl = nullptr) {
   bool any = false;
   uint32_t taken = 0;
   if (!full) {
@@ -115,14 +117,73 @@ __device__ __forceinline__ bool token_slots(const int8_t* sq, const uint8_t* sm,
       }
     }
     sg[p] = slot;
+    if (sl != nullptr) sl[p] = static_cast<int8_t>(slot);
   }
   return any;
 }
+// Group table entries E..E+S: the shared experts (Sec. 2.3, shared-expert
+// MoE eq.) follow the routed ones in the FFN's grouped GEMM, T rows each (every
+// token, in token order), so their offsets and tile prefixes continue the
+// routed totals (o rows, tu / td tiles).  Tile tables: up at [0, E+S],
+// down at [E+S+1, 2(E+S)+1].
+__device__ __forceinline__ void write_shared_groups(int32_t* __restrict__ off,
+                                                    int32_t* __restrict__ tiles, int E, int S,
+                                                    int T, int tm_up, int tm, int nt_up,
+                                                    int nt_down, int o, int tu, int td) {
+  const int mts_up = (T + tm_up - 1) / tm_up;
+  const int mts = (T + tm - 1) / tm;
+  for (int s2 = 0; s2 <= S; ++s2) {
+    off[E + s2] = o + s2 * T;
+    tiles[E + s2] = tu + s2 * mts_up * nt_up;
+    tiles[E + S + 1 + E + s2] = td + s2 * mts * nt_down;
+  }
+}
+
+// What the lists and the GEMM tile tables are made with and written to.
+struct ListArgs {
+  int S, T;  // shared experts, tokens of the batch
+  int tm_up, tm, nt_up, nt_down, tall_up, tall_down, cus;
+  int32_t *off, *tiles, *list, *pos, *row_dst;
+};
+
+// The tables from the experts' row counts, by one wave (lane e < E holds
+// expert e's count t): returns the expert's first list row, and where `write`
+// is set stores the group offsets and the tile prefixes.
+__device__ __forceinline__ int list_tables(int t, int E, const ListArgs& a, bool write) {
+  const int lane = threadIdx.x & (kWave - 1);
+  int tm_up = a.tm_up, tm = a.tm;
+  if (a.tall_up) tm_up = tall_rows(lane < E ? t : 0, E, a.S, a.T, a.nt_up, a.cus);
+  if (a.tall_down) tm = tall_rows(lane < E ? t : 0, E, a.S, a.T, a.nt_down, a.cus);
+  const int mt_up = (t + tm_up - 1) / tm_up;
+  const int mt = (t + tm - 1) / tm;
+  // inclusive scans over experts
+  const int o = wave_incl_scan_i32(t);
+  const int tu = wave_incl_scan_i32(mt_up * a.nt_up);
+  const int td = wave_incl_scan_i32(mt * a.nt_down);
+  if (write && lane < E) {
+    // exclusive prefixes per expert; the last expert also writes the
+    // prefixes of the shared experts and the totals
+    a.off[lane] = o - t;
+    a.tiles[lane] = tu - mt_up * a.nt_up;
+    a.tiles[E + a.S + 1 + lane] = td - mt * a.nt_down;
+    if (lane == E - 1) {
+      write_shared_groups(a.off, a.tiles, E, a.S, a.T, tm_up, tm, a.nt_up, a.nt_down, o, tu, td);
+      a.tiles[2 * (E + a.S + 1)] = tm_up;
+      a.tiles[2 * (E + a.S + 1) + 1] = tm;
+    }
+  }
+  return o - t;
+}
+
 // Ratio mode: once a digit leaves at most this many keys sharing the
 // threshold's prefix, one wave ranks them directly.
 constexpr int kDirect = 64;
 
-template <int R>
+// LISTS: a batch of one sample with at most two branches per thread also
+// builds the expert lists and tile tables here (lists_kernel's, the same
+// values) from what the block holds in registers and LDS: the launch of its
+// own took 3.4-4.8 us, nearly all of it ramp and round trips.
+template <int R, bool LISTS = false>
 __global__ __launch_bounds__(kSelThreads) void decide_kernel(
     const int32_t* __restrict__ e_t, const float* __restrict__ w_t,
     const int32_t* __restrict__ e_c, const float* __restrict__ w_c,
@@ -133,7 +194,10 @@ __global__ __launch_bounds__(kSelThreads) void decide_kernel(
     int32_t* __restrict__ q_out,
     float* __restrict__ margin, uint8_t* __restrict__ mask, int32_t* __restrict__ sigma,
     uint8_t* __restrict__ sync, int32_t* __restrict__ cnt_bs, int32_t* __restrict__ stats_bs,
-    int32_t* __restrict__ cnt_ch) {
+    int32_t* __restrict__ cnt_ch, ListArgs la) {
+  static_assert(!LISTS || R <= 2, "the lists need a branch's mask and expert in registers");
+  __shared__ int s_wcnt[LISTS ? R : 1][LISTS ? kSelWaves : 1][64];
+  __shared__ int s_base[64];
   extern __shared__ __attribute__((aligned(16))) unsigned char s_dyn[];
   int8_t* s_q = reinterpret_cast<int8_t*>(s_dyn);            // [N*k] matched slot or -1
   uint8_t* s_mask = reinterpret_cast<uint8_t*>(s_dyn) + N * k; // [N*k]
@@ -502,6 +566,7 @@ __global__ __launch_bounds__(kSelThreads) void decide_kernel(
   }
 
   // 3. mask and per-expert counts
+  int rec_e[LISTS ? R : 1], rk[LISTS ? R : 1];  // expert if recomputed, else -1; rank in the wave
 #pragma unroll kU
   for (int r = 0; r < R; ++r) {
     const int j = tid + kSelThreads * r;
@@ -529,14 +594,33 @@ __global__ __launch_bounds__(kSelThreads) void decide_kernel(
         atomicAdd(&s_cntr[r][e_of(r)], 1);
       }
     }
+    if constexpr (LISTS) rec_e[r] = rc ? e_of(r) : -1;
   }
   __syncthreads();
+  if constexpr (LISTS) {
+    // each wave ranks its recomputed branches per expert; the last wave (it
+    // has the fewest tokens below) makes the tables
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      rk[r] = 0;
+      for (int ee = 0; ee < E; ++ee) {
+        const uint64_t bal = __ballot(rec_e[r] == ee);
+        if (lane == ee) s_wcnt[r][wv][ee] = __popcll(bal);
+        if (rec_e[r] == ee) rk[r] = lane_rank(bal);
+      }
+    }
+    if (wv == kSelWaves - 1) {
+      const int first = list_tables(lane < E ? s_cnt[lane] : 0, E, la, true);
+      if (lane < E) s_base[lane] = first;
+    }
+  }
 
   // 4. per token: sync flag and slots
   int rec = 0, syn = 0;
   for (int i = tid; i < N; i += kSelThreads) {
     const bool any = token_slots(s_q + i * k, s_mask + i * k, k, mode == kSelFull,
-                                 sigma + base + int64_t(i) * k, rec);
+                                 sigma + base + int64_t(i) * k, rec,
+                                 LISTS ? s_q + i * k : nullptr);
     sync[int64_t(b) * N + i] = any ? 1 : 0;
     syn += any ? 1 : 0;
   }
@@ -547,6 +631,24 @@ __global__ __launch_bounds__(kSelThreads) void decide_kernel(
     atomicAdd(&s_sync, syn);
   }
   __syncthreads();
+  if constexpr (LISTS) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const int j = tid + kSelThreads * r;  // the flat id: one sample
+      if (j >= nb) continue;
+      const int e = rec_e[r];
+      if (e < 0) {
+        la.pos[j] = -1;
+        continue;
+      }
+      int idx = s_base[e] + rk[r];
+      for (int r2 = 0; r2 < r; ++r2) idx += s_cntr[r2][e];
+      for (int w2 = 0; w2 < wv; ++w2) idx += s_wcnt[r][w2][e];
+      la.list[idx] = j;
+      la.pos[j] = idx;
+      la.row_dst[idx] = j / k * k + s_q[j];
+    }
+  }
   if (tid < E) cnt_bs[b * E + tid] = s_cnt[tid];
   // per-chunk counts [B][RC][E] for the lists kernel (RC chunks of 1024 branches)
   const int rc_n = (nb + kSelThreads - 1) / kSelThreads;
@@ -557,24 +659,6 @@ __global__ __launch_bounds__(kSelThreads) void decide_kernel(
     stats_bs[b * 4 + 1] = mode == kSelFull ? 0 : n_unmatched;
     stats_bs[b * 4 + 2] = n_matched;
     stats_bs[b * 4 + 3] = s_sync;
-  }
-}
-
-// Group table entries E..E+S: the shared experts (Sec. 2.3, shared-expert
-// MoE eq.) follow the routed ones in the FFN's grouped GEMM, T rows each (every
-// token, in token order), so their offsets and tile prefixes continue the
-// routed totals (o rows, tu / td tiles).  Tile tables: up at [0, E+S],
-// down at [E+S+1, 2(E+S)+1].
-__device__ __forceinline__ void write_shared_groups(int32_t* __restrict__ off,
-                                                    int32_t* __restrict__ tiles, int E, int S,
-                                                    int T, int tm_up, int tm, int nt_up,
-                                                    int nt_down, int o, int tu, int td) {
-  const int mts_up = (T + tm_up - 1) / tm_up;
-  const int mts = (T + tm - 1) / tm;
-  for (int s2 = 0; s2 <= S; ++s2) {
-    off[E + s2] = o + s2 * T;
-    tiles[E + s2] = tu + s2 * mts_up * nt_up;
-    tiles[E + S + 1 + E + s2] = td + s2 * mts * nt_down;
   }
 }
 
@@ -591,10 +675,8 @@ __device__ __forceinline__ void write_shared_groups(int32_t* __restrict__ off,
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(kSelThreads) void lists_kernel(
     const uint8_t* __restrict__ mask, const int32_t* __restrict__ e_t,
-    const int32_t* __restrict__ cnt_ch, int B, int N, int E, int S, int k, int tm_up, int tm,
-    int nt_up, int nt_down, int tall_up, int tall_down, int cus, const int32_t* __restrict__ sigma, int32_t* __restrict__ off,
-    int32_t* __restrict__ tiles, int32_t* __restrict__ list, int32_t* __restrict__ pos,
-    int32_t* __restrict__ row_dst) {
+    const int32_t* __restrict__ cnt_ch, int B, int N, int E, int k,
+    const int32_t* __restrict__ sigma, ListArgs la) {
   __shared__ int s_part_tot[kSelThreads];
   __shared__ int s_part_bef[kSelThreads];
   __shared__ int s_base[64];
@@ -641,27 +723,8 @@ __global__ __launch_bounds__(kSelThreads) void lists_kernel(
         bf += s_part_bef[pp * E + lane];
       }
     }
-    if (tall_up) tm_up = tall_rows(lane < E ? t : 0, E, S, B * N, nt_up, cus);
-    if (tall_down) tm = tall_rows(lane < E ? t : 0, E, S, B * N, nt_down, cus);
-    const int mt_up = (t + tm_up - 1) / tm_up;
-    const int mt = (t + tm - 1) / tm;
-    // inclusive scans over experts
-    const int o = wave_incl_scan_i32(t);
-    const int tu = wave_incl_scan_i32(mt_up * nt_up);
-    const int td = wave_incl_scan_i32(mt * nt_down);
-    if (lane < E) s_base[lane] = o - t + bf;
-    if (my == 0 && lane < E) {
-      // exclusive prefixes per expert; the last expert also writes the
-      // prefixes of the shared experts and the totals
-      off[lane] = o - t;
-      tiles[lane] = tu - mt_up * nt_up;
-      tiles[E + S + 1 + lane] = td - mt * nt_down;
-      if (lane == E - 1) {
-        write_shared_groups(off, tiles, E, S, B * N, tm_up, tm, nt_up, nt_down, o, tu, td);
-        tiles[2 * (E + S + 1)] = tm_up;
-        tiles[2 * (E + S + 1) + 1] = tm;
-      }
-    }
+    const int first = list_tables(t, E, la, my == 0);
+    if (lane < E) s_base[lane] = first + bf;
   }
   int rk = 0;
   for (int ee = 0; ee < E; ++ee) {
@@ -673,15 +736,15 @@ __global__ __launch_bounds__(kSelThreads) void lists_kernel(
   __syncthreads();
   if (!in) return;
   if (!sel) {
-    pos[f] = -1;
+    la.pos[f] = -1;
     return;
   }
   int before = 0;
   for (int w2 = 0; w2 < wv; ++w2) before += s_wcnt[w2][ev];
   const int idx = s_base[ev] + before + rk;
-  list[idx] = static_cast<int32_t>(f);
-  pos[f] = idx;
-  row_dst[idx] = static_cast<int32_t>((f / k) * k + sg);
+  la.list[idx] = static_cast<int32_t>(f);
+  la.pos[f] = idx;
+  la.row_dst[idx] = static_cast<int32_t>((f / k) * k + sg);
 }
 
 // ---------------------------------------------------------------------------
@@ -1090,9 +1153,20 @@ __global__ void reset_kernel(int32_t* __restrict__ e_c, float* __restrict__ w_c,
 
 }  // namespace
 
+static ListArgs list_args(const Shape& s, const FfnPlan& plan, const Buffers& b) {
+  // units of the down projection per M tile: N tiles times K pieces
+  return ListArgs{s.S, static_cast<int>(s.tokens()), plan.tm_up, plan.tm,
+                  (s.up_rows() + plan.tn_up - 1) / plan.tn_up,
+                  (s.d + plan.tn_down - 1) / plan.tn_down * plan.split_down,
+                  plan.tall_up ? 1 : 0, plan.tall_down ? 1 : 0, device_cus(), b.off, b.tiles,
+                  b.list, b.pos, b.row_dst};
+}
+
+bool decide_lists(const Shape& s) { return s.B == 1 && s.N * s.k <= 2 * kSelThreads && s.E <= 64; }
+
 hipError_t launch_decide(const Shape& s, int sel_mode, int budget, float lambda0, float lambda1,
                          float lambda2, bool with_stat, float tau0, float alpha,
-                         const Buffers& b, hipStream_t st) {
+                         const FfnPlan& plan, const Buffers& b, hipStream_t st) {
   const int nb = s.N * s.k;
   const double log_n = std::log(static_cast<double>(s.N));  // the entropy's normaliser
   if (nb > 8 * kSelThreads && kSelThreads % s.k == 0 && s.E <= 64) {
@@ -1124,14 +1198,17 @@ hipError_t launch_decide(const Shape& s, int sel_mode, int budget, float lambda0
   }
   const size_t lds = size_t(2) * nb;
   if (lds > 64 * 1024) return hipErrorInvalidValue;
-#define MOECA_DECIDE(RR)                                                                      \
-  launch_kernel(&decide_kernel<RR>, dim3(s.B), dim3(kSelThreads), uint32_t(lds), st, b.e_t,   \
+  const ListArgs la = list_args(s, plan, b);
+#define MOECA_DECIDE(...)                                                                     \
+  launch_kernel(&decide_kernel<__VA_ARGS__>, dim3(s.B), dim3(kSelThreads), uint32_t(lds), st, b.e_t,   \
                 b.w_t, b.e_c, b.w_c, b.n_c, b.ent, with_stat ? 1 : 0, log_n, tau0,            \
                 alpha,                                                                        \
                 b.hbar, b.tau, s.N, s.E, s.k, sel_mode, budget, lambda0, lambda1, lambda2,    \
                 b.q,                                                                          \
-                b.margin, b.mask, b.sigma, b.sync, b.cnt_bs, b.stats_bs, b.cnt_ch)
-  if (nb <= 2 * kSelThreads) {
+                b.margin, b.mask, b.sigma, b.sync, b.cnt_bs, b.stats_bs, b.cnt_ch, la)
+  if (decide_lists(s)) {
+    MOECA_DECIDE(2, true);
+  } else if (nb <= 2 * kSelThreads) {
     MOECA_DECIDE(2);
   } else if (nb <= 8 * kSelThreads) {
     MOECA_DECIDE(8);
@@ -1145,16 +1222,10 @@ hipError_t launch_decide(const Shape& s, int sel_mode, int budget, float lambda0
 }
 
 hipError_t launch_lists(const Shape& s, const FfnPlan& plan, const Buffers& b, hipStream_t st) {
-  const int nb = s.N * s.k;
-  const int nt_up = (s.up_rows() + plan.tn_up - 1) / plan.tn_up;
-  // units of the down projection per M tile: N tiles times K pieces
-  const int nt_down = (s.d + plan.tn_down - 1) / plan.tn_down * plan.split_down;
-  const int rc_n = (nb + kSelThreads - 1) / kSelThreads;
+  const int rc_n = (s.N * s.k + kSelThreads - 1) / kSelThreads;
   if (s.E > 64) return hipErrorInvalidValue;
   launch_kernel(&lists_kernel, dim3(s.B * rc_n), dim3(kSelThreads), 0, st, b.mask, b.e_t,
-                b.cnt_ch, s.B, s.N, s.E, s.S, s.k, plan.tm_up, plan.tm, nt_up, nt_down,
-                plan.tall_up ? 1 : 0, plan.tall_down ? 1 : 0, device_cus(), b.sigma, b.off,
-                b.tiles, b.list, b.pos, b.row_dst);
+                b.cnt_ch, s.B, s.N, s.E, s.k, b.sigma, list_args(s, plan, b));
   return hipGetLastError();
 }
 

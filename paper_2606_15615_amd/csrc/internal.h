@@ -166,7 +166,10 @@ hipError_t launch_router(const Shape& s, const void* x, const void* W_r, const f
 // kernel then derives the entropy and thresholds first (hbar, tau).
 hipError_t launch_decide(const Shape& s, int sel_mode, int budget, float lambda0, float lambda1,
                          float lambda2, bool with_stat, float tau0, float alpha,
-                         const Buffers& b, hipStream_t st);
+                         const FfnPlan& plan, const Buffers& b, hipStream_t st);
+// Whether the decide kernel also builds the lists (one sample, up to 2048
+// branches); otherwise launch_lists follows it.
+bool decide_lists(const Shape& s);
 hipError_t launch_lists(const Shape& s, const FfnPlan& plan, const Buffers& b, hipStream_t st);
 // act: MOECA_ACT_* of the policy.  W_*_sh: the shared experts (S > 0).
 // chained: a block of a stack (see kActGeluErff).

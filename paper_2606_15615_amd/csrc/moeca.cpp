@@ -343,8 +343,8 @@ int moeca_forward_noalloc(const moeca_layer* L, const void* x, int samples, void
   if ((e = moeca::launch_router(s, x, L->W_r, L->b_r, p.norm_topk, p.beta, false, b, st)) ==
           hipSuccess &&
       (e = moeca::launch_decide(s, moeca::kSelFull, 0, p.lambda0, p.lambda1, p.lambda2, false,
-                                p.tau0, p.alpha, b, st)) == hipSuccess &&
-      (e = moeca::launch_lists(s, plan, b, st)) == hipSuccess &&
+                                p.tau0, p.alpha, plan, b, st)) == hipSuccess &&
+      (moeca::decide_lists(s) || (e = moeca::launch_lists(s, plan, b, st)) == hipSuccess) &&
       (e = moeca::launch_ffn_up(s, x, L->W_up, L->W_up_sh, p.act, false, plan, b, st)) ==
           hipSuccess &&
       (e = moeca::launch_ffn_down(s, L->W_down, L->W_down_sh, plan, b, st)) ==
@@ -446,11 +446,6 @@ int layer_step(moeca_layer* L, const void* x_t, const void* x_ffn, int t, void* 
     sel = p.mode == MOECA_MODE_THRESHOLD ? moeca::kSelThreshold : moeca::kSelRatio;
     budget = static_cast<int>(std::floor(static_cast<double>(p.ratio) * s.N * s.k + 0.5));
   }
-  arm();
-  if (!check(moeca::launch_decide(s, sel, budget, p.lambda0, p.lambda1, p.lambda2, !uncached, p.tau0,
-                                  p.alpha, b, st),
-             "decide"))
-    return MOECA_E_HIP;
   // rows the routed experts are expected to have: every branch on full
   // steps, the budget in ratio mode; a threshold step's count is not known to
   // the host (the default settings recompute five eighths of the branches)
@@ -463,7 +458,13 @@ int layer_step(moeca_layer* L, const void* x_t, const void* x_ffn, int t, void* 
   const bool pieces = b.part != nullptr && !(full && s.bf16 && L->mid_outside);
   const moeca::FfnPlan plan = moeca::ffn_plan(s, rows, pieces);
   arm();
-  if (!check(moeca::launch_lists(s, plan, b, st), "lists")) return MOECA_E_HIP;
+  if (!check(moeca::launch_decide(s, sel, budget, p.lambda0, p.lambda1, p.lambda2, !uncached, p.tau0,
+                                  p.alpha, plan, b, st),
+             "decide"))
+    return MOECA_E_HIP;
+  arm();
+  if (!check(moeca::decide_lists(s) ? hipSuccess : moeca::launch_lists(s, plan, b, st), "lists"))
+    return MOECA_E_HIP;
   if (between) {
     const int rc = between();
     if (rc != MOECA_OK) return rc;

@@ -379,6 +379,21 @@ def test_threshold_mode_plans(shape, plan):
     assert [i["ffn_plan"] for i in infos] == [full_step_plan(S.shape), plan, plan]
 
 
+@pytest.mark.parametrize("shape", [
+    LayerShape(d=128, E=16, k=2, d_ff=128, B=1, N=512, dtype="bf16"),   # 1024 branches
+    LayerShape(d=128, E=64, k=3, d_ff=128, B=1, N=342, dtype="bf16"),   # 1026
+    LayerShape(d=128, E=8, k=2, d_ff=128, B=1, N=1024, dtype="fp32"),   # 2048
+    LayerShape(d=128, E=8, k=3, d_ff=128, B=1, N=683, dtype="bf16"),    # 2049: separate launch
+    LayerShape(d=128, E=4, k=1, d_ff=64, B=1, N=1, dtype="bf16"),
+    LayerShape(d=128, E=8, k=2, d_ff=64, B=1, N=77, dtype="bf16", ffn="swiglu", n_shared=2),
+])
+def test_one_sample_lists(shape):
+    """One sample of up to 2048 branches: the decide kernel builds the expert
+    lists itself (every list entry is compared)."""
+    S = Setup(shape, mode="ratio", seed=33, T=3, ratio=0.4, refresh_cycle=0)
+    run_forced(S, 3, label=f"one sample {shape}")
+
+
 # ---------------------------------------------------------------------------
 # The expert-wide up projection at sizes the oracle evaluates whole: up to
 # 384 rows of an expert in one tile by 144 columns; experts past 384 rows
