@@ -200,19 +200,16 @@ __global__ __launch_bounds__(kGemvWaves * kWave) void gemv_kernel(
 // ---------------------------------------------------------------------------
 // LayerNorm + AdaLN modulation and the gated residuals
 // ---------------------------------------------------------------------------
-// d <= kMaxWidth: a lane holds float4 chunks lane + 64 j (j < NC) of the
-// row; NC = ceil(d / 256) is a template parameter, so the registers held
-// per lane (and the waves a CU keeps in flight) follow the width.
-//
-// Many rows take one wave each (WPR = 1).  At most kLnFewRows take a block of
-// four waves each (WPR = 4, NC = ceil(d / 1024)): with a row or two per CU the
-// kernel lasts as long as one row's chain of fp64 sums, conversions and waits
-// on memory, which four waves shorten, and the AdaLN vectors are requested
-// with the row (WPR = 1 has no registers for them).  Four blocks of width 1152, 250 tokens,
-// a cycle of four steps: 2966 us with a wave per row, 2841 so.
+// A block of four waves takes a row: thread l holds the float4 chunks l +
+// 256 j (j < NC), NC = ceil(d / 1024).  With few rows a launch lasts as long as
+// one row's chain of fp64 sums, conversions and waits on memory, which four
+// waves shorten, and at NC <= 2 the AdaLN vectors fit the registers and are
+// requested together with the row; with many rows it is bound by HBM.  Against
+// a wave per row (a cycle of four steps, width 1152): four blocks of 250
+// tokens 2966 -> 2841 us; two blocks of 2048, 4096 and 8192 tokens 2162 ->
+// 2149, 3041 -> 3000 and 4253 -> 4246 us.
 constexpr int kLnWaves = 4;
-constexpr int kLnChunks = kMaxWidth / 4 / kWave;  // 8, the most
-constexpr int kLnFewRows = 1024;
+constexpr int kLnThreads = kLnWaves * kWave;
 
 enum { kLnAttn = 0, kLnMlp = 1, kLnFinal = 2 };
 
@@ -235,51 +232,47 @@ struct LnArgs {
 };
 
 // Sum over the threads of a row; red: a buffer of its own for each sum.
-template <int WPR>
 __device__ __forceinline__ double row_sum(double x, double* red) {
   x = wave_sum_f64(x);
-  if constexpr (WPR > 1) {
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = x;
-    __syncthreads();
-    x = (red[0] + red[1]) + (red[2] + red[3]);
-  }
-  return x;
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = x;
+  __syncthreads();
+  return (red[0] + red[1]) + (red[2] + red[3]);
 }
 
-template <int WPR, int NC>
+template <int NC>
 __device__ __forceinline__ void ln_stats(const float (&v)[NC][4], int n4, int lane, int d,
                                          double* red, double& mean, double& rstd) {
   double s = 0.0;
 #pragma unroll
   for (int j = 0; j < NC; ++j)
-    if (lane + kWave * WPR * j < n4)
+    if (lane + kLnThreads * j < n4)
 #pragma unroll
       for (int e = 0; e < 4; ++e) s += v[j][e];
-  const double mu = row_sum<WPR>(s, red) / d;
+  const double mu = row_sum(s, red) / d;
   double q = 0.0;
 #pragma unroll
   for (int j = 0; j < NC; ++j)
-    if (lane + kWave * WPR * j < n4)
+    if (lane + kLnThreads * j < n4)
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const double t = v[j][e] - mu;
         q += t * t;
       }
-  const double var = row_sum<WPR>(q, red + 4) / d;
+  const double var = row_sum(q, red + kLnWaves) / d;
   mean = mu;
   rstd = 1.0 / sqrt(var + 1e-6);
 }
 
 // bf16(LN(v) * (1 + scale) + shift) into row `dst` in fp32: the attention
 // input (off the decision path)
-template <int WPR, int NC>
+template <int NC>
 __device__ __forceinline__ void ln_store_f32(const float (&v)[NC][4], int n4, int lane,
                                              double mean, double rstd, const float4 (&shift)[NC],
                                              const float4 (&scale)[NC], uint16_t* dst) {
   const float mf = static_cast<float>(mean), rf = static_cast<float>(rstd);
 #pragma unroll
   for (int j = 0; j < NC; ++j) {
-    const int c = lane + kWave * WPR * j;
+    const int c = lane + kLnThreads * j;
     if (c < n4) {
       const float4 sh = shift[j];
       const float4 sc = scale[j];
@@ -294,13 +287,13 @@ __device__ __forceinline__ void ln_store_f32(const float (&v)[NC][4], int n4, in
 
 // bf16(LN(v) * (1 + scale) + shift) into row `dst`, in fp64 and rounded
 // once: this is the MoE routing input (decision-path arithmetic)
-template <int WPR, int NC>
+template <int NC>
 __device__ __forceinline__ void ln_store(const float (&v)[NC][4], int n4, int lane,
                                          double mean, double rstd, const float4 (&shift)[NC],
                                          const float4 (&scale)[NC], uint16_t* dst) {
 #pragma unroll
   for (int j = 0; j < NC; ++j) {
-    const int c = lane + kWave * WPR * j;
+    const int c = lane + kLnThreads * j;
     if (c < n4) {
       const float4 sh = shift[j];
       const float4 sc = scale[j];
@@ -317,12 +310,11 @@ __device__ __forceinline__ void ln_store(const float (&v)[NC][4], int n4, int la
   }
 }
 
-template <int MODE, int NC, int WPR>
-__global__ __launch_bounds__(kLnWaves * kWave) void ln_kernel(LnArgs p) {
-  static_assert(WPR == 1 || WPR == kLnWaves, "a wave or a block per row");
-  __shared__ double red[WPR > 1 ? 16 : 1];  // four sums of four waves
-  const int lane = WPR > 1 ? threadIdx.x : threadIdx.x & 63;  // thread of the row
-  const int r = WPR > 1 ? blockIdx.x : blockIdx.x * kLnWaves + (threadIdx.x >> 6);
+template <int MODE, int NC>
+__global__ __launch_bounds__(kLnThreads) void ln_kernel(LnArgs p) {
+  __shared__ double red[4 * kLnWaves];  // four sums
+  const int lane = threadIdx.x;          // thread of the row
+  const int r = blockIdx.x;
   int row;
   if constexpr (MODE == kLnMlp) {
     if (r >= *p.count) return;
@@ -336,17 +328,16 @@ __global__ __launch_bounds__(kLnWaves * kWave) void ln_kernel(LnArgs p) {
   const int64_t o = int64_t(row) * d;
   const float* m = p.mod + int64_t(b) * 6 * d;  // sh_a, sc_a, g_a, sh_m, sc_m, g_m
   float v[NC][4];
-  // one of the sample's AdaLN vectors; requested here where a block has a row
+  // the sample's AdaLN vectors, requested with the row
   auto fetch = [&](float4 (&x)[NC], const float* q) __attribute__((always_inline)) {
 #pragma unroll
     for (int j = 0; j < NC; ++j) {
-      const int c = lane + kWave * WPR * j;
+      const int c = lane + kLnThreads * j;
       if (c < n4) x[j] = reinterpret_cast<const float4*>(q)[c];
     }
   };
   float4 sh_a[NC], sc_a[NC], g_a[NC], sh_m[NC], sc_m[NC];
-  constexpr bool kEarly = WPR > 1 && MODE != kLnFinal;
-  if constexpr (kEarly) {
+  if constexpr (MODE != kLnFinal) {
     if (MODE == kLnAttn) {
       fetch(sh_a, m);
       fetch(sc_a, m + d);
@@ -362,7 +353,7 @@ __global__ __launch_bounds__(kLnWaves * kWave) void ln_kernel(LnArgs p) {
     const float* g = m + 5 * d;
 #pragma unroll
     for (int j = 0; j < NC; ++j) {
-      const int c = lane + kWave * WPR * j;
+      const int c = lane + kLnThreads * j;
       if (c < n4) {
         const float4 x1 = reinterpret_cast<const float4*>(p.x1 + o)[c];
         const u32x2_t yy = reinterpret_cast<const u32x2_t*>(p.y + o)[c];
@@ -385,7 +376,7 @@ __global__ __launch_bounds__(kLnWaves * kWave) void ln_kernel(LnArgs p) {
     const float* gp = p.mod_prev + int64_t(b) * 6 * d + 5 * d;
 #pragma unroll
     for (int j = 0; j < NC; ++j) {
-      const int c = lane + kWave * WPR * j;
+      const int c = lane + kLnThreads * j;
       if (c < n4) {
         const float4 x1 = reinterpret_cast<const float4*>(p.x1p + o)[c];
         const u32x2_t yy = reinterpret_cast<const u32x2_t*>(p.y + o)[c];
@@ -401,7 +392,7 @@ __global__ __launch_bounds__(kLnWaves * kWave) void ln_kernel(LnArgs p) {
   } else {
 #pragma unroll
     for (int j = 0; j < NC; ++j) {
-      const int c = lane + kWave * WPR * j;
+      const int c = lane + kLnThreads * j;
       if (c < n4) {
         const float4 xx = reinterpret_cast<const float4*>(p.x + o)[c];
         v[j][0] = xx.x;
@@ -418,25 +409,20 @@ __global__ __launch_bounds__(kLnWaves * kWave) void ln_kernel(LnArgs p) {
   if (with_a) {
 #pragma unroll
     for (int j = 0; j < NC; ++j) {
-      const int c = lane + kWave * WPR * j;
+      const int c = lane + kLnThreads * j;
       if (c < n4) av[j] = reinterpret_cast<const u32x2_t*>(p.a + o)[c];
     }
   }
   double mean, rstd;
   if (MODE == kLnAttn) {
-    ln_stats<WPR>(v, n4, lane, d, red, mean, rstd);
-    if constexpr (!kEarly) {
-      fetch(sh_a, m);
-      fetch(sc_a, m + d);
-    }
-    ln_store_f32<WPR>(v, n4, lane, mean, rstd, sh_a, sc_a, p.h + o);
+    ln_stats(v, n4, lane, d, red, mean, rstd);
+    ln_store_f32(v, n4, lane, mean, rstd, sh_a, sc_a, p.h + o);
     if (!p.cached) return;
   }
   // x1 = x + g_a * a, then the MoE input from LN(x1)
-  if constexpr (!kEarly) fetch(g_a, m + 2 * d);
 #pragma unroll
   for (int j = 0; j < NC; ++j) {
-    const int c = lane + kWave * WPR * j;
+    const int c = lane + kLnThreads * j;
     if (c < n4) {
       const u32x2_t aa = av[j];
       const float4 gg = g_a[j];
@@ -447,18 +433,14 @@ __global__ __launch_bounds__(kLnWaves * kWave) void ln_kernel(LnArgs p) {
       reinterpret_cast<float4*>(p.x1 + o)[c] = float4{v[j][0], v[j][1], v[j][2], v[j][3]};
     }
   }
-  ln_stats<WPR>(v, n4, lane, d, red + (WPR > 1 ? 8 : 0), mean, rstd);
-  if constexpr (!kEarly) {
-    fetch(sh_m, m + 3 * d);
-    fetch(sc_m, m + 4 * d);
-  }
+  ln_stats(v, n4, lane, d, red + 2 * kLnWaves, mean, rstd);
   // a routing input (LN1 of a cache step, LN2 of a full step) takes the
   // decision-path arithmetic, so that the same input routes the same way on
   // either kind of step; the rebuilt FFN input of a cache step takes fp32
   if (MODE == kLnAttn || p.routing)
-    ln_store<WPR>(v, n4, lane, mean, rstd, sh_m, sc_m, p.u + o);
+    ln_store(v, n4, lane, mean, rstd, sh_m, sc_m, p.u + o);
   else
-    ln_store_f32<WPR>(v, n4, lane, mean, rstd, sh_m, sc_m, p.u + o);
+    ln_store_f32(v, n4, lane, mean, rstd, sh_m, sc_m, p.u + o);
 }
 
 // ---------------------------------------------------------------------------
@@ -865,30 +847,14 @@ hipError_t launch_gemv(const double* in, int B, int K, const GemvBatch& mats, in
   return hipGetLastError();
 }
 
-// one wave per row; the instantiation holding ceil(d / 256) float4 chunks
-// per lane.  Few rows: one block per row.
 template <int MODE>
 hipError_t launch_ln(const LnArgs& p, int T, int d, hipStream_t st) {
-  const dim3 grid((T + kLnWaves - 1) / kLnWaves), block(kLnWaves * kWave);
-  static_assert(kMaxWidth <= 2 * 4 * kLnWaves * kWave, "two chunks per thread of a block");
-  if (T <= kLnFewRows) {
-    if (d <= 4 * kLnWaves * kWave)
-      launch_kernel(&ln_kernel<MODE, 1, kLnWaves>, dim3(T), block, 0, st, p);
-    else
-      launch_kernel(&ln_kernel<MODE, 2, kLnWaves>, dim3(T), block, 0, st, p);
-    return hipGetLastError();
-  }
-  switch ((d / 4 + kWave - 1) / kWave) {
-    case 1: launch_kernel(&ln_kernel<MODE, 1, 1>, grid, block, 0, st, p); break;
-    case 2: launch_kernel(&ln_kernel<MODE, 2, 1>, grid, block, 0, st, p); break;
-    case 3: launch_kernel(&ln_kernel<MODE, 3, 1>, grid, block, 0, st, p); break;
-    case 4: launch_kernel(&ln_kernel<MODE, 4, 1>, grid, block, 0, st, p); break;
-    case 5: launch_kernel(&ln_kernel<MODE, 5, 1>, grid, block, 0, st, p); break;
-    case 6: launch_kernel(&ln_kernel<MODE, 6, 1>, grid, block, 0, st, p); break;
-    case 7: launch_kernel(&ln_kernel<MODE, 7, 1>, grid, block, 0, st, p); break;
-    case 8: launch_kernel(&ln_kernel<MODE, 8, 1>, grid, block, 0, st, p); break;
-    default: return hipErrorInvalidValue;
-  }
+  static_assert(kMaxWidth <= 2 * 4 * kLnThreads, "two chunks per thread at most");
+  if (d > kMaxWidth) return hipErrorInvalidValue;
+  if (d <= 4 * kLnThreads)
+    launch_kernel(&ln_kernel<MODE, 1>, dim3(T), dim3(kLnThreads), 0, st, p);
+  else
+    launch_kernel(&ln_kernel<MODE, 2>, dim3(T), dim3(kLnThreads), 0, st, p);
   return hipGetLastError();
 }
 
