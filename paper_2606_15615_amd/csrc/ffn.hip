@@ -2039,8 +2039,19 @@ FfnPlan ffn_plan(const Shape& s, int64_t rows, bool partials) {
   p.thin_down = few && partials;
   p.tn_up = tn(s.up_rows());
   p.tn_down = tn(s.d);
-  p.tall_up = tall_capable(s.tokens(), s.d, s.up_rows()) && mean_rows >= kTallRows;
-  p.tall_down = tall_capable(s.mid_rows(), s.d_ff, s.d) && mean_rows >= kTallRows;
+  // 256 x 256 tiles only where tiles of 192 rows come to five eighths of the
+  // CUs (12 experts of 640 x 2560, 300 and 600 rows each: a cycle of three
+  // steps 326 us with them, 311 with 128 x 256) and K is deep (960 x 3840:
+  // 480 us with the up projection in them, 465 without)
+  constexpr int kTallDeepK = 1152;
+  auto fills = [&](int n) {
+    return (mean_rows + 191) / 192 * s.groups() * ((n + kTallTN - 1) / kTallTN) >=
+           device_cus() * 5 / 8;
+  };
+  p.tall_up = tall_capable(s.tokens(), s.d, s.up_rows()) && mean_rows >= kTallRows &&
+              fills(s.up_rows()) && s.d >= kTallDeepK;
+  p.tall_down = tall_capable(s.mid_rows(), s.d_ff, s.d) && mean_rows >= kTallRows &&
+                fills(s.d) && s.d_ff >= kTallDeepK;
   if (p.thin_up) {
     p.tall_up = false;
     p.tn_up = kThinTN;
