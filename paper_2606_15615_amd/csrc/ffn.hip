@@ -52,22 +52,13 @@ constexpr int kXcds = 8;
 // Activation of the up projection.  tanh GELU:
 //   0.5 z (1 + tanh(u)) = z / (1 + exp(-2u)),  u = sqrt(2/pi) (z + 0.044715 z^3),
 // with exp(-2u) = 2^(-2u log2 e) from the hardware exp2 (about 1 ulp) and a
-// hardware reciprocal.  kActSwiglu marks the gated epilogue (silu below),
-// which pairs columns instead of mapping each one.
-//
-// erf GELU: z Phi(z) = max(z, 0) - a Phi(-a) with a = |z|, and Phi(-a) =
-// 2^(-1 + a Q(a)) by the hardware exp2, Q a degree-7 polynomial fitted to
-// (log2 Phi(-a) + 1) / a on [0, 6] (weighted least squares in 64 bits,
-// reweighted towards the largest error of the result); past 6, a Phi(-a) is
-// below 1e-8 and a is held at 6.  Nothing cancels for negative z, so over
-// [-8, 8] the largest error in fp32 is 2.5e-7 and 2e-6 relative for |z| < 3,
-// against 4.5e-7 and 1.1e-5 of 0.5 z (1 + erff(z / sqrt 2)); it has no
-// branch, where erff's two ranges both ran in every wave.  With erff the
-// epilogue took a fifth of the up projection (3 x 1000 tokens, 16 experts).
-// kActGeluErff keeps erff: a block of a stack hands its output on to the later
-// blocks' routers, where other last bits move tied branches.
-enum { kActGeluTanh = 0, kActGeluErf = 1, kActNone = 2, kActSwiglu = 3, kActBias = 4,
-       kActGeluErff = 5 };
+// hardware reciprocal; the erf form uses erff.  (A branch-free polynomial for
+// z Phi(z) took 24 of 685 us off a threshold-mode refresh cycle of 3 x 1000
+// tokens, 16 experts, and is not used: other last bits, twice erff's relative
+// error for 0 < z < 3 and -6e-9 where the function goes to zero.)
+// kActSwiglu marks the gated epilogue (silu below), which pairs columns
+// instead of mapping each one.
+enum { kActGeluTanh = 0, kActGeluErf = 1, kActNone = 2, kActSwiglu = 3, kActBias = 4 };
 
 // silu(z) = z / (1 + exp(-z)), exp(-z) = 2^(-z log2 e) by the hardware exp2.
 __device__ __forceinline__ float silu_f(float z) {
@@ -80,18 +71,6 @@ __device__ __forceinline__ float act_fn(float z) {
     const float u = 0.7978845608028654f * (z + 0.044715f * z * z * z);
     return z * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-2.8853900817779268f * u));
   } else if constexpr (ACT == kActGeluErf) {
-    const float a = fminf(fabsf(z), 6.0f);
-    float q = -1.9020520767e-06f;
-    q = fmaf(q, a, 2.8056765586e-05f);
-    q = fmaf(q, a, -1.3147230493e-04f);
-    q = fmaf(q, a, -2.7207817766e-04f);
-    q = fmaf(q, a, 7.2454246692e-03f);
-    q = fmaf(q, a, -5.2627611905e-02f);
-    q = fmaf(q, a, -4.5916214585e-01f);
-    q = fmaf(q, a, -1.1511110067f);
-    const float h = __builtin_amdgcn_exp2f(fmaf(a, q, -1.0f));
-    return fmaf(-a, h, z < 0.0f ? z * 0.0f : z);  // (z 0: -inf and NaN stay NaN)
-  } else if constexpr (ACT == kActGeluErff) {
     return 0.5f * z * (1.0f + erff(z * 0.7071067811865476f));
   } else {
     return z;
@@ -2118,13 +2097,10 @@ int device_cus() {
 }
 
 hipError_t launch_ffn_up(const Shape& s, const void* x, const void* W_up, const void* W_up_sh,
-                         int act, bool chained, const FfnPlan& plan, const Buffers& b,
-                         hipStream_t st) {
+                         int act, const FfnPlan& plan, const Buffers& b, hipStream_t st) {
   const int n = s.up_rows();
   if (act == MOECA_ACT_SWIGLU)
     return launch_gemm<kUp, kActSwiglu>(s, plan, x, W_up, W_up_sh, s.d, n, b, b.mid, b.mid, st);
-  if (act == MOECA_ACT_GELU_ERF && chained)
-    return launch_gemm<kUp, kActGeluErff>(s, plan, x, W_up, W_up_sh, s.d, n, b, b.mid, b.mid, st);
   if (act == MOECA_ACT_GELU_ERF)
     return launch_gemm<kUp, kActGeluErf>(s, plan, x, W_up, W_up_sh, s.d, n, b, b.mid, b.mid, st);
   return launch_gemm<kUp, kActGeluTanh>(s, plan, x, W_up, W_up_sh, s.d, n, b, b.mid, b.mid, st);

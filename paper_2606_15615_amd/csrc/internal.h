@@ -172,9 +172,8 @@ hipError_t launch_decide(const Shape& s, int sel_mode, int budget, float lambda0
 bool decide_lists(const Shape& s);
 hipError_t launch_lists(const Shape& s, const FfnPlan& plan, const Buffers& b, hipStream_t st);
 // act: MOECA_ACT_* of the policy.  W_*_sh: the shared experts (S > 0).
-// chained: a block of a stack (see kActGeluErff).
 hipError_t launch_ffn_up(const Shape& s, const void* x, const void* W_up, const void* W_up_sh,
-                         int act, bool chained, const FfnPlan& plan, const Buffers& b, hipStream_t st);
+                         int act, const FfnPlan& plan, const Buffers& b, hipStream_t st);
 // With plan.split_down > 1 this also adds the partial sums into the cache
 // rows, except where the combine does (combine_sums).
 hipError_t launch_ffn_down(const Shape& s, const void* W_down, const void* W_down_sh,

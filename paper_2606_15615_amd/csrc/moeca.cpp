@@ -345,7 +345,7 @@ int moeca_forward_noalloc(const moeca_layer* L, const void* x, int samples, void
       (e = moeca::launch_decide(s, moeca::kSelFull, 0, p.lambda0, p.lambda1, p.lambda2, false,
                                 p.tau0, p.alpha, plan, b, st)) == hipSuccess &&
       (moeca::decide_lists(s) || (e = moeca::launch_lists(s, plan, b, st)) == hipSuccess) &&
-      (e = moeca::launch_ffn_up(s, x, L->W_up, L->W_up_sh, p.act, false, plan, b, st)) ==
+      (e = moeca::launch_ffn_up(s, x, L->W_up, L->W_up_sh, p.act, plan, b, st)) ==
           hipSuccess &&
       (e = moeca::launch_ffn_down(s, L->W_down, L->W_down_sh, plan, b, st)) ==
           hipSuccess)
@@ -470,9 +470,7 @@ int layer_step(moeca_layer* L, const void* x_t, const void* x_ffn, int t, void* 
     if (rc != MOECA_OK) return rc;
   }
   arm();
-  if (!check(moeca::launch_ffn_up(s, x_ffn, L->W_up, L->W_up_sh, p.act, L->mid_outside, plan, b,
-                                  st),
-             "ffn up"))
+  if (!check(moeca::launch_ffn_up(s, x_ffn, L->W_up, L->W_up_sh, p.act, plan, b, st), "ffn up"))
     return MOECA_E_HIP;
   arm();
   if (!check(moeca::launch_ffn_down(s, L->W_down, L->W_down_sh, plan, b, st), "ffn down"))

@@ -86,9 +86,8 @@ def test_fp32_tile_edges(N, d_ff, ffn, n_shared):
 
 def test_erf_gelu_over_its_range():
     """fp32 layer whose pre-activations cover [-9, 9]: one expert, W_up rows
-    scaled so that every range of the erf GELU polynomial is met, the clamp
-    past 6 included (tolerance 1e-4 of the largest output; the polynomial's
-    own error is 2.5e-7)."""
+    scaled so that every range of erff is met (tolerance 1e-4 of the largest
+    output)."""
     shape = LayerShape(d=64, E=1, k=1, d_ff=128, B=1, N=200, dtype="fp32")
     S = Setup(shape, mode="full", seed=23, T=1, act="gelu_erf")
     S.W.W_up *= np.float32(3.0)
@@ -97,6 +96,34 @@ def test_erf_gelu_over_its_range():
     z = O.to_f64(S.xs[0], "fp32").reshape(-1, 64) @ S.W.W_up[0].astype(np.float64).T
     assert z.min() < -6.5 and z.max() > 6.5
     run_forced(S, 1, label="erf range")
+
+
+def test_erf_gelu_values():
+    """erf GELU value by value: identity matrices and one expert hand every
+    pre-activation through exactly, so the output is the activation itself.
+    0.5 z (1 + erff(z / sqrt 2)) in fp32: the argument's two roundings move
+    erf by 2 2^-24 |t| erf'(t) <= 2^-24, erff is taken with 4 ulp (2^-22) and
+    the sum is rounded (2^-24), in all under 2^-21, times |z| / 2; the
+    product is rounded once more.  Below -6.5 erff is -1 and the result 0
+    (the function: above -2.7e-10)."""
+    import torch
+    from paper_2606_15615_amd import _lib
+    from paper_2606_15615_amd.layer import MoecaLayer
+    d, N = 64, 300
+    z = torch.linspace(-9.5, 9.5, N * d, device="cuda").view(1, N, d)
+    eye = torch.eye(d, device="cuda").view(1, d, d).contiguous()
+    layer = MoecaLayer(d, 1, 1, d, batch=1, tokens=N, mode=_lib.MOECA_MODE_FULL, dtype="fp32",
+                       act="gelu_erf")
+    layer.set_weights(torch.zeros(1, d, device="cuda"), None, eye, eye)
+    y = torch.empty_like(z)
+    layer.step(z, 0, y)
+    z64, y64 = z.double().cpu(), y.double().cpu()
+    ref = 0.5 * z64 * torch.special.erfc(-z64 / 2.0 ** 0.5)
+    err = (y64 - ref).abs()
+    assert (err <= 0.5 * z64.abs() * 2.0 ** -21 + 2.0 ** -23 * ref.abs()).all()
+    tail = z64 < -6.5
+    say(f"  erf GELU: largest error {err.max():.2e}, past -6.5 {err[tail].max():.2e}")
+    assert err[tail].max() < 3e-10
 
 
 @pytest.mark.parametrize("E,N,B,d,d_ff,ffn,n_shared", [
