@@ -545,7 +545,7 @@ def main():
                 flushed.append(e0.elapsed_time(e1))
             rec.append(st.n_recompute)
             syn.append(st.n_sync)
-            plan.append(st.ffn_plan)
+            plan.append((st.ffn_plan, st.ffn_plan_down))
         ms_flushed = float(np.mean(flushed)) if flushed else None
         return ms_eager, ms_graph, graphed, stage, (rec, syn, ms_flushed, plan)
 
@@ -637,21 +637,22 @@ def main():
                                  dom)
         if args.workload != "xl1024":
             traffic = None
-        swiglu = act == "swiglu"
-        thin = np.mean(np.array(plan) == 1) > 0.5
-        wide = np.mean(np.array(plan) == 2) > 0.5
+        # the tilings that most of the counted steps took (MOECA_TILES_*)
+        up_plan, down_plan = (int(np.bincount(v).argmax()) for v in zip(*plan))
+        act_id = 3 if act == "swiglu" else 0
         kernel_names = {
-            "ffn_up": ("gemm_bf16_big_kernel<0,3> (expert FFN up-projection + SwiGLU)" if swiglu
-                       else "gemm_bf16_thin_kernel<0,0,1> (expert FFN up-projection + GELU, "
-                            "weight-streaming tiles)" if thin
-                       else "gemm_bf16_wide_kernel<0> (expert FFN up-projection + GELU, "
-                            "expert-wide tiles)" if wide
-                       else "gemm_bf16_big_kernel<0,0> (expert FFN up-projection + GELU)"),
-            "ffn_down": ("gemm_bf16_thin_kernel<1,2,4> + reduce_partials_kernel<4> (expert FFN "
-                         "down-projection, weight-streaming tiles in four K pieces)" if thin
-                         else "gemm_bf16_big_kernel<1,2> (expert FFN down-projection, "
-                              "scattered into the cache slots)"),
+            "ffn_up": (f"gemm_bf16_big_kernel<0,{act_id}>", "gemm_bf16_thin_kernel<0,0,1>",
+                       "gemm_bf16_wide_kernel<0>", f"gemm_bf16_tall_kernel<0,{act_id}>")[up_plan]
+                      + " (expert FFN up-projection + "
+                      + ("SwiGLU)" if act == "swiglu" else "GELU)"),
+            "ffn_down": ("gemm_bf16_big_kernel<1,2>", "gemm_bf16_thin_kernel<1,2,4>", None,
+                         "gemm_bf16_tall_kernel<1,2>")[down_plan]
+                        + (" (expert FFN down-projection, K in four pieces)" if down_plan == 1
+                           else " (expert FFN down-projection, scattered into the cache slots)"),
         }
+        if shape.dtype == "fp32":
+            kernel_names = {"ffn_up": "gemm_f32_kernel<0,0> (expert FFN up-projection + GELU)",
+                            "ffn_down": "gemm_f32_kernel<1,2> (expert FFN down-projection)"}
         roof = {
             "bound": "hbm" if hbm_bound else "mfma",
             "kernel": kernel_names[dom],
@@ -680,10 +681,13 @@ def main():
             "recomputed_branches": round(mean_rec, 1),
             "shared_expert_rows": shared_rows,
             "synchronized_tokens": round(float(np.mean(syn)), 1),
-            # tiling of the expert FFN on the counted steps: 0 the 128 x 256
-            # tiles, 1 the weight-streaming tiles, 2 the expert-wide
-            # up-projection tiles
-            "ffn_plan_steps": {str(v): int(c) for v, c in zip(*np.unique(plan, return_counts=True))},
+            # tiling of the up projection on the counted steps: 0 the 128 x 256
+            # tiles, 1 the weight-streaming tiles, 2 the expert-wide tiles, 3
+            # the 256 x 256 tiles; the same of the down projection
+            "ffn_plan_steps": {str(v): [p[0] for p in plan].count(v)
+                               for v in sorted({p[0] for p in plan})},
+            "ffn_plan_down_steps": {str(v): [p[1] for p in plan].count(v)
+                                    for v in sorted({p[1] for p in plan})},
             "stage_ms": {k: round(v, 4) for k, v in stage.items()},
             "step_hbm_frac": round(step_bytes / (ms_graph * 1e-3) / 1e9 / PEAK_HBM_GBS, 4),
             "gemm_launches": {n: {"ms": round(v["ms"], 4), "tflops": round(v["tflops"], 1),

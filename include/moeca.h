@@ -194,6 +194,16 @@ int moeca_forward_noalloc(const moeca_layer* layer, const void* x, int samples, 
 int moeca_cache_reset(moeca_layer* layer, void* stream);
 
 /* ---- statistics of the last step -------------------------------------- */
+/* Tilings of the expert FFN's grouped GEMMs. */
+enum {
+  MOECA_TILES_LARGE = 0,  /* 128 rows by 256 columns (bf16; fewer columns where
+                             the projection has fewer), or the fp32 tiles     */
+  MOECA_TILES_STREAM = 1, /* 128 x 288, weight-streaming: few rows per expert;
+                             a down projection adds K in four pieces          */
+  MOECA_TILES_WIDE = 2,   /* all rows of an expert (384 at most) x 144: a few
+                             hundred rows per expert; up projection only      */
+  MOECA_TILES_TALL = 3    /* 256 x 256: more rows                             */
+};
 typedef struct moeca_stats {
   int64_t n_branches;      /* B * N * k                                        */
   int64_t n_recompute;     /* |R| summed over tokens                           */
@@ -205,14 +215,8 @@ typedef struct moeca_stats {
   int32_t nonfinite;       /* 1 if a router logit was NaN or infinite          */
   double reuse_over_match; /* n_reused / n_matched (Sec. 5.4, Fig. 8); 0 if none */
   int32_t expert_count[64];/* recomputed branches per expert                  */
-  int32_t ffn_plan;        /* tiling of the last step's expert FFN: 0 the
-                              128 x 256 or 256 x 256 tiles, 1 a cache step in
-                              the weight-streaming tiles (few rows per
-                              expert), 2 the expert-wide up-projection tiles
-                              (a few hundred rows per expert) with a down
-                              projection as in 0; a full step with few rows
-                              per expert also streams its weights and reports
-                              2 or, where the layer cannot take those, 0    */
+  int32_t ffn_plan;        /* MOECA_TILES_* of the last step's up projection  */
+  int32_t ffn_plan_down;   /* and of its down projection                      */
 } moeca_stats;
 
 /* Copy the last step's statistics to *out.  Synchronises the stream. */

@@ -167,7 +167,7 @@ struct moeca_layer {
   bool mid_outside = false;      // the FFN intermediate is not in ws
   void* external_mid = nullptr;  // its address when mid_outside
   bool last_full = false;
-  int last_plan = 0;
+  int last_plan = 0, last_plan_down = 0;
   bool timing = false;
   std::vector<hipEvent_t> events;
   int timed_steps = 0;
@@ -484,9 +484,11 @@ int layer_step(moeca_layer* L, const void* x_t, const void* x_ffn, int t, void* 
   if (timed) ++L->timed_steps;
   if (!uncached) L->valid = true;
   L->last_full = full;
-  // a full step reports its size class whichever tiles stream its weights
-  L->last_plan = plan.thin_up && !full ? 1
-                 : plan.wide_up || (plan.thin_up && moeca::wide_capable(s)) ? 2 : 0;
+  L->last_plan = plan.thin_up ? MOECA_TILES_STREAM
+                 : plan.wide_up ? MOECA_TILES_WIDE
+                 : plan.tall_up ? MOECA_TILES_TALL : MOECA_TILES_LARGE;
+  L->last_plan_down = plan.thin_down ? MOECA_TILES_STREAM
+                      : plan.tall_down ? MOECA_TILES_TALL : MOECA_TILES_LARGE;
   return MOECA_OK;
 }
 
@@ -502,6 +504,9 @@ int moeca_cache_reset(moeca_layer* L, void* stream) {
   L->valid = false;
   return MOECA_OK;
 }
+
+// ffn_plan_down fills what was padding: the size callers pass has not changed.
+static_assert(sizeof(moeca_stats) == 328, "layout of moeca_stats");
 
 int moeca_get_stats(moeca_layer* L, moeca_stats* out, void* stream) {
   if (L == nullptr || out == nullptr) return fail(MOECA_E_INVAL, "layer and out are required");
@@ -532,6 +537,7 @@ int moeca_get_stats(moeca_layer* L, moeca_stats* out, void* stream) {
       out->n_matched > 0 ? double(out->n_reused) / double(out->n_matched) : 0.0;
   out->full_step = L->last_full ? 1 : 0;
   out->ffn_plan = L->last_plan;
+  out->ffn_plan_down = L->last_plan_down;
   for (int32_t v : rf) out->nonfinite |= v;
   return MOECA_OK;
 }

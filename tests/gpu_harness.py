@@ -28,15 +28,43 @@ def say(msg):
     print(msg, flush=True)
 
 
+# tilings of the expert FFN's GEMMs (MOECA_TILES_*)
+LARGE, STREAM, WIDE, TALL = 0, 1, 2, 3
+
+
+def step_plan(shape: LayerShape, rows: int, one_piece=False):
+    """Tilings of the up and the down projection that the library takes for a
+    step expected to leave `rows` routed branches (CUs: 256).  Weight-streaming
+    tiles up to 112 rows per expert, the expert-wide up projection up to 320,
+    256 x 256 tiles from 288 rows per group where tiles of 192 rows come to
+    160 and K is at least 1152, else the 128-row tiles.  one_piece: the down
+    projection adds K in one piece (full steps of a stack's block)."""
+    if shape.dtype != "bf16":
+        return LARGE, LARGE
+    plain = shape.n_shared == 0 and shape.ffn == "gelu"
+    few = (plain and rows <= 112 * shape.E and shape.branches <= 256 * shape.E
+           and 2 * shape.E * -(-shape.d_ff // 288) >= 256)
+    groups = shape.E + shape.n_shared
+    mean = (rows + shape.n_shared * shape.tokens) // groups
+
+    def tall(K, n):
+        return (K >= 1152 and n >= 512 and mean >= 288
+                and -(-mean // 192) * groups * -(-n // 256) >= 160)
+
+    if few:
+        up = STREAM
+    elif plain and rows <= 320 * shape.E and shape.d_ff % 144 == 0:
+        up = WIDE
+    else:
+        up = TALL if tall(shape.d, shape.up_rows) else LARGE
+    down = (STREAM if few and not one_piece
+            else TALL if tall(shape.d_ff, shape.d) else LARGE)
+    return up, down
+
+
 def full_step_plan(shape: LayerShape) -> int:
-    """FFN tiling the library takes on a full step of this layer: the
-    expert-wide up projection (2) when every branch leaves at most 320 rows
-    per expert on average and the layer can take it (bf16, ungated, no
-    shared experts, hidden width a multiple of 144), else the 128-row tiles
-    (0)."""
-    wide_capable = (shape.dtype == "bf16" and shape.n_shared == 0 and shape.ffn == "gelu"
-                    and shape.d_ff % 144 == 0 and shape.tokens * shape.d < 2 ** 31)
-    return 2 if wide_capable and shape.branches <= 320 * shape.E else 0
+    """Tiling of the up projection on a full step of this layer."""
+    return step_plan(shape, shape.branches)[0]
 
 
 class Setup:
@@ -195,7 +223,8 @@ def check_step(S: Setup, t: int, rec: dict, out_o, st_old: O.State, st_new: O.St
     dims, dt = S.dims, S.shape.dtype
     B, N, k, E, d = dims.B, dims.N, dims.k, dims.E, dims.d
     tol = TOL[dt]
-    info = {"label": label, "t": t, "ffn_plan": int(L.stats().ffn_plan)}
+    info = {"label": label, "t": t, "ffn_plan": int(L.stats().ffn_plan),
+            "ffn_plan_down": int(L.stats().ffn_plan_down)}
     forced = {}
 
     # router: logits bit-exact unless the oracle's fp64 sum is a near-tie

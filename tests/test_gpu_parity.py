@@ -16,7 +16,7 @@ from oracle import moeca_oracle as O
 from paper_2606_15615_amd.synth import LayerShape, WORKLOADS
 
 from gpu_harness import (Setup, check_step, full_step_plan, oracle_rerun, run_forced, say,
-                         rel_err)
+                         rel_err, step_plan)
 
 
 @pytest.fixture(scope="module", autouse=True)
@@ -340,17 +340,19 @@ def test_xl1024_sampled(mode):
     if mode == "ratio":
         for info in infos[1:]:
             assert abs(info["recompute_frac"] - 0.3) < 0.02
-        # cache steps: about 307 rows per expert, the expert-wide up projection
+        # a full step in the 256 x 256 tiles; cache steps: about 307 rows per
+        # expert, the expert-wide up projection
+        assert infos[0]["ffn_plan"] == infos[0]["ffn_plan_down"] == 3
         assert [i["ffn_plan"] for i in infos] == [full_step_plan(shape), 2, 2, 2]
 
 
 @pytest.mark.timeout(600)
-@pytest.mark.parametrize("ratio,plan", [(0.05, 2), (0.6, 0)])
+@pytest.mark.parametrize("ratio,plan", [(0.05, 2), (0.6, 3)])
 def test_xl1024_sampled_other_ratios(ratio, plan):
     """The benchmarked layer at a low and a high refresh ratio: the cache
     steps leave about 50 rows per expert plus the unmatched branches (the
     expert-wide up projection with few rows per tile) and about 600 (the
-    128 x 256 tiles for both projections); a refresh step, then two cache
+    256 x 256 tiles for both projections); a refresh step, then two cache
     steps."""
     shape = WORKLOADS["xl1024"]
     S = Setup(shape, mode="ratio", seed=13, T=3, ratio=ratio, refresh_cycle=0)
@@ -390,7 +392,10 @@ THIN_SHAPES = [
 def test_thin_plan_trajectory(shape, ratio):
     S = Setup(shape, mode="ratio", seed=31, T=4, ratio=ratio, refresh_cycle=0)
     infos = run_forced(S, 4, label=f"thin {shape}")
-    assert [i["ffn_plan"] for i in infos] == [full_step_plan(S.shape), 1, 1, 1]
+    first = step_plan(shape, shape.branches)
+    assert [(i["ffn_plan"], i["ffn_plan_down"]) for i in infos] == [first] + 3 * [(1, 1)]
+    # 32 and 25 rows per expert on a full step: it streams its weights too
+    assert first == ((1, 1) if shape.branches <= 112 * shape.E else (2, 0))
 
 
 @pytest.mark.parametrize("shape,plan", [
