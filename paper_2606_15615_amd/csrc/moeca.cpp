@@ -452,10 +452,13 @@ int layer_step(moeca_layer* L, const void* x_t, const void* x_ffn, int t, void* 
   const int64_t rows = full ? s.branches()
                        : p.mode == MOECA_MODE_RATIO ? int64_t(budget) * s.B
                                                     : s.branches() * 5 / 8;
-  // A full step of a stack's block adds K in one piece: its output goes on
-  // into every later block's router, where another order of the sums moves
-  // tied branches.  (The up projection's sums are the same in any tiling.)
-  const bool pieces = b.part != nullptr && !(full && s.bf16 && L->mid_outside);
+  // A block of a stack splits K of its down projection in ratio-mode cache
+  // steps only: its output goes on into every later block's router, where
+  // another order of the sums moves tied branches, and full and threshold-mode
+  // steps add K in one piece, as layers with more rows do.  (The up
+  // projection's sums are the same in any tiling.)
+  const bool pieces = b.part != nullptr &&
+                      !(L->mid_outside && (full || p.mode == MOECA_MODE_THRESHOLD));
   const moeca::FfnPlan plan = moeca::ffn_plan(s, rows, pieces);
   arm();
   if (!check(moeca::launch_decide(s, sel, budget, p.lambda0, p.lambda1, p.lambda2, !uncached, p.tau0,

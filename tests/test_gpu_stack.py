@@ -265,6 +265,22 @@ def test_stack_projection_tiles_forced(B, N):
     run_forced(SS, 2)
 
 
+@pytest.mark.parametrize("mode,down", [("threshold", 0), ("ratio", 1)])
+def test_stack_down_projection_pieces(mode, down):
+    """Blocks with few rows per expert (16 on a full step) stream their
+    weights; K of the down projection is split in ratio-mode cache steps only,
+    and added in one piece (the 128 x 256 tiles) in full and threshold steps."""
+    sh = StackShape(L=1, d=576, heads=8, E=16, k=2, d_ff=2304, B=1, N=128)
+    say(f"down projection pieces {mode}")
+    SS = StackSetup(sh, mode=mode, seed=5, T=2, refresh_cycle=0)
+    st, plans = D.BlockState(SS.dims), []
+    for t in range(2):
+        _, st = check_block(SS, 0, t, st, SS.xs[t])
+        stats = SS.S.layer(0).stats()
+        plans.append((stats.ffn_plan, stats.ffn_plan_down))
+    assert plans == [(1, 0), (1, down)]
+
+
 def test_stack_full_mode_forced():
     """The uncached comparator: every step is a full step."""
     say("stack_tiny full mode")
