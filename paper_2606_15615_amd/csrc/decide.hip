@@ -10,6 +10,7 @@
 // No atomic operation decides an order: counts use integer atomics only.
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 #include "common.h"
 #include "internal.h"
@@ -121,24 +122,6 @@ __device__ __forceinline__ bool token_slots(const int8_t* sq, const uint8_t* sm,
   }
   return any;
 }
-// Group table entries E..E+S: the shared experts (Sec. 2.3, shared-expert
-// MoE eq.) follow the routed ones in the FFN's grouped GEMM, T rows each (every
-// token, in token order), so their offsets and tile prefixes continue the
-// routed totals (o rows, tu / td tiles).  Tile tables: up at [0, E+S],
-// down at [E+S+1, 2(E+S)+1].
-__device__ __forceinline__ void write_shared_groups(int32_t* __restrict__ off,
-                                                    int32_t* __restrict__ tiles, int E, int S,
-                                                    int T, int tm_up, int tm, int nt_up,
-                                                    int nt_down, int o, int tu, int td) {
-  const int mts_up = (T + tm_up - 1) / tm_up;
-  const int mts = (T + tm - 1) / tm;
-  for (int s2 = 0; s2 <= S; ++s2) {
-    off[E + s2] = o + s2 * T;
-    tiles[E + s2] = tu + s2 * mts_up * nt_up;
-    tiles[E + S + 1 + E + s2] = td + s2 * mts * nt_down;
-  }
-}
-
 // What the lists and the GEMM tile tables are made with and written to.
 struct ListArgs {
   int S, T;  // shared experts, tokens of the batch
@@ -146,44 +129,54 @@ struct ListArgs {
   int32_t *off, *tiles, *list, *pos, *row_dst;
 };
 
-// The tables from the experts' row counts, by one wave (lane e < E holds
-// expert e's count t): returns the expert's first list row, and where `write`
-// is set stores the group offsets and the tile prefixes.
-__device__ __forceinline__ int list_tables(int t, int E, const ListArgs& a, bool write) {
+// Group table entries E..E+S: the shared experts (Sec. 2.3, shared-expert
+// MoE eq.) follow the routed ones in the FFN's grouped GEMM, T rows each (every
+// token, in token order), so their offsets and tile prefixes continue the
+// routed totals.  Both functions run on one wave, lane e < E holding expert e's
+// row count t (0 past the experts).
+
+// Offsets; returns the expert's first list row.
+__device__ __forceinline__ int list_offsets(int t, int E, const ListArgs& a, bool write) {
   const int lane = threadIdx.x & (kWave - 1);
-  int tm_up = a.tm_up, tm = a.tm;
-  if (a.tall_up) tm_up = tall_rows(lane < E ? t : 0, E, a.S, a.T, a.nt_up, a.cus);
-  if (a.tall_down) tm = tall_rows(lane < E ? t : 0, E, a.S, a.T, a.nt_down, a.cus);
-  const int mt_up = (t + tm_up - 1) / tm_up;
-  const int mt = (t + tm - 1) / tm;
-  // inclusive scans over experts
   const int o = wave_incl_scan_i32(t);
-  const int tu = wave_incl_scan_i32(mt_up * a.nt_up);
-  const int td = wave_incl_scan_i32(mt * a.nt_down);
   if (write && lane < E) {
-    // exclusive prefixes per expert; the last expert also writes the
-    // prefixes of the shared experts and the totals
     a.off[lane] = o - t;
-    a.tiles[lane] = tu - mt_up * a.nt_up;
-    a.tiles[E + a.S + 1 + lane] = td - mt * a.nt_down;
-    if (lane == E - 1) {
-      write_shared_groups(a.off, a.tiles, E, a.S, a.T, tm_up, tm, a.nt_up, a.nt_down, o, tu, td);
-      a.tiles[2 * (E + a.S + 1)] = tm_up;
-      a.tiles[2 * (E + a.S + 1) + 1] = tm;
-    }
+    if (lane == E - 1)
+      for (int s2 = 0; s2 <= a.S; ++s2) a.off[E + s2] = o + s2 * a.T;
   }
   return o - t;
+}
+
+// Tile prefixes and tile height of one projection: up at tiles [0, E+S], down
+// at [E+S+1, 2(E+S)+1], then the two heights.
+__device__ __forceinline__ void tile_table(int t, int E, const ListArgs& a, bool down) {
+  const int lane = threadIdx.x & (kWave - 1);
+  const int G = E + a.S;
+  const int nt = down ? a.nt_down : a.nt_up;
+  int tm = down ? a.tm : a.tm_up;
+  if (down ? a.tall_down : a.tall_up) tm = tall_rows(t, E, a.S, a.T, nt, a.cus);
+  const int n = (t + tm - 1) / tm * nt;
+  const int x = wave_incl_scan_i32(n);
+  int32_t* const out = a.tiles + (down ? G + 1 : 0);
+  if (lane < E) out[lane] = x - n;
+  if (lane == E - 1) {
+    const int ns = (a.T + tm - 1) / tm * nt;
+    for (int s2 = 0; s2 <= a.S; ++s2) out[E + s2] = x + s2 * ns;
+    a.tiles[2 * (G + 1) + (down ? 1 : 0)] = tm;
+  }
 }
 
 // Ratio mode: once a digit leaves at most this many keys sharing the
 // threshold's prefix, one wave ranks them directly.
 constexpr int kDirect = 64;
 
-// LISTS: a batch of one sample with at most two branches per thread also
+struct NoLists {};
+
+// LA = ListArgs: a batch of one sample with at most two branches per thread also
 // builds the expert lists and tile tables here (lists_kernel's, the same
 // values) from what the block holds in registers and LDS: the launch of its
 // own took 3.4-4.8 us, nearly all of it ramp and round trips.
-template <int R, bool LISTS = false>
+template <int R, typename LA>
 __global__ __launch_bounds__(kSelThreads) void decide_kernel(
     const int32_t* __restrict__ e_t, const float* __restrict__ w_t,
     const int32_t* __restrict__ e_c, const float* __restrict__ w_c,
@@ -194,7 +187,8 @@ __global__ __launch_bounds__(kSelThreads) void decide_kernel(
     int32_t* __restrict__ q_out,
     float* __restrict__ margin, uint8_t* __restrict__ mask, int32_t* __restrict__ sigma,
     uint8_t* __restrict__ sync, int32_t* __restrict__ cnt_bs, int32_t* __restrict__ stats_bs,
-    int32_t* __restrict__ cnt_ch, ListArgs la) {
+    int32_t* __restrict__ cnt_ch, LA la) {
+  constexpr bool LISTS = std::is_same<LA, ListArgs>::value;
   static_assert(!LISTS || R <= 2, "the lists need a branch's mask and expert in registers");
   __shared__ int s_wcnt[LISTS ? R : 1][LISTS ? kSelWaves : 1][64];
   __shared__ int s_base[64];
@@ -598,8 +592,8 @@ __global__ __launch_bounds__(kSelThreads) void decide_kernel(
   }
   __syncthreads();
   if constexpr (LISTS) {
-    // each wave ranks its recomputed branches per expert; the last wave (it
-    // has the fewest tokens below) makes the tables
+    // each wave ranks its recomputed branches per expert; the last waves (they
+    // have the fewest tokens below) make the tables
 #pragma unroll
     for (int r = 0; r < R; ++r) {
       rk[r] = 0;
@@ -609,10 +603,12 @@ __global__ __launch_bounds__(kSelThreads) void decide_kernel(
         if (rec_e[r] == ee) rk[r] = lane_rank(bal);
       }
     }
+    const int t = lane < E ? s_cnt[lane] : 0;
     if (wv == kSelWaves - 1) {
-      const int first = list_tables(lane < E ? s_cnt[lane] : 0, E, la, true);
+      const int first = list_offsets(t, E, la, true);
       if (lane < E) s_base[lane] = first;
     }
+    if (wv >= kSelWaves - 3 && wv < kSelWaves - 1) tile_table(t, E, la, wv == kSelWaves - 2);
   }
 
   // 4. per token: sync flag and slots
@@ -667,9 +663,11 @@ __global__ __launch_bounds__(kSelThreads) void decide_kernel(
 // expert; one 1024-thread block per chunk of 1024 consecutive branches of a
 // sample (chunk c of sample b covers flat ids b N k + 1024 c ..).  Every
 // block reads the [B][RC][E] chunk count table written by the decide kernel
-// and derives, per expert, the total (-> expert offsets, block 0 also writes
-// them and the GEMM tile tables) and the count in the chunks before its own
-// in flat order (-> its write base).  Within the chunk each wave ranks its
+// and derives, per expert, the total (-> expert offsets) and the count in the
+// chunks before its own in flat order (-> its write base).  One more block
+// writes the offsets and, a wave each, the two GEMM tile tables: in a block
+// with branches of its own the choice of the tile heights held up the lists
+// (16384 branches, both heights chosen: 6.4 us, 4.7 without).  Within the chunk each wave ranks its
 // selected branches per expert with ballots; branches of earlier waves, then
 // of lower lanes come first (stable, no atomics).
 // ---------------------------------------------------------------------------
@@ -683,9 +681,9 @@ __global__ __launch_bounds__(kSelThreads) void lists_kernel(
   __shared__ int s_wcnt[kSelWaves][64];
   const int nb = N * k;
   const int rc_n = (nb + kSelThreads - 1) / kSelThreads;
-  const int b = blockIdx.x / rc_n;
-  const int c = blockIdx.x % rc_n;
-  const int my = blockIdx.x;  // flat chunk index (b rc_n + c)
+  const int my = blockIdx.x;  // flat chunk index (b rc_n + c); B rc_n: the tables
+  const int b = my / rc_n;
+  const int c = my % rc_n;
   const int nchunks = B * rc_n;
   const int tid = threadIdx.x;
   const int lane = tid & (kWave - 1);
@@ -694,7 +692,7 @@ __global__ __launch_bounds__(kSelThreads) void lists_kernel(
   // this block's branch, loaded first
   const int j = c * kSelThreads + tid;
   const int64_t f = int64_t(b) * nb + j;
-  const bool in = j < nb;
+  const bool in = my < nchunks && j < nb;
   const bool sel = in && mask[f] != 0;
   const int ev = sel ? e_t[f] : -1;
   const int sg = sel ? sigma[f] : 0;
@@ -714,7 +712,7 @@ __global__ __launch_bounds__(kSelThreads) void lists_kernel(
   s_part_tot[tid] = tot;
   s_part_bef[tid] = bef;
   __syncthreads();
-  if (wv == 0) {
+  if (wv == 0 || (my == nchunks && wv < 3)) {
     int t = 0, bf = 0;
     if (lane < E) {
 #pragma unroll 4
@@ -723,9 +721,14 @@ __global__ __launch_bounds__(kSelThreads) void lists_kernel(
         bf += s_part_bef[pp * E + lane];
       }
     }
-    const int first = list_tables(t, E, la, my == 0);
-    if (lane < E) s_base[lane] = first + bf;
+    if (wv == 0) {
+      const int first = list_offsets(t, E, la, my == nchunks);
+      if (lane < E) s_base[lane] = first + bf;
+    } else {
+      tile_table(t, E, la, wv == 2);
+    }
   }
+  if (my == nchunks) return;
   int rk = 0;
   for (int ee = 0; ee < E; ++ee) {
     const bool mine = ev == ee;
@@ -1198,22 +1201,21 @@ hipError_t launch_decide(const Shape& s, int sel_mode, int budget, float lambda0
   }
   const size_t lds = size_t(2) * nb;
   if (lds > 64 * 1024) return hipErrorInvalidValue;
-  const ListArgs la = list_args(s, plan, b);
-#define MOECA_DECIDE(...)                                                                     \
-  launch_kernel(&decide_kernel<__VA_ARGS__>, dim3(s.B), dim3(kSelThreads), uint32_t(lds), st, b.e_t,   \
+#define MOECA_DECIDE(RR, LA, la)                                                              \
+  launch_kernel(&decide_kernel<RR, LA>, dim3(s.B), dim3(kSelThreads), uint32_t(lds), st, b.e_t,   \
                 b.w_t, b.e_c, b.w_c, b.n_c, b.ent, with_stat ? 1 : 0, log_n, tau0,            \
                 alpha,                                                                        \
                 b.hbar, b.tau, s.N, s.E, s.k, sel_mode, budget, lambda0, lambda1, lambda2,    \
                 b.q,                                                                          \
                 b.margin, b.mask, b.sigma, b.sync, b.cnt_bs, b.stats_bs, b.cnt_ch, la)
   if (decide_lists(s)) {
-    MOECA_DECIDE(2, true);
+    MOECA_DECIDE(2, ListArgs, list_args(s, plan, b));
   } else if (nb <= 2 * kSelThreads) {
-    MOECA_DECIDE(2);
+    MOECA_DECIDE(2, NoLists, NoLists{});
   } else if (nb <= 8 * kSelThreads) {
-    MOECA_DECIDE(8);
+    MOECA_DECIDE(8, NoLists, NoLists{});
   } else if (nb <= 32 * kSelThreads) {
-    MOECA_DECIDE(32);
+    MOECA_DECIDE(32, NoLists, NoLists{});
   } else {
     return hipErrorInvalidValue;
   }
@@ -1224,7 +1226,7 @@ hipError_t launch_decide(const Shape& s, int sel_mode, int budget, float lambda0
 hipError_t launch_lists(const Shape& s, const FfnPlan& plan, const Buffers& b, hipStream_t st) {
   const int rc_n = (s.N * s.k + kSelThreads - 1) / kSelThreads;
   if (s.E > 64) return hipErrorInvalidValue;
-  launch_kernel(&lists_kernel, dim3(s.B * rc_n), dim3(kSelThreads), 0, st, b.mask, b.e_t,
+  launch_kernel(&lists_kernel, dim3(s.B * rc_n + 1), dim3(kSelThreads), 0, st, b.mask, b.e_t,
                 b.cnt_ch, s.B, s.N, s.E, s.k, b.sigma, list_args(s, plan, b));
   return hipGetLastError();
 }
