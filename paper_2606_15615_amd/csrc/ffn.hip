@@ -1998,10 +1998,48 @@ static bool tall_capable(int64_t rows, int K, int Nout) {
   return K >= kTallMinK && Nout >= 512 && rows * K < (int64_t(1) << 31);
 }
 
+// Whether the projection takes the 256 x 256 tiles rather than the 128 x 256
+// ones when the routed experts are expected to have `rows` branches in all.
+//
+// Both run in rounds of one tile per CU.  Per k-tile of 64 a round costs, in
+// the units of tall_cost, 255 in the 128 x 256 tiles and 160 + tm in tiles of
+// tm rows; an up projection 320, and 12 tm (gated 6 tm, with half the stores)
+// per tile for the activation and the stores, which the larger tile has in one
+// piece after its k-loop.  An expert's rows are taken a 32nd above the mean, so
+// that a mean of just whole tiles counts as more than that, and the larger
+// tiles have to win by a 32nd.  Fitted to both kernels' times on 13 layers
+// (width 512 to 2048, 8 to 32 experts, 77 to 2048 rows per expert) and checked
+// on 13 others (704 to 3072, 8 to 64 experts): of 466 pairs none where the
+// larger tiles are chosen is more than 2 % slower.  The down projection of 16
+// experts of 1152 x 4608 in one round of 128 x 256 tiles, 307 and 358 rows per
+// expert: 72.0 and 73.2 us against 74.7 and 76.1 (one round of either); past
+// it, 410 and 512 rows: 123.7 and 129.6 against 89.6 and 88.1.  The up
+// projection, 359, 410, 512 and 614 rows: 88.6, 101.5, 117.9 and 130.0 us
+// against 95.9, 107.3, 109.7 and 138.9.  Below 144 rows (down) and 200 (up) the
+// times no longer follow the rounds.
+static bool tall_pays(const Shape& s, int64_t rows, int K, int n, bool up) {
+  const int64_t mean = rows / s.E;
+  if (mean < (up ? 200 : 144)) return false;
+  const int nt = (n + kTallTN - 1) / kTallTN, kt = K / kTK;
+  const int cus = device_cus();
+  auto rounds = [&](int tm) {
+    const int64_t most = mean + (mean + 31) / 32;
+    const int64_t mt = s.E * ((most + tm - 1) / tm) + s.S * ((s.tokens() + tm - 1) / tm);
+    return (mt * nt + cus - 1) / cus;
+  };
+  const int64_t tail = up ? (s.swiglu ? 6 : 12) : 0;
+  int64_t tall = -1;
+  for (int tm = 128; tm <= kTallTM; tm += 64) {
+    const int64_t c = rounds(tm) * (kt * tall_cost(tm) + tail * tm);
+    if (tall < 0 || c < tall) tall = c;
+  }
+  return 32 * tall < 31 * rounds(128) * kt * (up ? 320 : 255);
+}
+
 // Weight-row counts of at least 512 take the large 128 x 256 tile (a
-// partial last N tile is masked); smaller ones the 128 x 128 / 128 x 64
-// tiles; the thin plan the 128 x 288 tile; the wide plan the expert-wide
-// 384 x 144 up-projection tile (the down projection keeps the large tile).
+// partial last N tile is masked) or the 256 x 256 one; smaller ones the 128 x
+// 128 / 128 x 64 tiles; the thin plan the 128 x 288 tile; the wide plan the
+// expert-wide 384 x 144 up-projection tile.
 FfnPlan ffn_plan(const Shape& s, int64_t rows, bool partials) {
   auto tn = [](int n) { return n >= 512 ? kBigTN : (n % 128 == 0 ? 128 : 64); };
   FfnPlan p;
@@ -2012,25 +2050,13 @@ FfnPlan ffn_plan(const Shape& s, int64_t rows, bool partials) {
     p.split_down = f32_split(s);
     return p;
   }
-  const int64_t mean_rows = (rows + s.S * s.tokens()) / s.groups();
   const bool few = rows <= int64_t(kThinRows) * s.E && thin_capable(s);
   p.thin_up = few;
   p.thin_down = few && partials;
   p.tn_up = tn(s.up_rows());
   p.tn_down = tn(s.d);
-  // 256 x 256 tiles only where tiles of 192 rows come to five eighths of the
-  // CUs (12 experts of 640 x 2560, 300 and 600 rows each: a cycle of three
-  // steps 326 us with them, 311 with 128 x 256) and K is deep (960 x 3840:
-  // 480 us with the up projection in them, 465 without)
-  constexpr int kTallDeepK = 1152;
-  auto fills = [&](int n) {
-    return (mean_rows + 191) / 192 * s.groups() * ((n + kTallTN - 1) / kTallTN) >=
-           device_cus() * 5 / 8;
-  };
-  p.tall_up = tall_capable(s.tokens(), s.d, s.up_rows()) && mean_rows >= kTallRows &&
-              fills(s.up_rows()) && s.d >= kTallDeepK;
-  p.tall_down = tall_capable(s.mid_rows(), s.d_ff, s.d) && mean_rows >= kTallRows &&
-                fills(s.d) && s.d_ff >= kTallDeepK;
+  p.tall_up = tall_capable(s.tokens(), s.d, s.up_rows()) && tall_pays(s, rows, s.d, s.up_rows(), true);
+  p.tall_down = tall_capable(s.mid_rows(), s.d_ff, s.d) && tall_pays(s, rows, s.d_ff, s.d, false);
   if (p.thin_up) {
     p.tall_up = false;
     p.tn_up = kThinTN;

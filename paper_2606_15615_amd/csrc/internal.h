@@ -134,12 +134,6 @@ constexpr int kThinRows = 112;
 // against 92 us; a threshold-mode step with about 232, in the 128 x 256 tiles
 // before, the cycle of three 655 -> 591 us.
 constexpr int kWideRows = 320;
-// Steps with at least this many rows per group (routed and shared experts)
-// on average take the 256 x 256 tiles.  Measured sides (16 experts of 1152 x
-// 4608; 128 x 256 tiles against these): 375 rows per expert down 131 against 92
-// us, 307 rows down 80 against 76, 256 rows down 74 against 76, 225 rows up 49
-// against 53 and down 62 against 66 us.
-constexpr int kTallRows = 288;
 // rows: branches the routed experts are expected to have in this step;
 // partials: the down projection may split K (its partial sums have a place).
 FfnPlan ffn_plan(const Shape& s, int64_t rows, bool partials);

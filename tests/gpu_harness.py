@@ -32,34 +32,45 @@ def say(msg):
 LARGE, STREAM, WIDE, TALL = 0, 1, 2, 3
 
 
+def tall_pays(shape: LayerShape, rows: int, K: int, n: int, up: bool) -> bool:
+    """Whether a projection takes the 256 x 256 tiles rather than the 128 x 256
+    ones: rounds of tiles over 256 CUs times the cost of a tile (per k-tile 255,
+    up 320, against 160 + its rows, with a tail of 12 per row, gated 6, in an
+    up projection)."""
+    mean, kt = rows // shape.E, K // 64
+    if K < 256 or n < 512 or mean < (200 if up else 144):
+        return False
+    most = mean + -(-mean // 32)
+
+    def rounds(tm):
+        mt = shape.E * -(-most // tm) + shape.n_shared * -(-shape.tokens // tm)
+        return -(-mt * -(-n // 256) // 256)
+
+    tail = (6 if shape.ffn == "swiglu" else 12) if up else 0
+    tall = min(rounds(tm) * (kt * (160 + tm) + tail * tm) for tm in (128, 192, 256))
+    return 32 * tall < 31 * rounds(128) * kt * (320 if up else 255)
+
+
 def step_plan(shape: LayerShape, rows: int, one_piece=False):
     """Tilings of the up and the down projection that the library takes for a
-    step expected to leave `rows` routed branches (CUs: 256).  Weight-streaming
-    tiles up to 112 rows per expert, the expert-wide up projection up to 320,
-    256 x 256 tiles from 288 rows per group where tiles of 192 rows come to
-    160 and K is at least 1152, else the 128-row tiles.  one_piece: the down
+    step expected to leave `rows` routed branches: weight-streaming tiles up to
+    112 rows per expert, the expert-wide up projection up to 320, the 256 x 256
+    tiles where they pay, else the 128-row ones.  one_piece: the down
     projection adds K in one piece (full steps of a stack's block)."""
     if shape.dtype != "bf16":
         return LARGE, LARGE
     plain = shape.n_shared == 0 and shape.ffn == "gelu"
     few = (plain and rows <= 112 * shape.E and shape.branches <= 256 * shape.E
            and 2 * shape.E * -(-shape.d_ff // 288) >= 256)
-    groups = shape.E + shape.n_shared
-    mean = (rows + shape.n_shared * shape.tokens) // groups
-
-    def tall(K, n):
-        return (K >= 1152 and n >= 512 and mean >= 288
-                and -(-mean // 192) * groups * -(-n // 256) >= 160)
-
     if few:
         up = STREAM
     elif plain and rows <= 320 * shape.E and shape.d_ff % 144 == 0:
         up = WIDE
     else:
-        up = TALL if tall(shape.d, shape.up_rows) else LARGE
-    down = (STREAM if few and not one_piece
-            else TALL if tall(shape.d_ff, shape.d) else LARGE)
-    return up, down
+        up = TALL if tall_pays(shape, rows, shape.d, shape.up_rows, True) else LARGE
+    if few and not one_piece:
+        return up, STREAM
+    return up, TALL if tall_pays(shape, rows, shape.d_ff, shape.d, False) else LARGE
 
 
 def full_step_plan(shape: LayerShape) -> int:

@@ -343,16 +343,19 @@ def test_xl1024_sampled(mode):
         # a full step in the 256 x 256 tiles; cache steps: about 307 rows per
         # expert, the expert-wide up projection
         assert infos[0]["ffn_plan"] == infos[0]["ffn_plan_down"] == 3
+        # the down projection is one round of 128 x 256 tiles (240): no larger ones
+        assert [i["ffn_plan_down"] for i in infos[1:]] == [0, 0, 0]
         assert [i["ffn_plan"] for i in infos] == [full_step_plan(shape), 2, 2, 2]
 
 
 @pytest.mark.timeout(600)
-@pytest.mark.parametrize("ratio,plan", [(0.05, 2), (0.6, 3)])
+@pytest.mark.parametrize("ratio,plan", [(0.05, 2), (0.6, 0)])
 def test_xl1024_sampled_other_ratios(ratio, plan):
     """The benchmarked layer at a low and a high refresh ratio: the cache
     steps leave about 50 rows per expert plus the unmatched branches (the
     expert-wide up projection with few rows per tile) and about 600 (the
-    256 x 256 tiles for both projections); a refresh step, then two cache
+    128 x 256 tiles, and 256 x 256 ones for the down projection, whose 128 x
+    256 tiles would take a second round); a refresh step, then two cache
     steps."""
     shape = WORKLOADS["xl1024"]
     S = Setup(shape, mode="ratio", seed=13, T=3, ratio=ratio, refresh_cycle=0)
@@ -361,6 +364,7 @@ def test_xl1024_sampled_other_ratios(ratio, plan):
     for info in infos[1:]:
         assert info["recompute_frac"] >= ratio - 0.02
     assert [i["ffn_plan"] for i in infos] == [full_step_plan(S.shape), plan, plan]
+    assert [i["ffn_plan_down"] for i in infos] == [3] + 2 * [0 if ratio == 0.05 else 3]
 
 
 @pytest.mark.timeout(600)
