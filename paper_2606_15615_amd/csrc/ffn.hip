@@ -2040,7 +2040,7 @@ static bool tall_pays(const Shape& s, int64_t rows, int K, int n, bool up) {
 // partial last N tile is masked) or the 256 x 256 one; smaller ones the 128 x
 // 128 / 128 x 64 tiles; the thin plan the 128 x 288 tile; the wide plan the
 // expert-wide 384 x 144 up-projection tile.
-FfnPlan ffn_plan(const Shape& s, int64_t rows, bool partials) {
+FfnPlan ffn_plan(const Shape& s, int64_t rows, int64_t most, bool partials) {
   auto tn = [](int n) { return n >= 512 ? kBigTN : (n % 128 == 0 ? 128 : 64); };
   FfnPlan p;
   p.tm = p.tm_up = 128;
@@ -2050,7 +2050,8 @@ FfnPlan ffn_plan(const Shape& s, int64_t rows, bool partials) {
     p.split_down = f32_split(s);
     return p;
   }
-  const bool few = rows <= int64_t(kThinRows) * s.E && thin_capable(s);
+  const bool few = rows <= int64_t(kThinRows) * s.E &&
+                   (most == rows || most <= int64_t(kThinTM) * s.E) && thin_capable(s);
   p.thin_up = few;
   p.thin_down = few && partials;
   p.tn_up = tn(s.up_rows());

@@ -126,7 +126,9 @@ constexpr int kThinSplit = 4;
 // unmatched branches of a cache step come on top).  Measured (16 experts of
 // 1152 x 4608): a full step with 32 rows per expert, up and down, 108 us with
 // the expert-wide and the 128 x 256 tiles, 63 us with these; with 256 rows 144
-// against 205 us (two 128-row tiles read each weight slice twice).
+// against 205 us (two 128-row tiles read each weight slice twice).  A
+// threshold step, whose rows the host cannot know, takes them only if even all
+// of its branches come to one 128-row tile per expert on average.
 constexpr int kThinRows = 112;
 // A step with more rows per expert than that, and at most this many on
 // average, takes the expert-wide up-projection tiles (all of an expert's
@@ -134,9 +136,11 @@ constexpr int kThinRows = 112;
 // against 92 us; a threshold-mode step with about 232, in the 128 x 256 tiles
 // before, the cycle of three 655 -> 591 us.
 constexpr int kWideRows = 320;
-// rows: branches the routed experts are expected to have in this step;
-// partials: the down projection may split K (its partial sums have a place).
-FfnPlan ffn_plan(const Shape& s, int64_t rows, bool partials);
+// rows: branches the routed experts are expected to have in this step; most:
+// the most they may have where the host cannot know (threshold mode), else
+// rows; partials: the down projection may split K (its partial sums have a
+// place).
+FfnPlan ffn_plan(const Shape& s, int64_t rows, int64_t most, bool partials);
 // K pieces of an fp32 layer's down projection (1: not split).  Above 1 the
 // workspace holds `part`.
 int f32_split(const Shape& s);

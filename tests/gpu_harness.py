@@ -51,16 +51,18 @@ def tall_pays(shape: LayerShape, rows: int, K: int, n: int, up: bool) -> bool:
     return 32 * tall < 31 * rounds(128) * kt * (320 if up else 255)
 
 
-def step_plan(shape: LayerShape, rows: int, one_piece=False):
+def step_plan(shape: LayerShape, rows: int, one_piece=False, most=None):
     """Tilings of the up and the down projection that the library takes for a
     step expected to leave `rows` routed branches: weight-streaming tiles up to
     112 rows per expert, the expert-wide up projection up to 320, the 256 x 256
     tiles where they pay, else the 128-row ones.  one_piece: the down
-    projection adds K in one piece (full steps of a stack's block)."""
+    projection adds K in one piece (full steps of a stack's block); most: every
+    branch of a threshold step (one weight-streaming tile has to hold them)."""
     if shape.dtype != "bf16":
         return LARGE, LARGE
     plain = shape.n_shared == 0 and shape.ffn == "gelu"
     few = (plain and rows <= 112 * shape.E and shape.branches <= 256 * shape.E
+           and (most is None or most <= 128 * shape.E)
            and 2 * shape.E * -(-shape.d_ff // 288) >= 256)
     if few:
         up = STREAM

@@ -402,17 +402,22 @@ def test_thin_plan_trajectory(shape, ratio):
     assert first == ((1, 1) if shape.branches <= 112 * shape.E else (2, 0))
 
 
-@pytest.mark.parametrize("shape,plan", [
-    (THIN_SHAPES[0][0], 1),
-    (LayerShape(d=576, E=8, k=2, d_ff=1152, B=4, N=512, dtype="bf16"), 2),
+@pytest.mark.parametrize("shape,plan,tau0", [
+    (THIN_SHAPES[0][0], 1, 0.8),
+    (LayerShape(d=576, E=8, k=2, d_ff=4608, B=4, N=128, dtype="bf16"), 1, 0.02),
+    (LayerShape(d=576, E=8, k=2, d_ff=4608, B=3, N=230, dtype="bf16"), 2, 0.02),
+    (LayerShape(d=576, E=8, k=2, d_ff=1152, B=4, N=512, dtype="bf16"), 2, 0.8),
 ])
-def test_threshold_mode_plans(shape, plan):
-    """Threshold-mode cache steps choose their tiles by an expected row count:
-    20 rows per expert (weight-streaming tiles) and 320, the most that take
-    the expert-wide up projection."""
-    S = Setup(shape, mode="threshold", seed=32, T=3, refresh_cycle=0)
+def test_threshold_mode_plans(shape, plan, tau0):
+    """Threshold-mode cache steps choose their tiles by an expected row count
+    and the largest: 20 rows per expert of 32 and 80 of 128 (weight-streaming
+    tiles), 107 of 172, which would be two such tiles if everything is
+    recomputed, as it is with tau0 0.02, and 320, the most that take the
+    expert-wide up projection."""
+    S = Setup(shape, mode="threshold", seed=32, T=3, refresh_cycle=0, tau0=tau0)
     infos = run_forced(S, 3, label=f"threshold {shape}")
     assert [i["ffn_plan"] for i in infos] == [full_step_plan(S.shape), plan, plan]
+    assert step_plan(shape, shape.branches * 5 // 8, most=shape.branches)[0] == plan
 
 
 @pytest.mark.parametrize("shape", [
