@@ -200,16 +200,21 @@ __global__ __launch_bounds__(kGemvWaves * kWave) void gemv_kernel(
 // ---------------------------------------------------------------------------
 // LayerNorm + AdaLN modulation and the gated residuals
 // ---------------------------------------------------------------------------
-// A block of four waves takes a row: thread l holds the float4 chunks l +
-// 256 j (j < NC), NC = ceil(d / 1024).  With few rows a launch lasts as long as
-// one row's chain of fp64 sums, conversions and waits on memory, which four
-// waves shorten, and at NC <= 2 the AdaLN vectors fit the registers and are
-// requested together with the row; with many rows it is bound by HBM.  Against
-// a wave per row (a cycle of four steps, width 1152): four blocks of 250
-// tokens 2966 -> 2841 us; two blocks of 2048, 4096 and 8192 tokens 2162 ->
-// 2149, 3041 -> 3000 and 4253 -> 4246 us.
+// W waves take a row: thread l holds the float4 chunks l + 64 W j (j < NC), NC =
+// ceil(d / (256 W)), and the AdaLN vectors are requested together with the row.
+// With few rows a launch lasts as long as one row's chain of fp64 sums,
+// conversions and waits on memory, which more waves shorten; with many it is
+// bound by HBM, and waves that hold little of a row, or none of it, only cost
+// (four per row, 16384 rows: 128 wide 31 us against 14 with one, 384 wide 41
+// against 25).  Cycles of four steps of two blocks with one, two and four
+// waves per row, us:
+//   width   256 tokens             2048 tokens            16384 tokens
+//    256    750   756   755         848   851   867       1482  1534  1665
+//    384    809   789   792         907   903   913       1927  1949  2067
+//    576    867   852   833        1001   996  1001       2521  2560  2598
+//    768    916   899   884        1083  1078  1080       2937  2978  3005
+//   1152   1048  1015  1001        1372  1351  1364       4424  4273  4425
 constexpr int kLnWaves = 4;
-constexpr int kLnThreads = kLnWaves * kWave;
 
 enum { kLnAttn = 0, kLnMlp = 1, kLnFinal = 2 };
 
@@ -231,48 +236,50 @@ struct LnArgs {
   const float* x1p;         // [T][d] the previous block's x1 (with pending)
 };
 
-// Sum over the threads of a row; red: a buffer of its own for each sum.
+// Sum over the W waves of a row; red: a buffer of its own for each sum.
+template <int W>
 __device__ __forceinline__ double row_sum(double x, double* red) {
   x = wave_sum_f64(x);
+  if constexpr (W == 1) return x;
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = x;
   __syncthreads();
-  return (red[0] + red[1]) + (red[2] + red[3]);
+  return W == 2 ? red[0] + red[1] : (red[0] + red[1]) + (red[2] + red[3]);
 }
 
-template <int NC>
+template <int NC, int W>
 __device__ __forceinline__ void ln_stats(const float (&v)[NC][4], int n4, int lane, int d,
                                          double* red, double& mean, double& rstd) {
   double s = 0.0;
 #pragma unroll
   for (int j = 0; j < NC; ++j)
-    if (lane + kLnThreads * j < n4)
+    if (lane + W * kWave * j < n4)
 #pragma unroll
       for (int e = 0; e < 4; ++e) s += v[j][e];
-  const double mu = row_sum(s, red) / d;
+  const double mu = row_sum<W>(s, red) / d;
   double q = 0.0;
 #pragma unroll
   for (int j = 0; j < NC; ++j)
-    if (lane + kLnThreads * j < n4)
+    if (lane + W * kWave * j < n4)
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const double t = v[j][e] - mu;
         q += t * t;
       }
-  const double var = row_sum(q, red + kLnWaves) / d;
+  const double var = row_sum<W>(q, red + kLnWaves) / d;
   mean = mu;
   rstd = 1.0 / sqrt(var + 1e-6);
 }
 
 // bf16(LN(v) * (1 + scale) + shift) into row `dst` in fp32: the attention
 // input (off the decision path)
-template <int NC>
+template <int NC, int W>
 __device__ __forceinline__ void ln_store_f32(const float (&v)[NC][4], int n4, int lane,
                                              double mean, double rstd, const float4 (&shift)[NC],
                                              const float4 (&scale)[NC], uint16_t* dst) {
   const float mf = static_cast<float>(mean), rf = static_cast<float>(rstd);
 #pragma unroll
   for (int j = 0; j < NC; ++j) {
-    const int c = lane + kLnThreads * j;
+    const int c = lane + W * kWave * j;
     if (c < n4) {
       const float4 sh = shift[j];
       const float4 sc = scale[j];
@@ -287,13 +294,13 @@ __device__ __forceinline__ void ln_store_f32(const float (&v)[NC][4], int n4, in
 
 // bf16(LN(v) * (1 + scale) + shift) into row `dst`, in fp64 and rounded
 // once: this is the MoE routing input (decision-path arithmetic)
-template <int NC>
+template <int NC, int W>
 __device__ __forceinline__ void ln_store(const float (&v)[NC][4], int n4, int lane,
                                          double mean, double rstd, const float4 (&shift)[NC],
                                          const float4 (&scale)[NC], uint16_t* dst) {
 #pragma unroll
   for (int j = 0; j < NC; ++j) {
-    const int c = lane + kLnThreads * j;
+    const int c = lane + W * kWave * j;
     if (c < n4) {
       const float4 sh = shift[j];
       const float4 sc = scale[j];
@@ -310,11 +317,12 @@ __device__ __forceinline__ void ln_store(const float (&v)[NC][4], int n4, int la
   }
 }
 
-template <int MODE, int NC>
-__global__ __launch_bounds__(kLnThreads) void ln_kernel(LnArgs p) {
-  __shared__ double red[4 * kLnWaves];  // four sums
-  const int lane = threadIdx.x;          // thread of the row
-  const int r = blockIdx.x;
+// One wave per row: four rows to a block; W > 1: a block per row.
+template <int MODE, int NC, int W>
+__global__ __launch_bounds__(W == 1 ? kLnWaves * kWave : W * kWave) void ln_kernel(LnArgs p) {
+  __shared__ double red[W == 1 ? 1 : 4 * kLnWaves];  // four sums
+  const int lane = W == 1 ? threadIdx.x & 63 : threadIdx.x;  // thread of the row
+  const int r = W == 1 ? blockIdx.x * kLnWaves + (threadIdx.x >> 6) : blockIdx.x;
   int row;
   if constexpr (MODE == kLnMlp) {
     if (r >= *p.count) return;
@@ -332,7 +340,7 @@ __global__ __launch_bounds__(kLnThreads) void ln_kernel(LnArgs p) {
   auto fetch = [&](float4 (&x)[NC], const float* q) __attribute__((always_inline)) {
 #pragma unroll
     for (int j = 0; j < NC; ++j) {
-      const int c = lane + kLnThreads * j;
+      const int c = lane + W * kWave * j;
       if (c < n4) x[j] = reinterpret_cast<const float4*>(q)[c];
     }
   };
@@ -353,7 +361,7 @@ __global__ __launch_bounds__(kLnThreads) void ln_kernel(LnArgs p) {
     const float* g = m + 5 * d;
 #pragma unroll
     for (int j = 0; j < NC; ++j) {
-      const int c = lane + kLnThreads * j;
+      const int c = lane + W * kWave * j;
       if (c < n4) {
         const float4 x1 = reinterpret_cast<const float4*>(p.x1 + o)[c];
         const u32x2_t yy = reinterpret_cast<const u32x2_t*>(p.y + o)[c];
@@ -376,7 +384,7 @@ __global__ __launch_bounds__(kLnThreads) void ln_kernel(LnArgs p) {
     const float* gp = p.mod_prev + int64_t(b) * 6 * d + 5 * d;
 #pragma unroll
     for (int j = 0; j < NC; ++j) {
-      const int c = lane + kLnThreads * j;
+      const int c = lane + W * kWave * j;
       if (c < n4) {
         const float4 x1 = reinterpret_cast<const float4*>(p.x1p + o)[c];
         const u32x2_t yy = reinterpret_cast<const u32x2_t*>(p.y + o)[c];
@@ -392,7 +400,7 @@ __global__ __launch_bounds__(kLnThreads) void ln_kernel(LnArgs p) {
   } else {
 #pragma unroll
     for (int j = 0; j < NC; ++j) {
-      const int c = lane + kLnThreads * j;
+      const int c = lane + W * kWave * j;
       if (c < n4) {
         const float4 xx = reinterpret_cast<const float4*>(p.x + o)[c];
         v[j][0] = xx.x;
@@ -409,20 +417,20 @@ __global__ __launch_bounds__(kLnThreads) void ln_kernel(LnArgs p) {
   if (with_a) {
 #pragma unroll
     for (int j = 0; j < NC; ++j) {
-      const int c = lane + kLnThreads * j;
+      const int c = lane + W * kWave * j;
       if (c < n4) av[j] = reinterpret_cast<const u32x2_t*>(p.a + o)[c];
     }
   }
   double mean, rstd;
   if (MODE == kLnAttn) {
-    ln_stats(v, n4, lane, d, red, mean, rstd);
-    ln_store_f32(v, n4, lane, mean, rstd, sh_a, sc_a, p.h + o);
+    ln_stats<NC, W>(v, n4, lane, d, red, mean, rstd);
+    ln_store_f32<NC, W>(v, n4, lane, mean, rstd, sh_a, sc_a, p.h + o);
     if (!p.cached) return;
   }
   // x1 = x + g_a * a, then the MoE input from LN(x1)
 #pragma unroll
   for (int j = 0; j < NC; ++j) {
-    const int c = lane + kLnThreads * j;
+    const int c = lane + W * kWave * j;
     if (c < n4) {
       const u32x2_t aa = av[j];
       const float4 gg = g_a[j];
@@ -433,14 +441,14 @@ __global__ __launch_bounds__(kLnThreads) void ln_kernel(LnArgs p) {
       reinterpret_cast<float4*>(p.x1 + o)[c] = float4{v[j][0], v[j][1], v[j][2], v[j][3]};
     }
   }
-  ln_stats(v, n4, lane, d, red + 2 * kLnWaves, mean, rstd);
+  ln_stats<NC, W>(v, n4, lane, d, red + 2 * kLnWaves, mean, rstd);
   // a routing input (LN1 of a cache step, LN2 of a full step) takes the
   // decision-path arithmetic, so that the same input routes the same way on
   // either kind of step; the rebuilt FFN input of a cache step takes fp32
   if (MODE == kLnAttn || p.routing)
-    ln_store(v, n4, lane, mean, rstd, sh_m, sc_m, p.u + o);
+    ln_store<NC, W>(v, n4, lane, mean, rstd, sh_m, sc_m, p.u + o);
   else
-    ln_store_f32(v, n4, lane, mean, rstd, sh_m, sc_m, p.u + o);
+    ln_store_f32<NC, W>(v, n4, lane, mean, rstd, sh_m, sc_m, p.u + o);
 }
 
 // ---------------------------------------------------------------------------
@@ -847,15 +855,34 @@ hipError_t launch_gemv(const double* in, int B, int K, const GemvBatch& mats, in
   return hipGetLastError();
 }
 
+// Waves per row (the table above): one for the narrowest rows, and up to 768
+// wide where there are many; four for few rows; else two.
+int ln_waves(int T, int d) {
+  if (d <= 256 || (d <= 768 && T > 2048)) return 1;
+  return d > 512 && T <= 1024 ? 4 : 2;
+}
+
 template <int MODE>
 hipError_t launch_ln(const LnArgs& p, int T, int d, hipStream_t st) {
-  static_assert(kMaxWidth <= 2 * 4 * kLnThreads, "two chunks per thread at most");
   if (d > kMaxWidth) return hipErrorInvalidValue;
-  if (d <= 4 * kLnThreads)
-    launch_kernel(&ln_kernel<MODE, 1>, dim3(T), dim3(kLnThreads), 0, st, p);
-  else
-    launch_kernel(&ln_kernel<MODE, 2>, dim3(T), dim3(kLnThreads), 0, st, p);
-  return hipGetLastError();
+  const int W = ln_waves(T, d);
+  const dim3 grid(W == 1 ? (T + kLnWaves - 1) / kLnWaves : T), block(kWave * (W == 1 ? kLnWaves : W));
+#define MOECA_LN(WW, NC)                                                    \
+  if (W == WW && d <= 4 * kWave * WW * NC) {                                \
+    launch_kernel(&ln_kernel<MODE, NC, WW>, grid, block, 0, st, p);         \
+    return hipGetLastError();                                               \
+  }
+  MOECA_LN(1, 1)
+  MOECA_LN(1, 2)
+  MOECA_LN(1, 3)
+  MOECA_LN(2, 1)
+  MOECA_LN(2, 2)
+  MOECA_LN(2, 3)
+  MOECA_LN(2, 4)
+  MOECA_LN(4, 1)
+  MOECA_LN(4, 2)
+#undef MOECA_LN
+  return hipErrorInvalidValue;
 }
 
 hipError_t launch_ln_attn(const BlockBufs& k, int T, int N, int d, const float* mod,

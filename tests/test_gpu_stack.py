@@ -254,6 +254,26 @@ def test_stack_head_widths_ragged_forced(d, heads):
     run_forced(SS, 3)
 
 
+@pytest.mark.parametrize("d,heads,B,N", [
+    (64, 1, 3, 7),        # one wave per row, a ragged last block of four rows
+    (512, 8, 9, 229),     # one wave, two chunks
+    (576, 8, 9, 229),     # one wave, three chunks, the last a quarter full
+    (384, 6, 2, 33),      # two waves, the second half full
+    (576, 8, 5, 205),     # two waves, two chunks: the fewest rows
+    (1152, 16, 5, 205),   # two waves, three chunks
+    (2048, 32, 5, 205),   # two waves, four chunks
+    (576, 8, 4, 256),     # four waves: the most rows
+    (1152, 16, 1, 40),    # four waves, two chunks
+])
+def test_stack_layernorm_waves_forced(d, heads, B, N):
+    """Every number of waves and chunks per row that the LayerNorms take, at
+    the edges of the rule on width and rows (1024 and 2048)."""
+    sh = StackShape(L=2 if d < 576 else 1, d=d, heads=heads, E=2, k=1, d_ff=64, B=B, N=N)
+    say(f"LayerNorm {d} wide, {B} x {N}")
+    SS = StackSetup(sh, mode="ratio", seed=6, T=2, ratio=0.4)
+    run_forced(SS, 2)
+
+
 @pytest.mark.parametrize("B,N", [(16, 345), (3, 257), (2, 32)])
 def test_stack_projection_tiles_forced(B, N):
     """Projection tilings at d = 576 (nine k-tiles, 64-column remainders): 5520
