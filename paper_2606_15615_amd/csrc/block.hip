@@ -461,13 +461,12 @@ __global__ __launch_bounds__(W == 1 ? kLnWaves * kWave : W * kWave) void ln_kern
 // tab[0..3] = {0, nS, 0, tiles of nS rows x ntn_q} and tab[8] = the rows of a
 // tile, at most, for the projections of the listed tokens; the full-list call
 // also writes ident[t] = t and the same for the k/v projection, tab[4..7] and
-// tab[9].  cus_q, cus_kv > 0: 256-column tiles, their height chosen for that
-// many CUs; 0: 64-row tiles.
+// tab[9].  rows_q, rows_kv: the rows of a tile; 0: chosen for `cus` CUs.
 constexpr int kListThreads = 1024;
 
 __global__ __launch_bounds__(kListThreads) void slist_kernel(
-    const uint8_t* __restrict__ sync, int all, int B, int N, int ntn_q, int ntn_kv, int cus_q,
-    int cus_kv,
+    const uint8_t* __restrict__ sync, int all, int B, int N, int ntn_q, int ntn_kv,
+    int rows_q, int rows_kv, int cus,
     int32_t* __restrict__ slist, int32_t* __restrict__ soff, int32_t* __restrict__ ident,
     int32_t* __restrict__ tab) {
   __shared__ int s_wave[kListThreads / kWave];
@@ -513,8 +512,8 @@ __global__ __launch_bounds__(kListThreads) void slist_kernel(
   if (lane == 0) soff[b] = base;
   if (b == B - 1) {
     const int ns = run;
-    const int tm_q = cus_q > 0 ? tall_rows(lane == 0 ? ns : 0, 1, 0, 0, ntn_q, cus_q) : kSlimRows;
-    const int tm_kv = cus_kv > 0 ? tall_rows(lane == 0 ? T : 0, 1, 0, 0, ntn_kv, cus_kv) : kSlimRows;
+    const int tm_q = rows_q > 0 ? rows_q : tall_rows(lane == 0 ? ns : 0, 1, 0, 0, ntn_q, cus);
+    const int tm_kv = rows_kv > 0 ? rows_kv : tall_rows(lane == 0 ? T : 0, 1, 0, 0, ntn_kv, cus);
     if (lane == 0) {
       soff[B] = ns;
       tab[0] = 0;
@@ -910,11 +909,11 @@ hipError_t launch_ln_final(const BlockBufs& k, int T, int N, int d, const float*
 
 hipError_t launch_slist(const BlockBufs& k, const uint8_t* sync, int N, int d, hipStream_t st) {
   const int64_t T = int64_t(k.B) * N;
-  const bool tq = proj_tall(T, d, d), tkv = proj_tall(T, d, 2 * d);
-  const int cq = proj_tile_cols(tq), ckv = proj_tile_cols(tkv);
+  const ProjTile q = proj_tile(T, d, d), kv = proj_tile(T, d, 2 * d);
+  const int cq = proj_tile_cols(q), ckv = proj_tile_cols(kv);
   launch_kernel(&slist_kernel, dim3(k.B), dim3(kListThreads), 0, st, sync, sync == nullptr ? 1 : 0,
-                k.B, N, (d + cq - 1) / cq, (2 * d + ckv - 1) / ckv, tq ? device_cus() : 0,
-                tkv ? device_cus() : 0, k.slist, k.soff, k.ident, k.tab);
+                k.B, N, (d + cq - 1) / cq, (2 * d + ckv - 1) / ckv, proj_tile_rows(q),
+                proj_tile_rows(kv), device_cus(), k.slist, k.soff, k.ident, k.tab);
   return hipGetLastError();
 }
 

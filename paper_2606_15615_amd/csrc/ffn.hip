@@ -103,8 +103,10 @@ __device__ __forceinline__ void group_row(int e, int E, int r0, int rows, int r,
                                           const int32_t* __restrict__ row_dst, int& src,
                                           int& dst) {
   const int rr = r < rows ? r : 0;
-  static_assert(KIND != kProj, "projections read the list directly");
-  if (e < E) {
+  if (KIND == kProj) {
+    src = list[r0 + rr];
+    dst = r < rows ? list[r0 + r] : -1;
+  } else if (e < E) {
     if (KIND == kUp) {
       src = list[r0 + rr] / k;
       dst = r < rows ? r0 + r : -1;
@@ -465,7 +467,7 @@ __global__ __launch_bounds__(kBigThreads, 1) void gemm_bf16_big_kernel(
     const uint16_t* __restrict__ Wsh, const int32_t* __restrict__ off,
     const int32_t* __restrict__ tile_off, const int32_t* __restrict__ list,
     const int32_t* __restrict__ row_dst, int E, int G, int k, int K, int Nout,
-    uint16_t* __restrict__ dst, uint16_t* __restrict__ dst_sh) {
+    const float* __restrict__ bias, uint16_t* __restrict__ dst, uint16_t* __restrict__ dst_sh) {
   constexpr int TM = kBigTM, TN = kBigTN;
   constexpr bool kGated = ACT == kActSwiglu;
   constexpr int FM = 2, FN = 2;  // wave tile: 64 rows x 64 columns
@@ -628,8 +630,18 @@ __global__ __launch_bounds__(kBigThreads, 1) void gemm_bf16_big_kernel(
           uint32_t pk[4][2];
 #pragma unroll
           for (int q = 0; q < 4; ++q) {
-            pk[q][0] = pack2_bf16(act_fn<ACT>(a[4 * q]), act_fn<ACT>(a[4 * q + 1]));
-            pk[q][1] = pack2_bf16(act_fn<ACT>(a[4 * q + 2]), act_fn<ACT>(a[4 * q + 3]));
+            if constexpr (ACT == kActBias) {
+              // columns c .. c + 3 of the bias (clamped: masked columns are not stored)
+              const int c = c0 + i * 32 + 8 * q + 4 * h;
+              float bv[4];
+#pragma unroll
+              for (int s2 = 0; s2 < 4; ++s2) bv[s2] = bias[min(c + s2, Nout - 1)];
+              pk[q][0] = pack2_bf16(a[4 * q] + bv[0], a[4 * q + 1] + bv[1]);
+              pk[q][1] = pack2_bf16(a[4 * q + 2] + bv[2], a[4 * q + 3] + bv[3]);
+            } else {
+              pk[q][0] = pack2_bf16(act_fn<ACT>(a[4 * q]), act_fn<ACT>(a[4 * q + 1]));
+              pk[q][1] = pack2_bf16(act_fn<ACT>(a[4 * q + 2]), act_fn<ACT>(a[4 * q + 3]));
+            }
           }
 #pragma unroll
           for (int p = 0; p < 2; ++p) {
@@ -1519,7 +1531,7 @@ __global__ __launch_bounds__(256) void reduce_partials_kernel(
 // k-tiles in flight, so that at K = 1152 most of the operands are requested
 // before the first MFMA.
 // ---------------------------------------------------------------------------
-constexpr int kSlimTM = kSlimRows;
+constexpr int kSlimTM = 64;
 constexpr int kSlimTN = 64;
 constexpr int kSlimWaves = 4;
 constexpr int kSlimThreads = kSlimWaves * kWave;
@@ -1954,7 +1966,8 @@ hipError_t launch_gemm(const Shape& s, const FfnPlan& plan, const void* A, const
           b.tiles + 2 * (G + 1) + (KIND == kUp ? 0 : 1), static_cast<const float*>(nullptr), o, osh);
     } else if (tn == kBigTN) {
       launch_kernel(&gemm_bf16_big_kernel<KIND, ACT>, dim3(device_cus()), dim3(kBigThreads), 0, st,
-          a, w, wsh, b.off, toff, b.list, b.row_dst, s.E, G, s.k, K, Nout, o, osh);
+          a, w, wsh, b.off, toff, b.list, b.row_dst, s.E, G, s.k, K, Nout,
+          static_cast<const float*>(nullptr), o, osh);
     } else if (tn == 128) {
       launch_kernel(&gemm_bf16_kernel<128, 128, KIND, ACT>, dim3(grid), dim3(kGemmThreads), 0, st,
           a, w, wsh, b.off, toff, b.list, b.row_dst, s.E, G, s.k, K, Nout, o, osh);
@@ -2139,15 +2152,30 @@ hipError_t launch_ffn_down(const Shape& s, const void* W_down, const void* W_dow
                                       b.h_sh, st);
 }
 
-// 256-column tiles when the 64 x 64 ones would take more than about three
-// rounds over the CUs (at K = 1152 a round of them is 6 us, a 256-column tile
-// of 128 rows 18) and the tile can be taken.
-bool proj_tall(int64_t T, int K, int Nout) {
+// 64 x 64 tiles up to three rounds of them over the CUs, then 128 x 256 ones,
+// and the 256-column ones where every CU has some 43 k-tiles of the 128 x 256
+// tiles to do, so that their longer start and end count little.  Cycles of four
+// steps of two blocks (the cache steps project half the tokens), us, for the
+// q and output projections in the three tiles with k/v in 128 x 256, then for
+// k/v in the three with q and output in 128 x 256:
+//   width  tokens   q, output (64 x 64 tiles)      k/v (64 x 64 tiles)
+//    256     8192   1149  1151  1221  (512)        1187  1151  1169  (1024)
+//    384    16384   1894  1746  1811  (1536)       1954  1746  1776  (3072)
+//    768     4096   1420  1417  1486  (768)        1566  1417  1451  (1536)
+//   1024     2048   1257  1284  1345  (512)        1366  1284  1253  (1024)
+//   1152     3000   1726  1628  1700  (846)        1737  1628  1710  (1692)
+//   1152     8192   3000  2542  2588  (2304)       3304  2542  2630  (4608)
+//   1152    16384   5100  4293  4232  (4608)       5681  4293  4247  (9216)
+//   1536     8192   4137  3318  3355  (3072)       4387  3318  3111  (6144)
+ProjTile proj_tile(int64_t T, int K, int Nout) {
   const int64_t slim = (T + kSlimTM - 1) / kSlimTM * ((Nout + kSlimTN - 1) / kSlimTN);
-  return slim > 3 * device_cus() && tall_capable(T, K, Nout);
+  if (slim < 3 * device_cus()) return kProjSlim;
+  const int64_t big = (T + kBigTM - 1) / kBigTM * ((Nout + kBigTN - 1) / kBigTN);
+  return big * (K / kTK) >= 43 * device_cus() && tall_capable(T, K, Nout) ? kProjTall : kProjBig;
 }
 
-int proj_tile_cols(bool tall) { return tall ? kTallTN : kSlimTN; }
+int proj_tile_rows(ProjTile p) { return p == kProjSlim ? kSlimTM : p == kProjBig ? kBigTM : 0; }
+int proj_tile_cols(ProjTile p) { return p == kProjSlim ? kSlimTN : kBigTN; }
 
 hipError_t launch_proj(const void* A, const void* W, const float* bias, const int32_t* off,
                        const int32_t* tiles, const int32_t* list, const int32_t* tm, int64_t T,
@@ -2157,10 +2185,16 @@ hipError_t launch_proj(const void* A, const void* W, const float* bias, const in
   const int grid = blocks_per_xcd > 0 ? kXcds * std::min(blocks_per_xcd, cus_per_xcd())
                                       : device_cus();
   const auto* w = static_cast<const uint16_t*>(W);
-  if (proj_tall(T, K, Nout))
+  const ProjTile tile = proj_tile(T, K, Nout);
+  if (tile == kProjTall)
     launch_kernel(&gemm_bf16_tall_kernel<kProj, kActBias>, dim3(grid), dim3(kTallThreads), 0, st,
                   static_cast<const uint16_t*>(A), w, w, off, tiles, list,
                   static_cast<const int32_t*>(nullptr), 1, 1, 1, K, Nout, tm, bias,
+                  static_cast<uint16_t*>(dst), static_cast<uint16_t*>(dst));
+  else if (tile == kProjBig)
+    launch_kernel(&gemm_bf16_big_kernel<kProj, kActBias>, dim3(grid), dim3(kBigThreads), 0, st,
+                  static_cast<const uint16_t*>(A), w, w, off, tiles, list,
+                  static_cast<const int32_t*>(nullptr), 1, 1, 1, K, Nout, bias,
                   static_cast<uint16_t*>(dst), static_cast<uint16_t*>(dst));
   else
     launch_kernel(&gemm_bf16_slim_kernel, dim3(grid), dim3(kSlimThreads), 0, st,

@@ -216,7 +216,6 @@ const Buffers& layer_buffers(const moeca_layer* L);
 // ---- DiT block kernels (block.hip, ffn.hip) -----------------------------
 constexpr int kFreqDim = 256;    // timestep embedding width
 constexpr int kMaxWidth = 2048;  // largest block width d
-constexpr int kSlimRows = 64;    // rows of a 64-column projection tile, at most
 
 // Shared per-step activations of a block stack (device).
 struct BlockBufs {
@@ -247,10 +246,13 @@ struct BlockBufs {
 hipError_t launch_proj(const void* A, const void* W, const float* bias, const int32_t* off,
                        const int32_t* tiles, const int32_t* list, const int32_t* tm, int64_t T,
                        int K, int Nout, void* dst, hipStream_t st, int blocks_per_xcd = 0);
-// Whether a projection of up to T rows takes the 256-column tiles (of 256, 192
-// or 128 rows) or the 64 x 64 ones, and the columns of a tile of either kind.
-bool proj_tall(int64_t T, int K, int Nout);
-int proj_tile_cols(bool tall);
+// Tiles of a projection of up to T rows: 64 x 64, 128 x 256, or 256-column ones
+// of 256, 192 or 128 rows; the rows (0: chosen on the device) and columns of
+// each.
+enum ProjTile { kProjSlim, kProjBig, kProjTall };
+ProjTile proj_tile(int64_t T, int K, int Nout);
+int proj_tile_rows(ProjTile p);
+int proj_tile_cols(ProjTile p);
 // CUs per XCD (the device's CU count over 8).
 int cus_per_xcd();
 hipError_t launch_sinusoid(const float* t_values, int B, double* e, hipStream_t st);

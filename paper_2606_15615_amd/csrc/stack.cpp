@@ -325,11 +325,12 @@ int moeca_stack_step_blocks(moeca_stack* S, float* x, const float* c, int t, int
     // cannot share a CU with a GEMM block) and the q projection starts on them.
     int kv_share = 0;
     if (fork && !full) {
-      const bool tall = moeca::proj_tall(T, d, 2 * d);
-      const int cols = moeca::proj_tile_cols(tall);
+      const moeca::ProjTile tile = moeca::proj_tile(T, d, 2 * d);
+      const int cols = moeca::proj_tile_cols(tile);
       const int nt = (2 * d + cols - 1) / cols;
       const int cus = moeca::cus_per_xcd() * 8;
-      const int tm = tall ? moeca::tall_rows_one(T, nt, cus) : moeca::kSlimRows;
+      const int tm = tile == moeca::kProjTall ? moeca::tall_rows_one(T, nt, cus)
+                                              : moeca::proj_tile_rows(tile);
       const int per_xcd = ((T + tm - 1) / tm * nt + 7) / 8;
       const int rounds = (per_xcd + moeca::cus_per_xcd() - 1) / moeca::cus_per_xcd();
       kv_share = std::max(1, (per_xcd + rounds - 1) / std::max(1, rounds));

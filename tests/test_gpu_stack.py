@@ -274,13 +274,30 @@ def test_stack_layernorm_waves_forced(d, heads, B, N):
     run_forced(SS, 2)
 
 
-@pytest.mark.parametrize("B,N", [(16, 345), (3, 257), (2, 32)])
-def test_stack_projection_tiles_forced(B, N):
-    """Projection tilings at d = 576 (nine k-tiles, 64-column remainders): 5520
-    tokens take the 256-column tiles for q, k/v and the output, 771 and 64 the
-    64 x 64 ones (parts of 60 rows, and one exactly full)."""
-    sh = StackShape(L=1, d=576, heads=8, E=4, k=2, d_ff=128, B=B, N=N)
-    say(f"projection tiles {B} x {N}")
+# slim: 64 x 64 tiles; big: 128 x 256; tall: 256 columns, up to 256 rows
+@pytest.mark.parametrize("d,heads,B,N,q,kv", [
+    (576, 8, 2, 32, "slim", "slim"),     # nine k-tiles, a part exactly full
+    (576, 8, 3, 257, "slim", "slim"),    # parts of 60 rows
+    (576, 8, 16, 345, "big", "big"),     # 64-column remainders
+    (128, 2, 8, 1541, "slim", "big"),    # two k-tiles; k/v 256 columns
+    (128, 2, 8, 3073, "big", "big"),     # q and output: half a column tile
+    (192, 3, 8, 2057, "big", "big"),     # three k-tiles, 192 columns
+    (1152, 16, 8, 1025, "big", "big"),   # 18 k-tiles, the last row tile nearly empty
+    (1216, 19, 8, 1025, "big", "tall"),  # 19 k-tiles (odd), 64-column remainder
+    (1216, 19, 8, 2048, "tall", "tall"),
+])
+def test_stack_projection_tiles_forced(d, heads, B, N, q, kv):
+    """Every tiling of the q, k/v and output projections, at the edges of their
+    tiles; the rule that chooses them is repeated here."""
+    def tile(n):
+        T = B * N
+        if -(-T // 64) * -(-n // 64) < 3 * 256:
+            return "slim"
+        tall = d >= 256 and n >= 512 and -(-T // 128) * -(-n // 256) * (d // 64) >= 43 * 256
+        return "tall" if tall else "big"
+    assert (tile(d), tile(2 * d)) == (q, kv)
+    sh = StackShape(L=1, d=d, heads=heads, E=2, k=1, d_ff=64, B=B, N=N)
+    say(f"projection tiles {d} {B} x {N}")
     SS = StackSetup(sh, mode="ratio", seed=4, T=2, ratio=0.5)
     run_forced(SS, 2)
 
