@@ -126,27 +126,35 @@ def test_erf_gelu_values():
     assert err[tail].max() < 3e-10
 
 
-@pytest.mark.parametrize("E,N,B,d,d_ff,ffn,n_shared", [
-    (1, 384, 1, 576, 512, "gelu", 0),      # full parts of 128; 9 k-tiles (odd), N = 512 and 576
-    (1, 385, 1, 640, 832, "gelu", 1),      # parts of 96 and 97 rows, a shared expert
-    (2, 300, 2, 512, 512, "swiglu", 0),    # gated, uneven experts
-    (3, 611, 3, 704, 640, "gelu", 0),      # ragged rows, column remainders of 192 and 128
-    (2, 161, 4, 512, 1088, "swiglu", 2),   # 17 k-tiles, two shared experts
-    (4, 1024, 2, 512, 256, "gelu", 0),     # four k-tiles, the shortest the tile takes
-    (1, 1100, 1, 320, 8192, "gelu", 0),    # up: parts of up to 192 rows waste least (192 tiles)
-    (1, 1900, 1, 320, 8192, "gelu", 0),    # up: parts of up to 256 rows (256 tiles)
-    (1, 1900, 1, 320, 4096, "swiglu", 0),  # the same, gated
-    (2, 4500, 1, 320, 4160, "gelu", 0),    # several tiles per CU of different heights
+# rows per expert, then k-tiles of 64, columns past the last 256 and the tile
+# height that wastes least
+@pytest.mark.parametrize("E,N,B,k,d,d_ff,ffn,n_shared,up,down", [
+    (3, 2067, 1, 1, 1152, 256, "gelu", 2, 0, 3),   # 689; down 4 (the fewest), 128, 192
+    (8, 646, 2, 1, 1600, 320, "gelu", 2, 0, 3),    # 161; down 5, 64, 192
+    (8, 2162, 1, 1, 1728, 320, "gelu", 2, 0, 3),   # 270; down 5, 192, 256
+    (8, 1360, 3, 1, 1792, 256, "gelu", 0, 0, 3),   # 510; down 4, 0, 128
+    (2, 1413, 2, 1, 576, 832, "gelu", 2, 3, 0),    # 1413; up 9, 64, 192
+    (1, 320, 2, 1, 576, 2112, "swiglu", 2, 3, 0),  # 640; up 9, 128, 128
+    (8, 1943, 1, 1, 576, 832, "swiglu", 2, 3, 0),  # 242; up 9, 128, 256
+    (3, 1865, 2, 1, 640, 704, "gelu", 2, 3, 3),    # 1243; up 10, 192, 192; down 11, 128, 192
+    (8, 2032, 1, 1, 768, 1088, "gelu", 2, 3, 0),   # 254; up 12, 64, 128
+    (8, 1051, 2, 1, 512, 1536, "swiglu", 0, 3, 0), # 262; up 8, 0, 192
+    (2, 1159, 3, 1, 960, 704, "gelu", 2, 3, 3),    # 1738; up 15, 192, 128; down 11, 192, 192
+    (6, 700, 3, 2, 1216, 2432, "gelu", 0, 3, 0),   # 700; up 19, 128, 192; two branches a token
 ])
-def test_tall_tile_edges(E, N, B, d, d_ff, ffn, n_shared):
-    """Steps with at least 288 rows per group take the 256 x 256 tiles: every
-    class of tile height (up to 128, 192, 256 rows, equal parts), odd and
-    even k-tile counts, column remainders, gated and shared experts, several
-    tiles per CU; and the cache steps after a full one."""
-    shape = LayerShape(d=d, E=E, k=1, d_ff=d_ff, B=B, N=N, dtype="bf16", ffn=ffn,
+def test_tall_tile_edges(E, N, B, k, d, d_ff, ffn, n_shared, up, down):
+    """The 256 x 256 tiles (plan 3) at their edges: every class of tile height
+    (up to 128, 192, 256 rows, equal parts), odd and even k-tile counts down to
+    the fewest, every column remainder, gated and shared experts, several tiles
+    per CU; and the cache step after a full one.  The statistics say that the
+    tiles ran."""
+    shape = LayerShape(d=d, E=E, k=k, d_ff=d_ff, B=B, N=N, dtype="bf16", ffn=ffn,
                        n_shared=n_shared)
+    assert step_plan(shape, shape.branches) == (up, down)
     S = Setup(shape, mode="ratio", seed=22, T=2, ratio=0.9)
-    run_forced(S, 2, label=f"tall {E} {N} {B} {d} {d_ff} {ffn} {n_shared}")
+    infos = run_forced(S, 2, label=f"tall {E} {N} {B} {d} {d_ff} {ffn} {n_shared}")
+    cache = step_plan(shape, B * int(S.pol.ratio * N * k + 0.5))
+    assert [(i["ffn_plan"], i["ffn_plan_down"]) for i in infos] == [(up, down), cache]
 
 
 WIDE = LayerShape(d=128, E=16, k=8, d_ff=128, B=2, N=1100, dtype="bf16")
