@@ -729,7 +729,8 @@ __global__ __launch_bounds__(kTallThreads, 1) void gemm_bf16_tall_kernel(
     const uint16_t* __restrict__ Wsh, const int32_t* __restrict__ off,
     const int32_t* __restrict__ tile_off, const int32_t* __restrict__ list,
     const int32_t* __restrict__ row_dst, int E, int G, int k, int K, int Nout,
-    const int32_t* __restrict__ tm_dev, const float* __restrict__ bias, uint16_t* __restrict__ dst, uint16_t* __restrict__ dst_sh) {
+    const int32_t* __restrict__ tm_dev, const float* __restrict__ bias,
+    uint16_t* __restrict__ dst, uint16_t* __restrict__ dst_sh) {
   constexpr bool kGated = ACT == kActSwiglu;
   constexpr bool kListed = KIND != kDown;  // token rows come through the list
   __shared__ __attribute__((aligned(16))) unsigned char lds[2 * kTallBuf];
@@ -749,7 +750,7 @@ __global__ __launch_bounds__(kTallThreads, 1) void gemm_bf16_tall_kernel(
   if (tid < 128) s_toff[tid] = tid < G ? tile_off[tid] : 0x7fffffff;
   __syncthreads();
   const int KT = K / kTK;
-  const int TM = tm_dev != nullptr ? *tm_dev : kTallTM;  // rows of a tile, at most
+  const int TM = *tm_dev;  // rows of a tile, at most
   const int Nw = kGated ? Nout / 2 : Nout;
   const uint32_t lds0 = __builtin_amdgcn_readfirstlane(lds_addr(lds) + wv * 1024);
   const uint32_t sl0 = __builtin_amdgcn_readfirstlane(lds_addr(&s_list[0][0]) + (wv & 3) * 256);
@@ -1904,7 +1905,7 @@ hipError_t launch_gemm(const Shape& s, const FfnPlan& plan, const void* A, const
   const int G = s.groups();
   if (KIND == kUp && plan.wide_up) {
     // bf16, ungated, no shared experts (wide_capable)
-    if constexpr (ACT == kActSwiglu || ACT == kActBias || KIND != kUp) {
+    if constexpr (ACT == kActSwiglu || KIND != kUp) {
       return hipErrorInvalidValue;
     } else {
       launch_kernel(&gemm_bf16_wide_kernel<ACT>, dim3(device_cus()), dim3(kWideThreads), 0, st,
@@ -1914,23 +1915,25 @@ hipError_t launch_gemm(const Shape& s, const FfnPlan& plan, const void* A, const
     }
   }
   if (KIND == kUp ? plan.thin_up : plan.thin_down) {
-    // bf16, ungated, no shared experts (thin_capable)
-    if constexpr (ACT == kActSwiglu || ACT == kActBias) {
+    // bf16, ungated, no shared experts (thin_capable); the down projection with
+    // room for its partial sums (ffn_plan)
+    if constexpr (ACT == kActSwiglu) {
       return hipErrorInvalidValue;
     } else {
       const int32_t* toff = b.tiles + (KIND == kUp ? 0 : G + 1);
       const auto* a = static_cast<const uint16_t*>(A);
       const auto* w = static_cast<const uint16_t*>(W);
       const int64_t rows = s.mid_rows();
-      if (KIND == kDown && plan.split_down == kThinSplit && b.part != nullptr) {
+      if constexpr (KIND == kDown) {
+        if (b.part == nullptr) return hipErrorInvalidValue;
         // the stage's start event goes with the GEMM, its stop event with
         // the addition of the partial sums
         const LaunchEvents ev = launch_events();
         launch_events() = LaunchEvents{};
         const bool reduce = !combine_sums(s);
         launch_kernel_ev(&gemm_bf16_thin_kernel<kDown, kActNone, kThinSplit>, dim3(device_cus()),
-                         dim3(kThinThreads), 0, st, ev.start, reduce ? nullptr : ev.stop, a, w, b.off, toff, b.list,
-                         b.row_dst, s.E, s.k, K, Nout, rows, static_cast<uint16_t*>(nullptr),
+                         dim3(kThinThreads), 0, st, ev.start, reduce ? nullptr : ev.stop, a, w,
+                         b.off, toff, b.list, b.row_dst, s.E, s.k, K, Nout, rows, static_cast<uint16_t*>(nullptr),
                          b.part);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess || !reduce) return e;
@@ -1938,10 +1941,6 @@ hipError_t launch_gemm(const Shape& s, const FfnPlan& plan, const void* A, const
                          dim3(static_cast<unsigned>((rows + 3) / 4)), dim3(256), 0, st, nullptr,
                          ev.stop, static_cast<const float*>(b.part), rows, b.off, b.row_dst, s.E,
                          s.d, static_cast<uint16_t*>(b.h_c));
-      } else if (KIND == kDown) {
-        launch_kernel(&gemm_bf16_thin_kernel<kDown, kActNone, 1>, dim3(device_cus()),
-                      dim3(kThinThreads), 0, st, a, w, b.off, toff, b.list, b.row_dst, s.E, s.k,
-                      K, Nout, rows, static_cast<uint16_t*>(dst), static_cast<float*>(nullptr));
       } else {
         launch_kernel(&gemm_bf16_thin_kernel<kUp, ACT, 1>, dim3(device_cus()),
                       dim3(kThinThreads), 0, st, a, w, b.off, toff, b.list, b.row_dst, s.E, s.k,
