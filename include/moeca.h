@@ -166,6 +166,15 @@ int moeca_bind_attention(moeca_layer* layer, const void* attn_in, void* attn_cac
  * weights are unbound. */
 int moeca_step(moeca_layer* layer, const void* x_t, int t, void* out, void* stream);
 
+/* Last bits.  A row's sums over K are added in an order that depends on the
+ * tiling, and that is chosen from the layer and the number of branches a step
+ * is expected to compute: down projections of steps with few rows per expert
+ * (bf16: 112) or of small fp32 layers add K in 2, 4 or 8 pieces, others in
+ * one.  A sample's output can therefore differ in its last bits (fp32 sums in
+ * another order, before the one rounding to the policy type) between batch
+ * sizes, and between moeca_step and moeca_forward_noalloc, which adds in one
+ * piece where the pieces do not fit its array.  Equal calls give equal bits. */
+
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid allocation): the
  * uncached routed MoE layer, i.e. what moeca_step computes for a

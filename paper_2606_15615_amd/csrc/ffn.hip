@@ -665,8 +665,8 @@ __global__ __launch_bounds__(kBigThreads, 1) void gemm_bf16_big_kernel(
 }
 
 // ---------------------------------------------------------------------------
-// bf16 MFMA grouped GEMM, 256 x 256 tiles, for steps with at least a few
-// hundred rows per group.
+// bf16 MFMA grouped GEMM, 256 x 256 tiles, for steps with many rows per group
+// (tall_pays) and the largest projections (proj_tile).
 //
 // What a CU can load (about 20-25 bytes per clock from L2 and beyond), not the
 // MFMA rate, bounds the 128 x 256 tile of the kernel above: 48 KB per 4.2
@@ -1054,8 +1054,8 @@ __global__ __launch_bounds__(kTallThreads, 1) void gemm_bf16_tall_kernel(
 // an expert's up-projection rows split into equal tiles that give every CU
 // about one (16 experts x 4608 rows: 256 tiles); the down projection splits
 // K into SPLIT equal pieces (units), each writing its fp32 partial sums to
-// part[piece][row][column], which reduce_partials_kernel adds in piece
-// order.  8 waves (two per SIMD) of 32 rows x 144 columns, each 2 x 9
+// part[piece][row][column], which the combine (layers of combine_sums) or
+// reduce_partials_kernel adds in piece order.  8 waves (two per SIMD) of 32 rows x 144 columns, each 2 x 9
 // v_mfma_f32_16x16x32_bf16 tiles (weights the A operand, token rows the B
 // operand: a lane holds four consecutive output columns of one row), on the
 // large kernel's three-stage direct-to-LDS ring of 64-wide k-tiles with the
@@ -1663,8 +1663,8 @@ __global__ __launch_bounds__(kSlimThreads, 1) void gemm_bf16_slim_kernel(
 // the two fullest experts behind (204 against 191 us on a full step).  The
 // down projection may split K into `split` pieces (units), whose
 // partial sums go to part[piece][row][column] and are added in piece order
-// by reduce_partials_f32_kernel, so that layers with few output columns
-// still give every CU work.
+// by the combine or by reduce_partials_f32_kernel, so that layers with few
+// output columns still give every CU work.
 //
 // Measured at 2 x 333 tokens, 16 experts of 1152 x 4608, top-2 (340 MB of
 // weights per launch; the earlier kernel: 64 x 64 tiles, 16-wide k steps,
@@ -2094,8 +2094,9 @@ FfnPlan ffn_plan(const Shape& s, int64_t rows, int64_t most, bool partials) {
 }
 
 // K pieces of an fp32 layer's down projection: as many (1, 2, 4 or 8) as it
-// takes to give every block slot a unit at the mean row count per expert,
-// each of at least 192 inputs, while the partial sums stay below 32 MB.
+// takes to make four units per CU at the mean row count per expert, one more
+// than a CU holds at a time, each of at least 192 inputs, while the partial
+// sums stay below 32 MB.
 int f32_split(const Shape& s) {
   if (s.bf16 || s.S != 0) return 1;
   const int64_t mt = std::max<int64_t>(1, (s.branches() / s.E + kF32TM - 1) / kF32TM);
