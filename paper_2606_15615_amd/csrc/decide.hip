@@ -1165,7 +1165,11 @@ static ListArgs list_args(const Shape& s, const FfnPlan& plan, const Buffers& b)
                   b.list, b.pos, b.row_dst};
 }
 
-bool decide_lists(const Shape& s) { return s.B == 1 && s.N * s.k <= 2 * kSelThreads && s.E <= 64; }
+// Every wave ranks its branches by a ballot per expert, which the launch of its
+// own spreads over more blocks: select and lists together, 16, 32 and 64
+// experts, 9.5, 12.5 and 18.4 us apart (and a launch more) against 9.4, 13.7 and
+// 22.4 in one; with 64 a step of 374 tokens took 2 us more.
+bool decide_lists(const Shape& s) { return s.B == 1 && s.N * s.k <= 2 * kSelThreads && s.E <= 32; }
 
 hipError_t launch_decide(const Shape& s, int sel_mode, int budget, float lambda0, float lambda1,
                          float lambda2, bool with_stat, float tau0, float alpha,

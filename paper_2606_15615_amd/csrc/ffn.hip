@@ -2048,11 +2048,41 @@ static bool tall_pays(const Shape& s, int64_t rows, int K, int n, bool up) {
   return 32 * tall < 31 * rounds(128) * kt * (up ? 320 : 255);
 }
 
+// Whether a threshold step, or a full one that might have streamed its weights,
+// expected to leave `mean` rows per expert takes the expert-wide up projection
+// rather than 128 x 256 tiles: rounds over the CUs
+// times the cost of a tile, which for an expert-wide one grows with its rows.
+// One round of 128 x 256 tiles is not beaten.  Up projections, us, default
+// settings, 128 x 256 against expert-wide: 16 experts of 1152 x 4608 (2 rounds
+// of the latter; 2, 3 and 3 of the former), 103, 135 and 191 rows 55.8 and
+// 51.3, 55.5 and 54.7, 67.9 and 58.0; of 2688 x 5184 (3; 2, 3 and 3), 103, 137
+// and 190 rows 112 and 148, 143 and 153, 137 and 160; 8 experts of 1536 x 4608
+// (1; 1 and 2), 69 and 172 rows 25 and 31, 49 and 35.
+static bool wide_pays(const Shape& s, int64_t mean) {
+  const int cus = device_cus();
+  auto rounds = [&](int64_t tiles) { return (tiles + cus - 1) / cus; };
+  const int64_t big = rounds(s.E * ((mean + kBigTM - 1) / kBigTM) * ((s.up_rows() + kBigTN - 1) / kBigTN));
+  const int64_t wide = rounds(int64_t(s.E) * (s.up_rows() / kWideTN));
+  return big >= 2 && wide * (10000 + 22 * mean) < big * 12500;
+}
+
 // Weight-row counts of at least 512 take the large 128 x 256 tile (a
 // partial last N tile is masked) or the 256 x 256 one; smaller ones the 128 x
 // 128 / 128 x 64 tiles; the thin plan the 128 x 288 tile; the wide plan the
 // expert-wide 384 x 144 up-projection tile.
-FfnPlan ffn_plan(const Shape& s, int64_t rows, int64_t most, bool partials) {
+//
+// Full and threshold steps of few rows per expert stream the weights of the up
+// projection only where that takes fewer rounds over the CUs than 128 x 256
+// tiles (one per expert and column tile), and of the down projection only where
+// those would leave more than half of the CUs idle: elsewhere they read the
+// weights as fast, without the partial sums.  Threshold steps, default
+// settings, 128 x 256 against streaming, us: 16 experts of 1152 x 4608, 103
+// rows, up (288 tiles; 1 round of the latter) 55.8 and 35.1, down (80) 70 and
+// 42; of 2688 x 5184, 70 rows, up (336; 2 rounds) 105 and 109, down (176) 93 and
+// 114; 32 experts of 1920 x 4608, 76 rows, up (576; 2 rounds) 131 and 105, down
+// (256) 109 and 130; 8 experts of 1536 x 4608, 69 rows, up (144; 1 round) 25
+// and 33, down (48) 55 and 31.
+FfnPlan ffn_plan(const Shape& s, StepKind kind, int64_t rows, bool partials) {
   auto tn = [](int n) { return n >= 512 ? kBigTN : (n % 128 == 0 ? 128 : 64); };
   FfnPlan p;
   p.tm = p.tm_up = 128;
@@ -2062,10 +2092,17 @@ FfnPlan ffn_plan(const Shape& s, int64_t rows, int64_t most, bool partials) {
     p.split_down = f32_split(s);
     return p;
   }
+  const int cus = device_cus();
+  auto tiles = [&](int n, int cols) { return int64_t(s.E) * ((n + cols - 1) / cols); };
+  auto rounds = [&](int64_t t) { return (t + cus - 1) / cus; };
   const bool few = rows <= int64_t(kThinRows) * s.E &&
-                   (most == rows || most <= int64_t(kThinTM) * s.E) && thin_capable(s);
-  p.thin_up = few;
-  p.thin_down = few && partials;
+                   (kind != kThresholdStep || s.branches() <= int64_t(kThinTM) * s.E) &&
+                   thin_capable(s);
+  p.thin_up = few && (kind == kRatioStep || rounds(tiles(s.up_rows(), kThinTN)) <
+                                                rounds(tiles(s.up_rows(), kBigTN)));
+  p.thin_down = few && partials && (kind == kRatioStep || 2 * tiles(s.d, kBigTN) < cus);
+  const bool wide = rows <= int64_t(kWideRows) * s.E && wide_capable(s) &&
+                    (kind == kRatioStep || (kind == kFullStep && !few) || wide_pays(s, rows / s.E));
   p.tn_up = tn(s.up_rows());
   p.tn_down = tn(s.d);
   p.tall_up = tall_capable(s.tokens(), s.d, s.up_rows()) && tall_pays(s, rows, s.d, s.up_rows(), true);
@@ -2073,7 +2110,7 @@ FfnPlan ffn_plan(const Shape& s, int64_t rows, int64_t most, bool partials) {
   if (p.thin_up) {
     p.tall_up = false;
     p.tn_up = kThinTN;
-  } else if (rows <= int64_t(kWideRows) * s.E && wide_capable(s)) {
+  } else if (wide) {
     p.tall_up = false;
     p.wide_up = true;
     p.tm_up = kWideTM;

@@ -121,9 +121,10 @@ struct FfnPlan {
   bool tall_up = false, tall_down = false;  // the 256 x 256 tiles (tm chosen on the device)
 };
 constexpr int kThinSplit = 4;
-// A step takes the weight-streaming tiles for both projections when it is
-// expected to leave at most this many rows per expert on average (the
-// unmatched branches of a cache step come on top).  Measured (16 experts of
+// A ratio-mode cache step takes the weight-streaming tiles for both projections
+// when it is expected to leave at most this many rows per expert on average
+// (the unmatched branches come on top), other steps for each projection where
+// that also pays (ffn_plan).  Measured (16 experts of
 // 1152 x 4608): a full step with 32 rows per expert, up and down, 108 us with
 // the expert-wide and the 128 x 256 tiles, 63 us with these; with 256 rows 144
 // against 205 us (two 128-row tiles read each weight slice twice).  A
@@ -136,11 +137,10 @@ constexpr int kThinRows = 112;
 // against 92 us; a threshold-mode step with about 232, in the 128 x 256 tiles
 // before, the cycle of three 655 -> 591 us.
 constexpr int kWideRows = 320;
-// rows: branches the routed experts are expected to have in this step; most:
-// the most they may have where the host cannot know (threshold mode), else
-// rows; partials: the down projection may split K (its partial sums have a
-// place).
-FfnPlan ffn_plan(const Shape& s, int64_t rows, int64_t most, bool partials);
+enum StepKind { kFullStep, kThresholdStep, kRatioStep };
+// rows: branches the routed experts are expected to have in this step;
+// partials: the down projection may split K (its partial sums have a place).
+FfnPlan ffn_plan(const Shape& s, StepKind kind, int64_t rows, bool partials);
 // K pieces of an fp32 layer's down projection (1: not split).  Above 1 the
 // workspace holds `part`.
 int f32_split(const Shape& s);
@@ -166,7 +166,7 @@ hipError_t launch_decide(const Shape& s, int sel_mode, int budget, float lambda0
                          float lambda2, bool with_stat, float tau0, float alpha,
                          const FfnPlan& plan, const Buffers& b, hipStream_t st);
 // Whether the decide kernel also builds the lists (one sample, up to 2048
-// branches); otherwise launch_lists follows it.
+// branches and 32 experts); otherwise launch_lists follows it.
 bool decide_lists(const Shape& s);
 hipError_t launch_lists(const Shape& s, const FfnPlan& plan, const Buffers& b, hipStream_t st);
 // act: MOECA_ACT_* of the policy.  W_*_sh: the shared experts (S > 0).

@@ -336,7 +336,7 @@ int moeca_forward_noalloc(const moeca_layer* L, const void* x, int samples, void
   const Buffers b = map_buffers(static_cast<char*>(base), lay, nullptr);
   const moeca_policy& p = L->pol;
   const auto st = static_cast<hipStream_t>(stream);
-  moeca::FfnPlan plan = moeca::ffn_plan(s, s.branches(), s.branches(), b.part != nullptr);
+  moeca::FfnPlan plan = moeca::ffn_plan(s, moeca::kFullStep, s.branches(), b.part != nullptr);
   if (b.part == nullptr) plan.split_down = 1;
   // the uncached layer: every branch recomputed, no statistic, no cache
   // metadata and no attention path (the MOECA_MODE_FULL step)
@@ -448,25 +448,28 @@ int layer_step(moeca_layer* L, const void* x_t, const void* x_ffn, int t, void* 
   }
   // rows the routed experts are expected to have: every branch on full steps,
   // the budget in ratio mode.  A threshold step's count is not known to the
-  // host: five eighths of the branches, what the default settings recompute,
-  // and at most all of them.  Where that is far off the tiles are still no
-  // slower than the 128 x 256 ones: cycles of four steps with tau0 0.02
-  // (everything recomputed) and 8 (unmatched branches only), 16 experts of 1152
-  // x 4608, 256 x 4 tokens 622 and 410 us against 628 and 550, 700 x 2 tokens
-  // 582 and 490 against 655 and 553, 1024 x 4 tokens 1093 and 607 against 1151
-  // and 710.
-  const int64_t rows = full ? s.branches()
-                       : p.mode == MOECA_MODE_RATIO ? int64_t(budget) * s.B
-                                                    : s.branches() * 5 / 8;
-  const int64_t most = !full && p.mode == MOECA_MODE_THRESHOLD ? s.branches() : rows;
+  // host: five eighths of the branches, what the default settings recompute
+  // (measured, consecutive steps of a 250-step sampler: 36 to 77 % with 8 to 32
+  // experts).  Cycles of four steps with tau0 0.02 (everything recomputed) and 8
+  // (unmatched branches only), 16 experts of 1152 x 4608, 256 x 4 tokens 621 and
+  // 409 us against 623 and 547 in the 128 x 256 tiles, 700 x 2 tokens 583 and
+  // 489 against 650 and 551, 1024 x 4 tokens 1091 and 612 against 1167 and 714;
+  // up projections of 8 experts of 1536 x 4608, 300 rows, where next to nothing
+  // is recomputed, 29 us against 21.
+  const moeca::StepKind kind = full ? moeca::kFullStep
+                               : p.mode == MOECA_MODE_RATIO ? moeca::kRatioStep
+                                                            : moeca::kThresholdStep;
+  const int64_t rows = kind == moeca::kFullStep    ? s.branches()
+                       : kind == moeca::kRatioStep ? int64_t(budget) * s.B
+                                                   : s.branches() * 5 / 8;
   // A block of a stack splits K of its down projection in ratio-mode cache
   // steps only: its output goes on into every later block's router, where
   // another order of the sums moves tied branches, and full and threshold-mode
   // steps add K in one piece, as layers with more rows do.  (The up
   // projection's sums are the same in any tiling.)
   const bool pieces = b.part != nullptr &&
-                      !(L->mid_outside && (full || p.mode == MOECA_MODE_THRESHOLD));
-  const moeca::FfnPlan plan = moeca::ffn_plan(s, rows, most, pieces);
+                      !(L->mid_outside && kind != moeca::kRatioStep);
+  const moeca::FfnPlan plan = moeca::ffn_plan(s, kind, rows, pieces);
   arm();
   if (!check(moeca::launch_decide(s, sel, budget, p.lambda0, p.lambda1, p.lambda2, !uncached, p.tau0,
                                   p.alpha, plan, b, st),

@@ -51,33 +51,48 @@ def tall_pays(shape: LayerShape, rows: int, K: int, n: int, up: bool) -> bool:
     return 32 * tall < 31 * rounds(128) * kt * (320 if up else 255)
 
 
-def step_plan(shape: LayerShape, rows: int, one_piece=False, most=None):
+def step_plan(shape: LayerShape, rows: int, kind: str, one_piece=False):
     """Tilings of the up and the down projection that the library takes for a
-    step expected to leave `rows` routed branches: weight-streaming tiles up to
-    112 rows per expert, the expert-wide up projection up to 320, the 256 x 256
-    tiles where they pay, else the 128-row ones.  one_piece: the down
-    projection adds K in one piece (full steps of a stack's block); most: every
-    branch of a threshold step (one weight-streaming tile has to hold them)."""
+    "full", "threshold" or "ratio" step expected to leave `rows` routed
+    branches (256 CUs).  Up to 112 rows per expert: weight-streaming tiles, on
+    full and threshold steps where they pay (fewer rounds than 128 x 256 tiles
+    in the up projection, less than half of the CUs taken by those in the down
+    projection).  Up to 320: the expert-wide up projection, on threshold steps
+    (and full ones of the first kind) where its rounds cost less.  Else the 256 x
+    256 tiles where they pay, or the 128-row ones.  one_piece: the down
+    projection adds K in one piece (a stack's full and threshold steps)."""
     if shape.dtype != "bf16":
         return LARGE, LARGE
+    E, up_n = shape.E, shape.up_rows
+
+    def rounds(tiles):
+        return -(-tiles // 256)
+
     plain = shape.n_shared == 0 and shape.ffn == "gelu"
-    few = (plain and rows <= 112 * shape.E and shape.branches <= 256 * shape.E
-           and (most is None or most <= 128 * shape.E)
-           and 2 * shape.E * -(-shape.d_ff // 288) >= 256)
-    if few:
+    few = (plain and rows <= 112 * E and shape.branches <= 256 * E
+           and 2 * E * -(-shape.d_ff // 288) >= 256
+           and (kind != "threshold" or shape.branches <= 128 * E))
+    stream_up = few and (kind == "ratio"
+                         or rounds(E * -(-up_n // 288)) < rounds(E * -(-up_n // 256)))
+    stream_down = few and not one_piece and (kind == "ratio" or 2 * E * -(-shape.d // 256) < 256)
+    mean = rows // E
+    big = rounds(E * -(-mean // 128) * -(-up_n // 256))
+    wide_pays = big >= 2 and rounds(E * (up_n // 144)) * (10000 + 22 * mean) < big * 12500
+    if stream_up:
         up = STREAM
-    elif plain and rows <= 320 * shape.E and shape.d_ff % 144 == 0:
+    elif (plain and rows <= 320 * E and up_n % 144 == 0
+          and (kind == "ratio" or (kind == "full" and not few) or wide_pays)):
         up = WIDE
     else:
-        up = TALL if tall_pays(shape, rows, shape.d, shape.up_rows, True) else LARGE
-    if few and not one_piece:
+        up = TALL if tall_pays(shape, rows, shape.d, up_n, True) else LARGE
+    if stream_down:
         return up, STREAM
     return up, TALL if tall_pays(shape, rows, shape.d_ff, shape.d, False) else LARGE
 
 
 def full_step_plan(shape: LayerShape) -> int:
     """Tiling of the up projection on a full step of this layer."""
-    return step_plan(shape, shape.branches)[0]
+    return step_plan(shape, shape.branches, "full")[0]
 
 
 class Setup:

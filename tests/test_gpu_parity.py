@@ -150,10 +150,10 @@ def test_tall_tile_edges(E, N, B, k, d, d_ff, ffn, n_shared, up, down):
     tiles ran."""
     shape = LayerShape(d=d, E=E, k=k, d_ff=d_ff, B=B, N=N, dtype="bf16", ffn=ffn,
                        n_shared=n_shared)
-    assert step_plan(shape, shape.branches) == (up, down)
+    assert step_plan(shape, shape.branches, "full") == (up, down)
     S = Setup(shape, mode="ratio", seed=22, T=2, ratio=0.9)
     infos = run_forced(S, 2, label=f"tall {E} {N} {B} {d} {d_ff} {ffn} {n_shared}")
-    cache = step_plan(shape, B * int(S.pol.ratio * N * k + 0.5))
+    cache = step_plan(shape, B * int(S.pol.ratio * N * k + 0.5), "ratio")
     assert [(i["ffn_plan"], i["ffn_plan_down"]) for i in infos] == [(up, down), cache]
 
 
@@ -404,28 +404,31 @@ THIN_SHAPES = [
 def test_thin_plan_trajectory(shape, ratio):
     S = Setup(shape, mode="ratio", seed=31, T=4, ratio=ratio, refresh_cycle=0)
     infos = run_forced(S, 4, label=f"thin {shape}")
-    first = step_plan(shape, shape.branches)
+    first = step_plan(shape, shape.branches, "full")
     assert [(i["ffn_plan"], i["ffn_plan_down"]) for i in infos] == [first] + 3 * [(1, 1)]
-    # 32 and 25 rows per expert on a full step: it streams its weights too
-    assert first == ((1, 1) if shape.branches <= 112 * shape.E else (2, 0))
 
 
-@pytest.mark.parametrize("shape,plan,tau0", [
-    (THIN_SHAPES[0][0], 1, 0.8),
-    (LayerShape(d=576, E=8, k=2, d_ff=4608, B=4, N=128, dtype="bf16"), 1, 0.02),
-    (LayerShape(d=576, E=8, k=2, d_ff=4608, B=3, N=230, dtype="bf16"), 2, 0.02),
-    (LayerShape(d=576, E=8, k=2, d_ff=1152, B=4, N=512, dtype="bf16"), 2, 0.8),
+@pytest.mark.parametrize("shape,full,cache,tau0", [
+    # 16 rows per expert, 10 expected: 256 streaming tiles where 128 x 256 ones take two rounds
+    (LayerShape(d=576, E=64, k=2, d_ff=1152, B=4, N=128, dtype="bf16"), (1, 0), (1, 0), 0.8),
+    # 32 and 20: one round of either; 48 of 128 x 256 tiles in the down projection
+    (THIN_SHAPES[0][0], (0, 1), (0, 1), 0.8),
+    # 112 (the most) and 70; 130 and 81, which might be two streaming tiles
+    (LayerShape(d=192, E=16, k=2, d_ff=4608, B=4, N=224, dtype="bf16"), (1, 1), (1, 1), 0.02),
+    (LayerShape(d=192, E=16, k=2, d_ff=4608, B=4, N=260, dtype="bf16"), (2, 0), (2, 0), 0.02),
+    # 172 and 107: one round of 128 x 256 tiles is not beaten
+    (LayerShape(d=576, E=8, k=2, d_ff=4608, B=3, N=230, dtype="bf16"), (2, 0), (0, 0), 0.02),
+    # 512 and 320, the most that take the expert-wide tiles
+    (LayerShape(d=576, E=16, k=2, d_ff=2304, B=4, N=1024, dtype="bf16"), (0, 0), (2, 0), 0.8),
 ])
-def test_threshold_mode_plans(shape, plan, tau0):
-    """Threshold-mode cache steps choose their tiles by an expected row count
-    and the largest: 20 rows per expert of 32 and 80 of 128 (weight-streaming
-    tiles), 107 of 172, which would be two such tiles if everything is
-    recomputed, as it is with tau0 0.02, and 320, the most that take the
-    expert-wide up projection."""
+def test_threshold_mode_plans(shape, full, cache, tau0):
+    """Full and threshold steps choose their tiles by the rows expected and the
+    rounds of tiles; with tau0 0.02 everything is recomputed."""
+    assert step_plan(shape, shape.branches, "full") == full
+    assert step_plan(shape, shape.branches * 5 // 8, "threshold") == cache
     S = Setup(shape, mode="threshold", seed=32, T=3, refresh_cycle=0, tau0=tau0)
     infos = run_forced(S, 3, label=f"threshold {shape}")
-    assert [i["ffn_plan"] for i in infos] == [full_step_plan(S.shape), plan, plan]
-    assert step_plan(shape, shape.branches * 5 // 8, most=shape.branches)[0] == plan
+    assert [(i["ffn_plan"], i["ffn_plan_down"]) for i in infos] == [full, cache, cache]
 
 
 @pytest.mark.parametrize("shape", [

@@ -304,10 +304,10 @@ def test_stack_projection_tiles_forced(d, heads, B, N, q, kv):
 
 @pytest.mark.parametrize("mode,down", [("threshold", 0), ("ratio", 1)])
 def test_stack_down_projection_pieces(mode, down):
-    """Blocks with few rows per expert (16 on a full step) stream their
+    """Blocks with few rows per expert (4 on a full step) stream their
     weights; K of the down projection is split in ratio-mode cache steps only,
-    and added in one piece (the 128 x 256 tiles) in full and threshold steps."""
-    sh = StackShape(L=1, d=576, heads=8, E=16, k=2, d_ff=2304, B=1, N=128)
+    and added in one piece (the 128-row tiles) in full and threshold steps."""
+    sh = StackShape(L=1, d=256, heads=4, E=64, k=2, d_ff=1152, B=1, N=128)
     say(f"down projection pieces {mode}")
     SS = StackSetup(sh, mode=mode, seed=5, T=2, refresh_cycle=0)
     st, plans = D.BlockState(SS.dims), []
