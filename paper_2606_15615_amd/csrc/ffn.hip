@@ -1960,9 +1960,12 @@ hipError_t launch_gemm(const Shape& s, const FfnPlan& plan, const void* A, const
     auto* osh = static_cast<uint16_t*>(dst_sh);
     const bool tall = KIND == kUp ? plan.tall_up : plan.tall_down;
     if (tall) {
-      launch_kernel(&gemm_bf16_tall_kernel<KIND, ACT>, dim3(device_cus()), dim3(kTallThreads), 0,
-          st, a, w, wsh, b.off, toff, b.list, b.row_dst, s.E, G, s.k, K, Nout,
-          b.tiles + 2 * (G + 1) + (KIND == kUp ? 0 : 1), static_cast<const float*>(nullptr), o, osh);
+      if constexpr (ACT == kActGeluErf) return hipErrorInvalidValue;  // never planned
+      else
+        launch_kernel(&gemm_bf16_tall_kernel<KIND, ACT>, dim3(device_cus()), dim3(kTallThreads), 0,
+            st, a, w, wsh, b.off, toff, b.list, b.row_dst, s.E, G, s.k, K, Nout,
+            b.tiles + 2 * (G + 1) + (KIND == kUp ? 0 : 1), static_cast<const float*>(nullptr), o,
+            osh);
     } else if (tn == kBigTN) {
       launch_kernel(&gemm_bf16_big_kernel<KIND, ACT>, dim3(device_cus()), dim3(kBigThreads), 0, st,
           a, w, wsh, b.off, toff, b.list, b.row_dst, s.E, G, s.k, K, Nout,
@@ -2028,10 +2031,13 @@ static bool tall_capable(int64_t rows, int K, int Nout) {
 // it, 410 and 512 rows: 123.7 and 129.6 against 89.6 and 88.1.  The up
 // projection, 359, 410, 512 and 614 rows: 88.6, 101.5, 117.9 and 130.0 us
 // against 95.9, 107.3, 109.7 and 138.9.  Below 144 rows (down) and 200 (up) the
-// times no longer follow the rounds.
+// times no longer follow the rounds.  The erf GELU's two ranges of erff make the
+// larger tile's epilogue, which no other block covers, too long: of the same
+// up projections 307, 563 and 1024 rows 130, 178 and 286 us against 101, 154 and
+// 258 (only K = 2048 gained, by 4 and 8 % past 430 rows).
 static bool tall_pays(const Shape& s, int64_t rows, int K, int n, bool up) {
   const int64_t mean = rows / s.E;
-  if (mean < (up ? 200 : 144)) return false;
+  if (mean < (up ? 200 : 144) || (up && s.erf)) return false;
   const int nt = (n + kTallTN - 1) / kTallTN, kt = K / kTK;
   const int cus = device_cus();
   auto rounds = [&](int tm) {

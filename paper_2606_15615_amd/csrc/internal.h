@@ -57,6 +57,7 @@ struct Shape {
   bool bf16;
   int S = 0;            // shared experts
   bool swiglu = false;  // gated experts: 2 d_ff up-projection rows
+  bool erf = false;     // erf GELU
   int64_t tokens() const { return int64_t(B) * N; }
   int64_t branches() const { return int64_t(B) * N * k; }
   size_t act_bytes() const { return bf16 ? 2 : 4; }

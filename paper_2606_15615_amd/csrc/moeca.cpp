@@ -237,6 +237,7 @@ moeca_layer* moeca_layer_create(int d, int E, int k, int d_ff, const moeca_polic
   L->shape = Shape{d, E, k, d_ff, p->batch, p->tokens, p->dtype == MOECA_DTYPE_BF16};
   L->shape.S = p->n_shared;
   L->shape.swiglu = p->act == MOECA_ACT_SWIGLU;
+  L->shape.erf = p->act == MOECA_ACT_GELU_ERF;
   L->pol = *p;
   L->layout = make_layout(L->shape);
   return L;

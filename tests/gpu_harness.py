@@ -32,13 +32,13 @@ def say(msg):
 LARGE, STREAM, WIDE, TALL = 0, 1, 2, 3
 
 
-def tall_pays(shape: LayerShape, rows: int, K: int, n: int, up: bool) -> bool:
+def tall_pays(shape: LayerShape, rows: int, K: int, n: int, up: bool, act: str) -> bool:
     """Whether a projection takes the 256 x 256 tiles rather than the 128 x 256
     ones: rounds of tiles over 256 CUs times the cost of a tile (per k-tile 255,
     up 320, against 160 + its rows, with a tail of 12 per row, gated 6, in an
-    up projection)."""
+    up projection); no up projection with the erf GELU."""
     mean, kt = rows // shape.E, K // 64
-    if K < 256 or n < 512 or mean < (200 if up else 144):
+    if K < 256 or n < 512 or mean < (200 if up else 144) or (up and act == "gelu_erf"):
         return False
     most = mean + -(-mean // 32)
 
@@ -51,7 +51,7 @@ def tall_pays(shape: LayerShape, rows: int, K: int, n: int, up: bool) -> bool:
     return 32 * tall < 31 * rounds(128) * kt * (320 if up else 255)
 
 
-def step_plan(shape: LayerShape, rows: int, kind: str, one_piece=False):
+def step_plan(shape: LayerShape, rows: int, kind: str, one_piece=False, act="gelu_tanh"):
     """Tilings of the up and the down projection that the library takes for a
     "full", "threshold" or "ratio" step expected to leave `rows` routed
     branches (256 CUs).  Up to 112 rows per expert: weight-streaming tiles, on
@@ -84,10 +84,10 @@ def step_plan(shape: LayerShape, rows: int, kind: str, one_piece=False):
           and (kind == "ratio" or (kind == "full" and not few) or wide_pays)):
         up = WIDE
     else:
-        up = TALL if tall_pays(shape, rows, shape.d, up_n, True) else LARGE
+        up = TALL if tall_pays(shape, rows, shape.d, up_n, True, act) else LARGE
     if stream_down:
         return up, STREAM
-    return up, TALL if tall_pays(shape, rows, shape.d_ff, shape.d, False) else LARGE
+    return up, TALL if tall_pays(shape, rows, shape.d_ff, shape.d, False, act) else LARGE
 
 
 def full_step_plan(shape: LayerShape) -> int:

@@ -157,6 +157,17 @@ def test_tall_tile_edges(E, N, B, k, d, d_ff, ffn, n_shared, up, down):
     assert [(i["ffn_plan"], i["ffn_plan_down"]) for i in infos] == [(up, down), cache]
 
 
+def test_erf_gelu_keeps_the_128_row_tiles():
+    """An up projection of the erf GELU does not take the 256 x 256 tiles where
+    the tanh one does; the down projection does."""
+    shape = LayerShape(d=640, E=3, k=1, d_ff=704, B=2, N=1865, dtype="bf16", n_shared=2)
+    for act, plan in (("gelu_tanh", (3, 3)), ("gelu_erf", (0, 3))):
+        assert step_plan(shape, shape.branches, "full", act=act) == plan
+        S = Setup(shape, mode="full", seed=24, T=1, act=act)
+        (info,) = run_forced(S, 1, label=f"tall {act}")
+        assert (info["ffn_plan"], info["ffn_plan_down"]) == plan
+
+
 WIDE = LayerShape(d=128, E=16, k=8, d_ff=128, B=2, N=1100, dtype="bf16")
 
 
