@@ -2017,32 +2017,32 @@ static bool tall_capable(int64_t rows, int K, int Nout) {
 // ones when the routed experts are expected to have `rows` branches in all.
 //
 // Both run in rounds of one tile per CU.  Per k-tile of 64 a round costs, in
-// the units of tall_cost, 255 in the 128 x 256 tiles and 160 + tm in tiles of
-// tm rows; an up projection 320, and 12 tm (gated 6 tm, with half the stores)
+// the units of tall_cost, 270 in the 128 x 256 tiles and 160 + tm in tiles of
+// tm rows; an up projection 340, and 12 tm (gated 6 tm, with half the stores)
 // per tile for the activation and the stores, which the larger tile has in one
-// piece after its k-loop.  An expert's rows are taken a 32nd above the mean, so
-// that a mean of just whole tiles counts as more than that, and the larger
-// tiles have to win by a 32nd.  Fitted to both kernels' times on 13 layers
-// (width 512 to 2048, 8 to 32 experts, 77 to 2048 rows per expert) and checked
-// on 13 others (704 to 3072, 8 to 64 experts): of 466 pairs none where the
-// larger tiles are chosen is more than 2 % slower.  The down projection of 16
-// experts of 1152 x 4608 in one round of 128 x 256 tiles, 307 and 358 rows per
+// piece after its k-loop.  The experts' rows are taken 1/56 and 3/56 below and
+// above the mean, a quarter of them each.  Fitted to both kernels' times on 26
+// layers (width 512 to 3072, 8 to 64 experts, 75 to 2048 rows per expert): of 466
+// pairs the larger tiles are chosen wrongly, by more than 2 %, in two (5 and 7 %,
+// up projections of 24 experts of 960 x 1216 and 8 of 512 x 2048, some 700 rows).
+// The down projection of 16 experts of 1152 x 4608, 307 and 358 rows per
 // expert: 72.0 and 73.2 us against 74.7 and 76.1 (one round of either); past
 // it, 410 and 512 rows: 123.7 and 129.6 against 89.6 and 88.1.  The up
 // projection, 359, 410, 512 and 614 rows: 88.6, 101.5, 117.9 and 130.0 us
-// against 95.9, 107.3, 109.7 and 138.9.  Below 144 rows (down) and 200 (up) the
+// against 95.9, 107.3, 109.7 and 138.9.  Below 144 rows (down) and 160 (up) the
 // times no longer follow the rounds.  The erf GELU's two ranges of erff make the
 // larger tile's epilogue, which no other block covers, too long: of the same
 // up projections 307, 563 and 1024 rows 130, 178 and 286 us against 101, 154 and
 // 258 (only K = 2048 gained, by 4 and 8 % past 430 rows).
 static bool tall_pays(const Shape& s, int64_t rows, int K, int n, bool up) {
   const int64_t mean = rows / s.E;
-  if (mean < (up ? 200 : 144) || (up && s.erf)) return false;
+  if (mean < (up ? 160 : 144) || (up && s.erf)) return false;
   const int nt = (n + kTallTN - 1) / kTallTN, kt = K / kTK;
   const int cus = device_cus();
   auto rounds = [&](int tm) {
-    const int64_t most = mean + (mean + 31) / 32;
-    const int64_t mt = s.E * ((most + tm - 1) / tm) + s.S * ((s.tokens() + tm - 1) / tm);
+    int64_t mt = 0;  // of the routed experts, times four
+    for (int i = -3; i <= 3; i += 2) mt += s.E * ((mean + mean * i / 56 + tm - 1) / tm);
+    mt = (mt + 3) / 4 + s.S * ((s.tokens() + tm - 1) / tm);
     return (mt * nt + cus - 1) / cus;
   };
   const int64_t tail = up ? (s.swiglu ? 6 : 12) : 0;
@@ -2051,7 +2051,7 @@ static bool tall_pays(const Shape& s, int64_t rows, int K, int n, bool up) {
     const int64_t c = rounds(tm) * (kt * tall_cost(tm) + tail * tm);
     if (tall < 0 || c < tall) tall = c;
   }
-  return 32 * tall < 31 * rounds(128) * kt * (up ? 320 : 255);
+  return tall < rounds(128) * kt * (up ? 340 : 270);
 }
 
 // Whether a threshold step, or a full one that might have streamed its weights,

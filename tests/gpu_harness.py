@@ -34,21 +34,23 @@ LARGE, STREAM, WIDE, TALL = 0, 1, 2, 3
 
 def tall_pays(shape: LayerShape, rows: int, K: int, n: int, up: bool, act: str) -> bool:
     """Whether a projection takes the 256 x 256 tiles rather than the 128 x 256
-    ones: rounds of tiles over 256 CUs times the cost of a tile (per k-tile 255,
-    up 320, against 160 + its rows, with a tail of 12 per row, gated 6, in an
+    ones: rounds of tiles over 256 CUs times the cost of a tile (per k-tile 270,
+    up 340, against 160 + its rows, with a tail of 12 per row, gated 6, in an
     up projection); no up projection with the erf GELU."""
     mean, kt = rows // shape.E, K // 64
-    if K < 256 or n < 512 or mean < (200 if up else 144) or (up and act == "gelu_erf"):
+    if K < 256 or n < 512 or mean < (160 if up else 144) or (up and act == "gelu_erf"):
         return False
-    most = mean + -(-mean // 32)
 
     def rounds(tm):
-        mt = shape.E * -(-most // tm) + shape.n_shared * -(-shape.tokens // tm)
+        # a quarter of the experts each 1/56 and 3/56 below and above the mean
+        around = [mean + int(mean * i / 56) for i in (-3, -1, 1, 3)]
+        mt = -(-shape.E * sum(-(-r // tm) for r in around) // 4)
+        mt += shape.n_shared * -(-shape.tokens // tm)
         return -(-mt * -(-n // 256) // 256)
 
     tail = (6 if shape.ffn == "swiglu" else 12) if up else 0
     tall = min(rounds(tm) * (kt * (160 + tm) + tail * tm) for tm in (128, 192, 256))
-    return 32 * tall < 31 * rounds(128) * kt * (320 if up else 255)
+    return tall < rounds(128) * kt * (340 if up else 270)
 
 
 def step_plan(shape: LayerShape, rows: int, kind: str, one_piece=False, act="gelu_tanh"):

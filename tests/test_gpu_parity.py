@@ -132,14 +132,14 @@ def test_erf_gelu_values():
     (3, 2067, 1, 1, 1152, 256, "gelu", 2, 0, 3),   # 689; down 4 (the fewest), 128, 192
     (8, 646, 2, 1, 1600, 320, "gelu", 2, 0, 3),    # 161; down 5, 64, 192
     (8, 2162, 1, 1, 1728, 320, "gelu", 2, 0, 3),   # 270; down 5, 192, 256
-    (8, 1360, 3, 1, 1792, 256, "gelu", 0, 0, 3),   # 510; down 4, 0, 128
+    (4, 1342, 3, 1, 2048, 256, "gelu", 0, 0, 3),   # 1006; down 4, 0, 128
     (2, 1413, 2, 1, 576, 832, "gelu", 2, 3, 0),    # 1413; up 9, 64, 192
     (1, 320, 2, 1, 576, 2112, "swiglu", 2, 3, 0),  # 640; up 9, 128, 128
     (8, 1943, 1, 1, 576, 832, "swiglu", 2, 3, 0),  # 242; up 9, 128, 256
     (3, 1865, 2, 1, 640, 704, "gelu", 2, 3, 3),    # 1243; up 10, 192, 192; down 11, 128, 192
     (8, 2032, 1, 1, 768, 1088, "gelu", 2, 3, 0),   # 254; up 12, 64, 128
     (8, 1051, 2, 1, 512, 1536, "swiglu", 0, 3, 0), # 262; up 8, 0, 192
-    (2, 1159, 3, 1, 960, 704, "gelu", 2, 3, 3),    # 1738; up 15, 192, 128; down 11, 192, 192
+    (2, 1159, 3, 1, 960, 704, "gelu", 2, 0, 3),    # 1738; down 11, 192, 192
     (6, 700, 3, 2, 1216, 2432, "gelu", 0, 3, 0),   # 700; up 19, 128, 192; two branches a token
 ])
 def test_tall_tile_edges(E, N, B, k, d, d_ff, ffn, n_shared, up, down):
