@@ -109,8 +109,8 @@ struct Buffers {
 // the up and down projections, and the number of K pieces of the down
 // projection.  The lists kernel turns the per-expert row counts into tile
 // (unit) prefixes with the same plan.  thin: the weight-streaming kernel
-// (128 x 288 tiles) for both projections, the down projection in
-// kThinSplit K pieces whose fp32 partial sums are added in piece order.
+// (128 x 288 tiles), a down projection in kThinSplit K pieces whose fp32
+// partial sums are added in piece order.
 struct FfnPlan {
   int tm;
   int tn_up;
@@ -134,7 +134,8 @@ constexpr int kThinSplit = 4;
 constexpr int kThinRows = 112;
 // A step with more rows per expert than that, and at most this many on
 // average, takes the expert-wide up-projection tiles (all of an expert's
-// rows, up to 384, by 144 columns).  Measured (same experts): 307 rows 75
+// rows, up to 384, by 144 columns), a threshold step where they pay
+// (ffn_plan).  Measured (same experts): 307 rows 75
 // against 92 us; a threshold-mode step with about 232, in the 128 x 256 tiles
 // before, the cycle of three 655 -> 591 us.
 constexpr int kWideRows = 320;
