@@ -201,19 +201,21 @@ __global__ __launch_bounds__(kGemvWaves * kWave) void gemv_kernel(
 // LayerNorm + AdaLN modulation and the gated residuals
 // ---------------------------------------------------------------------------
 // W waves take a row: thread l holds the float4 chunks l + 64 W j (j < NC), NC =
-// ceil(d / (256 W)), and the AdaLN vectors are requested together with the row.
-// With few rows a launch lasts as long as one row's chain of fp64 sums,
-// conversions and waits on memory, which more waves shorten; with many it is
-// bound by HBM, and waves that hold little of a row, or none of it, only cost
-// (four per row, 16384 rows: 128 wide 31 us against 14 with one, 384 wide 41
-// against 25).  Cycles of four steps of two blocks with one, two and four
-// waves per row, us:
-//   width   256 tokens             2048 tokens            16384 tokens
-//    256    750   756   755         848   851   867       1482  1534  1665
-//    384    809   789   792         907   903   913       1927  1949  2067
-//    576    867   852   833        1001   996  1001       2521  2560  2598
-//    768    916   899   884        1083  1078  1080       2937  2978  3005
-//   1152   1048  1015  1001        1372  1351  1364       4424  4273  4425
+// ceil(d / (256 W)).  With few rows a launch lasts as long as one row's chain of
+// fp64 sums, conversions and waits on memory, which more waves shorten, and
+// with four the AdaLN vectors are requested together with the row; with many
+// rows it is bound by HBM, and waves that hold little of a row, or none of it,
+// only cost (four per row, 16384 rows: 128 wide 31 us against 14 with one, 384
+// wide 41 against 25), as do the registers of vectors requested early.  Cycles
+// of four steps of two blocks with one, two and four waves per row, us (two
+// waves with the vectors requested early: 2536 at 1152 wide, 8192 tokens):
+//   width   1024 tokens            2048 tokens            8192 tokens
+//    256     801   810   824         829   840   860       1116  1149  1216
+//    384     873   857   873         908   899   913       1320  1331  1405
+//    576     950   937   929        1014  1002  1000       1531  1544  1589
+//    768    1002   987   981        1083  1069  1076       1780  1797  1827
+//   1152    1178  1136  1124        1381  1343  1362       2506  2489  2575
+//   1536    1372  1311  1306        1633  1583  1594       3098  3071  3138
 constexpr int kLnWaves = 4;
 
 enum { kLnAttn = 0, kLnMlp = 1, kLnFinal = 2 };
@@ -270,19 +272,31 @@ __device__ __forceinline__ void ln_stats(const float (&v)[NC][4], int n4, int la
   rstd = 1.0 / sqrt(var + 1e-6);
 }
 
+// A thread's chunks of one of the sample's AdaLN vectors: PRE: in registers,
+// requested early; else read where they are used.
+template <int NC, bool PRE>
+struct AdaVec {
+  const float4* p;
+  float4 r[PRE ? NC : 1];
+  __device__ __forceinline__ float4 at(int j, int c) const {
+    if constexpr (PRE) return r[j];
+    else return p[c];
+  }
+};
+
 // bf16(LN(v) * (1 + scale) + shift) into row `dst` in fp32: the attention
 // input (off the decision path)
-template <int NC, int W>
+template <int NC, int W, typename V>
 __device__ __forceinline__ void ln_store_f32(const float (&v)[NC][4], int n4, int lane,
-                                             double mean, double rstd, const float4 (&shift)[NC],
-                                             const float4 (&scale)[NC], uint16_t* dst) {
+                                             double mean, double rstd, const V& shift,
+                                             const V& scale, uint16_t* dst) {
   const float mf = static_cast<float>(mean), rf = static_cast<float>(rstd);
 #pragma unroll
   for (int j = 0; j < NC; ++j) {
     const int c = lane + W * kWave * j;
     if (c < n4) {
-      const float4 sh = shift[j];
-      const float4 sc = scale[j];
+      const float4 sh = shift.at(j, c);
+      const float4 sc = scale.at(j, c);
       const float z0 = fmaf((v[j][0] - mf) * rf, 1.0f + sc.x, sh.x);
       const float z1 = fmaf((v[j][1] - mf) * rf, 1.0f + sc.y, sh.y);
       const float z2 = fmaf((v[j][2] - mf) * rf, 1.0f + sc.z, sh.z);
@@ -294,16 +308,16 @@ __device__ __forceinline__ void ln_store_f32(const float (&v)[NC][4], int n4, in
 
 // bf16(LN(v) * (1 + scale) + shift) into row `dst`, in fp64 and rounded
 // once: this is the MoE routing input (decision-path arithmetic)
-template <int NC, int W>
+template <int NC, int W, typename V>
 __device__ __forceinline__ void ln_store(const float (&v)[NC][4], int n4, int lane,
-                                         double mean, double rstd, const float4 (&shift)[NC],
-                                         const float4 (&scale)[NC], uint16_t* dst) {
+                                         double mean, double rstd, const V& shift,
+                                         const V& scale, uint16_t* dst) {
 #pragma unroll
   for (int j = 0; j < NC; ++j) {
     const int c = lane + W * kWave * j;
     if (c < n4) {
-      const float4 sh = shift[j];
-      const float4 sc = scale[j];
+      const float4 sh = shift.at(j, c);
+      const float4 sc = scale.at(j, c);
       const float s4[4] = {sc.x, sc.y, sc.z, sc.w};
       const float h4[4] = {sh.x, sh.y, sh.z, sh.w};
       uint32_t z[4];
@@ -336,15 +350,19 @@ __global__ __launch_bounds__(W == 1 ? kLnWaves * kWave : W * kWave) void ln_kern
   const int64_t o = int64_t(row) * d;
   const float* m = p.mod + int64_t(b) * 6 * d;  // sh_a, sc_a, g_a, sh_m, sc_m, g_m
   float v[NC][4];
-  // the sample's AdaLN vectors, requested with the row
-  auto fetch = [&](float4 (&x)[NC], const float* q) __attribute__((always_inline)) {
+  // the sample's AdaLN vectors
+  constexpr bool kPre = W == 4;
+  auto fetch = [&](AdaVec<NC, kPre>& x, const float* q) __attribute__((always_inline)) {
+    x.p = reinterpret_cast<const float4*>(q);
+    if constexpr (kPre) {
 #pragma unroll
-    for (int j = 0; j < NC; ++j) {
-      const int c = lane + W * kWave * j;
-      if (c < n4) x[j] = reinterpret_cast<const float4*>(q)[c];
+      for (int j = 0; j < NC; ++j) {
+        const int c = lane + W * kWave * j;
+        if (c < n4) x.r[j] = x.p[c];
+      }
     }
   };
-  float4 sh_a[NC], sc_a[NC], g_a[NC], sh_m[NC], sc_m[NC];
+  AdaVec<NC, kPre> sh_a, sc_a, g_a, sh_m, sc_m;
   if constexpr (MODE != kLnFinal) {
     if (MODE == kLnAttn) {
       fetch(sh_a, m);
@@ -433,7 +451,7 @@ __global__ __launch_bounds__(W == 1 ? kLnWaves * kWave : W * kWave) void ln_kern
     const int c = lane + W * kWave * j;
     if (c < n4) {
       const u32x2_t aa = av[j];
-      const float4 gg = g_a[j];
+      const float4 gg = g_a.at(j, c);
       v[j][0] = gated_add(v[j][0], gg.x, __uint_as_float(aa[0] << 16));
       v[j][1] = gated_add(v[j][1], gg.y, __uint_as_float(aa[0] & 0xffff0000u));
       v[j][2] = gated_add(v[j][2], gg.z, __uint_as_float(aa[1] << 16));
