@@ -1078,6 +1078,7 @@ constexpr int kThinStage = kThinTileA + kThinTileB;  // 52 KB
 constexpr int kThinLoadsA = kThinTM / 8 / kThinWaves;                     // 2 per wave
 constexpr int kThinInstB = kThinTN / 8;                                   // 36
 constexpr int kThinLoadsB = (kThinInstB + kThinWaves - 1) / kThinWaves;   // 5 (waves 0-3), 4
+constexpr int kThinLongK = 3200;  // see ffn_plan
 static_assert(kThinInstB % kThinWaves == kThinWaves / 2, "waves 0-3 issue one more weight load");
 
 template <int KIND, int ACT, int SPLIT>
@@ -2079,15 +2080,18 @@ static bool wide_pays(const Shape& s, int64_t mean) {
 //
 // Full and threshold steps of few rows per expert stream the weights of the up
 // projection only where that takes fewer rounds over the CUs than 128 x 256
-// tiles (one per expert and column tile), and of the down projection only where
-// those would leave more than half of the CUs idle: elsewhere they read the
-// weights as fast, without the partial sums.  Threshold steps, default
-// settings, 128 x 256 against streaming, us: 16 experts of 1152 x 4608, 103
-// rows, up (288 tiles; 1 round of the latter) 55.8 and 35.1, down (80) 70 and
-// 42; of 2688 x 5184, 70 rows, up (336; 2 rounds) 105 and 109, down (176) 93 and
-// 114; 32 experts of 1920 x 4608, 76 rows, up (576; 2 rounds) 131 and 105, down
-// (256) 109 and 130; 8 experts of 1536 x 4608, 69 rows, up (144; 1 round) 25
-// and 33, down (48) 55 and 31.
+// tiles (one per expert and column tile), and of the down projection where the
+// rounds of K quarters take at most a quarter of the K of those tiles' rounds,
+// or half of it with a long K, over which the partial sums count little:
+// elsewhere 128 x 256 tiles read the weights as fast.  128 x 256 against
+// streaming, us; up: 16 experts of 1152 x 4608 (2 rounds against 1), 103 rows,
+// 55.8 and 35.1; of 2688 x 5184 (2, 2), 70 rows, 105 and 109; 32 of 1920 x 4608
+// (3, 2), 76 rows, 131 and 105; 8 of 1536 x 4608 (1, 1), 69 rows, 25 and 33.
+// Down, full K against quarters: 16 experts of 1152 x 4608 (1 round against 1
+// quarter) 70 and 42; 28 of 1152 x 3456 (1, 2), 86 rows, 64 and 57; 32 of 2304 x
+// 7872 (2, 4), 88 rows, 291 and 252; 24 of 1408 x 2880 (1, 2), 83 rows, 39 and
+// 50; 16 of 2688 x 5184 (1, 3), 70 rows, 93 and 114; 32 of 1920 x 4608 (1, 4),
+// 76 rows, 109 and 130.
 FfnPlan ffn_plan(const Shape& s, StepKind kind, int64_t rows, bool partials) {
   auto tn = [](int n) { return n >= 512 ? kBigTN : (n % 128 == 0 ? 128 : 64); };
   FfnPlan p;
@@ -2106,7 +2110,9 @@ FfnPlan ffn_plan(const Shape& s, StepKind kind, int64_t rows, bool partials) {
                    thin_capable(s);
   p.thin_up = few && (kind == kRatioStep || rounds(tiles(s.up_rows(), kThinTN)) <
                                                 rounds(tiles(s.up_rows(), kBigTN)));
-  p.thin_down = few && partials && (kind == kRatioStep || 2 * tiles(s.d, kBigTN) < cus);
+  const int64_t quarters = rounds(tiles(s.d, kThinTN) * kThinSplit), whole = rounds(tiles(s.d, kBigTN));
+  p.thin_down = few && partials && (kind == kRatioStep || quarters <= whole ||
+                                    (quarters <= 2 * whole && s.d_ff >= kThinLongK));
   const bool wide = rows <= int64_t(kWideRows) * s.E && wide_capable(s) &&
                     (kind == kRatioStep || (kind == kFullStep && !few) || wide_pays(s, rows / s.E));
   p.tn_up = tn(s.up_rows());

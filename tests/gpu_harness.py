@@ -58,8 +58,8 @@ def step_plan(shape: LayerShape, rows: int, kind: str, one_piece=False, act="gel
     "full", "threshold" or "ratio" step expected to leave `rows` routed
     branches (256 CUs).  Up to 112 rows per expert: weight-streaming tiles, on
     full and threshold steps where they pay (fewer rounds than 128 x 256 tiles
-    in the up projection, less than half of the CUs taken by those in the down
-    projection).  Up to 320: the expert-wide up projection, on threshold steps
+    in the up projection; in the down projection at most a quarter of the K of
+    their rounds in rounds of K quarters, or half of it with a long K).  Up to 320: the expert-wide up projection, on threshold steps
     (and full ones of the first kind) where its rounds cost less.  Else the 256 x
     256 tiles where they pay, or the 128-row ones.  one_piece: the down
     projection adds K in one piece (a stack's full and threshold steps)."""
@@ -76,7 +76,9 @@ def step_plan(shape: LayerShape, rows: int, kind: str, one_piece=False, act="gel
            and (kind != "threshold" or shape.branches <= 128 * E))
     stream_up = few and (kind == "ratio"
                          or rounds(E * -(-up_n // 288)) < rounds(E * -(-up_n // 256)))
-    stream_down = few and not one_piece and (kind == "ratio" or 2 * E * -(-shape.d // 256) < 256)
+    quarters, whole = rounds(4 * E * -(-shape.d // 288)), rounds(E * -(-shape.d // 256))
+    stream_down = few and not one_piece and (
+        kind == "ratio" or quarters <= whole or (quarters <= 2 * whole and shape.d_ff >= 3200))
     mean = rows // E
     big = rounds(E * -(-mean // 128) * -(-up_n // 256))
     wide_pays = big >= 2 and rounds(E * (up_n // 144)) * (10000 + 22 * mean) < big * 12500

@@ -422,11 +422,14 @@ def test_thin_plan_trajectory(shape, ratio):
 @pytest.mark.parametrize("shape,full,cache,tau0", [
     # 16 rows per expert, 10 expected: 256 streaming tiles where 128 x 256 ones take two rounds
     (LayerShape(d=576, E=64, k=2, d_ff=1152, B=4, N=128, dtype="bf16"), (1, 0), (1, 0), 0.8),
-    # 32 and 20: one round of either; 48 of 128 x 256 tiles in the down projection
+    # 32 and 20: one round of either; one round of K quarters in the down projection
     (THIN_SHAPES[0][0], (0, 1), (0, 1), 0.8),
     # 112 (the most) and 70; 130 and 81, which might be two streaming tiles
     (LayerShape(d=192, E=16, k=2, d_ff=4608, B=4, N=224, dtype="bf16"), (1, 1), (1, 1), 0.02),
     (LayerShape(d=192, E=16, k=2, d_ff=4608, B=4, N=260, dtype="bf16"), (2, 0), (2, 0), 0.02),
+    # 16 and 10: two rounds of K quarters against one of whole K, K short and long
+    (LayerShape(d=320, E=64, k=2, d_ff=1152, B=4, N=128, dtype="bf16"), (1, 0), (1, 0), 0.8),
+    (LayerShape(d=320, E=64, k=2, d_ff=3200, B=1, N=200, dtype="bf16"), (1, 1), (1, 1), 0.8),
     # 172 and 107: one round of 128 x 256 tiles is not beaten
     (LayerShape(d=576, E=8, k=2, d_ff=4608, B=3, N=230, dtype="bf16"), (2, 0), (0, 0), 0.02),
     # 512 and 320, the most that take the expert-wide tiles
